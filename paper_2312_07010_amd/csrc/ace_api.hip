@@ -44,43 +44,123 @@ int64_t nodes_per_axis(int64_t N, int bc)
     return N;
 }
 
-// Newton steps of the device root (ace_device.h, cubic_root) needed for
-// |xi| <= 1: the same start (theta_0 = a + h a (1 - a^2) for h <= 1/2, else
-// theta_0 = a) and the same Newton
-// step are run in long double on a grid of a in (0, 1]; nit is the first step
-// count whose largest relative error against the converged root is below
-// 2^-60 (well under half an ulp, leaving room for the reciprocal estimate and
-// the rounding of the double iteration).
-int newton_iters_for(double h, int start2)
+namespace {
+
+using Real = long double;
+
+Real newton(Real x, Real a, Real H)
 {
-    const long double H = h;
-    const int G = 2048;
-    int need = 1;
-    for (int j = 1; j <= G + 8; ++j) {
-        long double a = (j <= G) ? (long double)j / G : 1.0L - ldexpl(1.0L, -(j - G) * 6);
-        long double ref = a;
-        for (int k = 0; k < 200; ++k) {
-            const long double p = ref + H * (ref * ref * ref - ref) - a;
-            const long double dp = 1.0L + H * (3.0L * ref * ref - 1.0L);
-            const long double nx = ref - p / dp;
-            if (nx == ref) break;
-            ref = nx;
-        }
-        long double x = a;
-        if (H <= 0.5L) {
-            const long double f = a * a * a - a;
-            x = start2 ? a - H * f * (1.0L - H * (3.0L * a * a - 1.0L)) : a + H * a * (1.0L - a * a);
-        }
-        int k = 0;
-        while (fabsl(x - ref) > ldexpl(ref, -60) && k < 60) {
-            const long double p = x + H * (x * x * x - x) - a;
-            const long double dp = 1.0L + H * (3.0L * x * x - 1.0L);
-            x -= p / dp;
-            ++k;
-        }
-        if (k > need) need = k;
+    return x - (x + H * (x * x * x - x) - a) / (1.0L + H * (3.0L * x * x - 1.0L));
+}
+
+// The root for xi = a by Newton's method from x, to the last place.  (For
+// h > 1/2 the slope near 0 is small and the last places may not settle: there
+// until the iteration repeats itself, which newton_steps then does too.)
+Real root_from(Real x, Real a, Real H)
+{
+    const Real tol = H > 0.5L ? 0.0L : 0x1p-63L;
+    for (int k = 0; k < 200; ++k) {
+        const Real nx = newton(x, a, H);
+        if (fabsl(nx - x) <= tol * nx) return nx;
+        x = nx;
     }
-    return need;
+    return x;
+}
+
+// Newton steps from x until it is within 2^-60 of the root th.
+int newton_steps(Real x, Real a, Real th, Real H)
+{
+    int k = 0;
+    for (; fabsl(x - th) > 0x1p-60L * th && k < 60; ++k) x = newton(x, a, H);
+    return k;
+}
+
+// Coefficients (lowest power of w first) of the polynomial S of degree D that
+// interpolates (theta - a) / (a w), a = sqrt(1 - w), theta the root for
+// xi = a, at D + 1 points of w in (0, 1]: the zeros, but for w = 0, of the
+// Chebyshev polynomial of degree D + 2 on the interval that ends at 1 and puts
+// its lowest zero at w = 0.  S's error enters theta times w, and that product
+// has the zero at w = 0 too, so its largest value over [0, 1] is near the
+// least possible.
+void root_polynomial(Real H, int D, Real *p)
+{
+    const Real pi = 3.14159265358979323846264L;
+    Real node[ROOT_MAX_DEG + 1], c[ROOT_MAX_DEG + 1];
+    const Real c0 = cosl(pi / (2 * (D + 2)));
+    for (int j = 0; j <= D; ++j) {
+        const Real w = (cosl(pi * (2 * j + 1) / (2 * (D + 2))) + c0) / (1.0L + c0);
+        const Real a = sqrtl(1.0L - w);
+        node[j] = w;
+        c[j] = (root_from(a, a, H) - a) / (a * w);
+    }
+    for (int k = 1; k <= D; ++k)  // divided differences
+        for (int j = D; j >= k; --j) c[j] = (c[j] - c[j - 1]) / (node[j] - node[j - k]);
+    p[0] = c[D];
+    for (int j = D - 1; j >= 0; --j) {  // p = p (w - node[j]) + c[j]
+        p[D - j] = p[D - j - 1];
+        for (int k = D - j - 1; k >= 1; --k) p[k] = p[k - 1] - node[j] * p[k];
+        p[0] = c[j] - node[j] * p[0];
+    }
+}
+
+}  // namespace
+
+// The device root's choice for p.h (ace_device.h), for 0 < xi <= 1.
+//
+// nit and start2: the Newton steps of root_common without a polynomial.  Both
+// starts (theta_0 = a + h a (1 - a^2), or to second order in h; theta_0 = a
+// for h > 1/2) and the same Newton step are run in long double on a grid of
+// a in (0, 1]; nit is the first step count whose largest relative error
+// against the converged root is below 2^-60 (well under half an ulp, leaving
+// room for the reciprocal estimate and the rounding of the double iteration).
+// The second-order start costs two FMAs more and is used where it saves
+// steps.
+//
+// rv and q: the first of the polynomial variants that stays within 2^-60 of
+// the root over every eighth point of that grid and a few near 0, or 0 (from
+// about dt = 0.45 none does).
+void choose_root(Problem &p)
+{
+    constexpr int G = 2048, NG = G + 8;
+    const Real H = p.h;
+    Real a[NG + 8], th[NG + 8];
+    int need[2] = {1, 1};
+    for (int j = 1; j <= NG; ++j) {
+        a[j - 1] = (j <= G) ? (Real)j / G : 1.0L - ldexpl(1.0L, -(j - G) * 6);
+        // (the root's slope is near 1, so the last point's root plus the step in a is a close start)
+        th[j - 1] = root_from(H <= 0.5L && j > 1 && j <= G ? th[j - 2] + 1.0L / G : a[j - 1], a[j - 1], H);
+        const Real x = a[j - 1], f = x * x * x - x;
+        const Real x1 = H <= 0.5L ? x - H * f : x;
+        const Real x2 = H <= 0.5L ? x - H * f * (1.0L - H * (3.0L * x * x - 1.0L)) : x;
+        need[0] = std::max(need[0], newton_steps(x1, x, th[j - 1], H));
+        need[1] = std::max(need[1], newton_steps(x2, x, th[j - 1], H));
+    }
+    p.start2 = need[1] < need[0];
+    p.nit = need[p.start2];
+    for (int j = 0; j < 8; ++j) {
+        a[NG + j] = ldexpl(1.0L, -12 - 4 * j);
+        th[NG + j] = root_from(a[NG + j], a[NG + j], H);
+    }
+    auto within = [&](int v, const Real *q) {
+        for (int j = 7; j < NG + 8; j += j < G - 1 ? 8 : 1) {
+            const Real w = 1.0L - a[j] * a[j];
+            Real s = q[ROOT_DEG[v]];
+            for (int k = ROOT_DEG[v] - 1; k >= 0; --k) s = s * w + q[k];
+            Real x = a[j] + a[j] * w * s;
+            for (int k = 0; k < ROOT_NEWTON[v]; ++k) x = newton(x, a[j], H);
+            if (!(fabsl(x - th[j]) <= 0x1p-60L * th[j])) return false;
+        }
+        return true;
+    };
+    p.rv = 0;
+    for (int v = 1; v <= ROOT_POLYS && p.h <= 0.3; ++v) {
+        Real q[ROOT_MAX_DEG + 1];
+        root_polynomial(H, ROOT_DEG[v], q);
+        if (!within(v, q)) continue;
+        p.rv = v;
+        for (int k = 0; k <= ROOT_DEG[v]; ++k) p.q[k] = (double)q[k];
+        break;
+    }
 }
 
 // Theorem 2's step condition dt <= 1 - 2 d kappa, 0 < kappa < 1/(2d) (with
@@ -140,15 +220,7 @@ int derive(int d, const int64_t *N, const double *L, const double *R, double eps
         total *= m;
     }
     p.total = total;
-    // the second-order start costs two FMAs more and is used where it saves
-    // Newton steps (e.g. one step instead of two for 1e-3 <= dt <= 5e-3)
-    p.nit = newton_iters_for(p.h, 0);
-    p.start2 = 0;
-    const int nit2 = newton_iters_for(p.h, 1);
-    if (nit2 < p.nit) {
-        p.nit = nit2;
-        p.start2 = 1;
-    }
+    choose_root(p);
     p.scheme = ACE_SCHEME_RLB_MIE;
     set_conditions(p);
     return p.cond_ok ? ACE_OK : ACE_W_CONDITIONS;
@@ -187,7 +259,9 @@ StepCoef coef_of(const Problem &p)
     c.nit = p.nit;
     c.start2 = p.start2;
     c.fex = (p.scheme == ACE_SCHEME_FEX) ? 1 : 0;
+    c.rv = c.fex ? ROOT_FEX : p.rv;
     c.dt = p.dt;
+    memcpy(c.q, p.q, sizeof c.q);
     return c;
 }
 

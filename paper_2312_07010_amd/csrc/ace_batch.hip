@@ -261,7 +261,7 @@ __device__ void batch_regions(const BatchInst &I, double *__restrict__ fa, doubl
     s.M2 = I.M2;
     MonAcc m;
     mon_zero(m);
-    const StepCoef c = coef_vgpr(I.c);
+    const StepCoef c = coef_vgpr<RV>(I.c);
     int64_t done = 0;
     int par = 0;  // 0: the field is in fa
     while (done < nsteps) {
@@ -331,16 +331,10 @@ __global__ __launch_bounds__(kBT) void k_batch(const BatchInst *__restrict__ ins
             constexpr int RYT = REGION == 64 ? 4 : 2;
             auto by_rv = [&](auto BCc) {
                 constexpr int B = decltype(BCc)::value;
-                // every root variant with an instantiation compiled in (the
-                // explicit scheme and more than 3 Newton steps: the run-time root)
-                switch (root_variant(I.c)) {
-                case 1: batch_regions<B, RYT, 1>(I, fa, fb, nsteps, f, tk); break;
-                case 2: batch_regions<B, RYT, 2>(I, fa, fb, nsteps, f, tk); break;
-                case 3: batch_regions<B, RYT, 3>(I, fa, fb, nsteps, f, tk); break;
-                case 5: batch_regions<B, RYT, 5>(I, fa, fb, nsteps, f, tk); break;
-                case 6: batch_regions<B, RYT, 6>(I, fa, fb, nsteps, f, tk); break;
-                default: batch_regions<B, RYT, 0>(I, fa, fb, nsteps, f, tk); break;
-                }
+                with_root(I.c.rv, [&](auto RVc) {  // (batches have no explicit scheme)
+                    constexpr int RV = decltype(RVc)::value;
+                    batch_regions<B, RYT, RV == ROOT_FEX ? 0 : RV>(I, fa, fb, nsteps, f, tk);
+                });
             };
             if (I.bc == BC_HN) by_rv(std::integral_constant<int, BC_HN>());
             else if (I.bc == BC_HD) by_rv(std::integral_constant<int, BC_HD>());

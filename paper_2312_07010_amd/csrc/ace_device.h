@@ -13,6 +13,33 @@
 
 namespace ace {
 
+// Unique real root theta of theta + h (theta^3 - theta) = xi, 0 < h < 1.
+//
+// For |xi| <= 1 (always the case under Theorem 2's conditions) and dt up to
+// 0.05 the root is the polynomial theta = xi + xi w S(w), w = 1 - xi^2:
+// (theta - xi) / (xi w) is an analytic function of w on [0, 1], which the
+// host interpolates with the least degree of ROOT_DEG that brings theta
+// within 2^-60 of the root (choose_root in ace_api.hip).  It takes
+// deg + 3 instructions (6 at dt = 5e-4, 7 at 1e-3), where a Newton step from
+// an expansion of the root takes 12, one of them a quarter-rate reciprocal.
+// It is odd, and exact at 0 and +-1 (xi or w is 0).  Its error is that of the
+// Newton steps it replaced: 0.29 ulp root mean square, at most 0.51 at
+// dt = 5e-4 and 0.53 at 0.05.  Up to dt = 0.45 a polynomial of the same form
+// starts one Newton step.  Measured against Newton steps alone, on the tuned
+// launches: 24.6 to 19.9 ms per 100 monitored steps at 512^3 (dt = 5e-4), 2.65
+// to 2.08 ms per 1000 at 1024^2 (dt = 1e-3).
+//
+// Larger dt takes Newton's method alone, from the expansion of the root in h
+// on a = |xi|, to first order, theta_0 = a - h f(a) = a + h a (1 - a^2), or
+// (c.start2) to second order, theta_0 = a - h f(a) (1 - h f'(a)) with
+// f' = 3 a^2 - 1, and `nit` steps; the host picks the start and nit by
+// running this same iteration in extended precision over a <= 1.  When
+// h > 1/2 the expansion is poor and the start is a itself: the expansion's h
+// is then c.hs = 0, which gives a exactly (a + 0 * (finite) = a), so no lane
+// selects.  For |xi| > 1 (only when the conditions fail) the iteration starts
+// from a, takes the same `nit` steps and continues until the correction stops
+// mattering (at most 200 more steps).
+
 // Reciprocal of a positive double near [0.5, 4]: hardware estimate plus one
 // Newton-Raphson correction.  Only used for Newton steps on the cubic, whose
 // own iteration absorbs the remaining error.
@@ -24,21 +51,6 @@ __device__ __forceinline__ double approx_rcp(double d)
     return r;
 }
 
-// Unique real root of theta + h (theta^3 - theta) = xi for 0 < h < 1.
-// The root map is odd, so the iteration runs on a = |xi| and the sign is
-// restored.  For a <= 1 (always the case under Theorem 2's conditions) it
-// starts from the expansion of the root in h, to first order,
-// theta_0 = a - h f(a) = a + h a (1 - a^2), or (c.start2) to second order,
-// theta_0 = a - h f(a) (1 - h f'(a)) with f' = 3 a^2 - 1, and takes `nit`
-// Newton steps on the cubic; the host picks the start and nit by running
-// this same iteration in extended precision over a <= 1.  When h > 1/2 the
-// expansion is poor and the start is a itself: the expansion's h is then
-// c.hs = 0, which gives a exactly (a + 0 * (finite) = a), so no lane selects.
-// 0 and 1 are exact fixed points of both starts and of the step
-// (f(0) = f(1) = 0), so 0 and +-1 are returned exactly.  For a > 1 (only
-// when the conditions fail) the iteration starts from a instead, takes the
-// same `nit` steps and continues until the correction stops mattering (at
-// most 200 more steps).
 template <bool S2>
 __device__ __forceinline__ double root_start_t(double a, const StepCoef &c)
 {
@@ -56,27 +68,17 @@ __device__ __forceinline__ double root_start(double a, const StepCoef &c)
     return c.start2 ? root_start_t<true>(a, c) : root_start_t<false>(a, c);
 }
 
-// Root variants fixed at compile time: RV = NIT + 4 * START2, with NIT = 1..3
-// Newton steps and START2 the second-order start; RV = 0 takes both from the
-// coefficients at run time.  root_variant() gives a launcher the RV of a
-// coefficient set (0 for combinations without an instantiation: the explicit
-// scheme, and nit > 3).
-__host__ __device__ inline int root_variant(const StepCoef &c)
-{
-    if (c.fex || c.nit < 1 || c.nit > 3 || (c.start2 && c.nit == 3)) return 0;
-    return c.nit + 4 * c.start2;
-}
-
-// A copy of c with omh and oph held in vector registers.  A VOP3
-// instruction reads at most one scalar register, so fma(h3, x^2, omh) of the
-// Newton step and fma(-h3, a^2, oph) of the second-order start, with both
-// coefficients in scalar registers, cost a move at every node; a kernel that
-// passes this copy to the root pays those moves once.  (The empty asm only
-// makes the values look per-lane to the compiler; it emits no instruction.)
+// A copy of c with omh held in vector registers for the variants whose common
+// path takes Newton steps: a VOP3 instruction reads at most one scalar
+// register, so fma(h3, x^2, omh) with both coefficients in scalar registers
+// costs a move at every node; a kernel that passes this copy to the root pays
+// it once.  (The empty asm only makes the value look per-lane to the
+// compiler; it emits no instruction.)
+template <int RV>
 __device__ __forceinline__ StepCoef coef_vgpr(const StepCoef &c)
 {
     StepCoef v = c;
-    asm volatile("" : "+v"(v.omh), "+v"(v.oph));
+    if (RV == 0 || (RV <= ROOT_POLYS && ROOT_NEWTON[RV] > 0)) asm volatile("" : "+v"(v.omh));
     return v;
 }
 
@@ -105,74 +107,78 @@ __device__ __forceinline__ double newton_converge(double x, double a, const Step
     return x;
 }
 
-// (With the step count known only at run time, a lane with a > 1 selects
-// the start a and goes on after the common steps, in less code than the
-// restart of cubic_root_n for kernels that inline many roots; the
-// arithmetic is the same.)
-__device__ __forceinline__ double cubic_root(double xi, const StepCoef &c)
+// The root's two paths for one xi with the variant fixed at compile time:
+// root_common is the root for |xi| <= 1, root_restart the one for |xi| > 1.
+// root_restart is the same code in every variant, and the run-time variant
+// repeats the compiled one's operations, so every kernel rounds the same.
+template <int RV>
+__device__ __forceinline__ double root_common(double xi, const StepCoef &c)
+{
+    if constexpr (RV >= 1 && RV <= ROOT_POLYS) {
+        constexpr int D = ROOT_DEG[RV];
+        const double w = fma(-xi, xi, 1.0);
+        double q = c.q[D];
+#pragma unroll
+        for (int k = D - 1; k >= 0; --k) q = fma(q, w, c.q[k]);
+        double x = fma(xi * w, q, xi);
+#pragma unroll
+        for (int k = 0; k < ROOT_NEWTON[RV]; ++k) x = newton_step(x, xi, c);
+        return x;
+    } else {
+        const double a = fabs(xi);
+        double x = root_start(a, c);
+        for (int k = 0; k < c.nit; ++k) x = newton_step(x, a, c);
+        return copysign(x, xi);
+    }
+}
+
+__device__ __forceinline__ double root_restart(double xi, const StepCoef &c)
 {
     const double a = fabs(xi);
-    double x = a > 1.0 ? a : root_start(a, c);
-    for (int k = 0; k < c.nit; ++k) x = newton_step(x, a, c);
-    if (a > 1.0) x = newton_converge(x, a, c);
-    return copysign(x, xi);
-}
-
-// The root's two paths for a = |xi| with the start and the Newton count
-// fixed at compile time (RV > 0, see root_variant): root_common is the start
-// and NIT steps, the root for a <= 1; root_restart the root for a > 1 (from
-// a, the same NIT steps, then newton_converge).  The iteration and hence
-// every rounding is identical to cubic_root's with the matching
-// coefficients, so the loop unrolls and its constants stay in registers.
-template <int RV>
-__device__ __forceinline__ double root_common(double a, const StepCoef &c)
-{
-    constexpr int NIT = RV > 0 ? (RV & 3) : 1;
-    double x = root_start_t<(RV >= 4)>(a, c);
-#pragma unroll
-    for (int k = 0; k < NIT; ++k) x = newton_step(x, a, c);
-    return x;
-}
-
-template <int RV>
-__device__ __forceinline__ double root_restart(double a, const StepCoef &c)
-{
-    constexpr int NIT = RV > 0 ? (RV & 3) : 1;
     double x = a;
-#pragma unroll
-    for (int k = 0; k < NIT; ++k) x = newton_step(x, a, c);
-    return newton_converge(x, a, c);
+#pragma unroll 1
+    for (int k = 0; k < c.nit; ++k) x = newton_step(x, a, c);
+    return copysign(newton_converge(x, a, c), xi);
 }
 
 template <int RV>
 __device__ __forceinline__ double cubic_root_n(double xi, const StepCoef &c)
 {
-    if (RV <= 0) return cubic_root(xi, c);
-    const double a = fabs(xi);
-    double x = root_common<RV>(a, c);
-    if (a > 1.0) x = root_restart<RV>(a, c);  // this lane's first pass is discarded
-    return copysign(x, xi);
+    double x = root_common<RV>(xi, c);
+    if (fabs(xi) > 1.0) x = root_restart(xi, c);  // this lane's first pass is discarded
+    return x;
 }
 
-// The roots of N values with one test for the a > 1 case (on the largest
+// The root with the variant known only at run time (uniform: one branch).
+__device__ __forceinline__ double cubic_root(double xi, const StepCoef &c)
+{
+    double x = with_root(c.rv, [&](auto RVc) { return root_common<decltype(RVc)::value>(xi, c); });
+    if (fabs(xi) > 1.0) x = root_restart(xi, c);
+    return x;
+}
+
+// The roots of N values with one test for the |xi| > 1 case (on the largest
 // |xi|; a NaN never needs it), so the common paths of the N values form one
 // block that the compiler can interleave.  Same results as cubic_root_n.
 template <int RV, int N>
 __device__ __forceinline__ void cubic_roots_n(const double (&xi)[N], double (&th)[N], const StepCoef &c)
 {
+    if constexpr (RV == ROOT_FEX) {
+#pragma unroll
+        for (int r = 0; r < N; ++r) th[r] = xi[r];
+        return;
+    }
     double amax = fabs(xi[0]);
 #pragma unroll
     for (int r = 0; r < N; ++r) {
-        th[r] = root_common<RV>(fabs(xi[r]), c);
+        th[r] = root_common<RV>(xi[r], c);
         if (r > 0) amax = fmax(amax, fabs(xi[r]));
     }
     if (amax > 1.0) {
 #pragma unroll
         for (int r = 0; r < N; ++r)
-            if (fabs(xi[r]) > 1.0) th[r] = root_restart<RV>(fabs(xi[r]), c);
+            if (fabs(xi[r]) > 1.0) th[r] = root_restart(xi[r], c);
     }
-#pragma unroll
-    for (int r = 0; r < N; ++r) th[r] = copysign(th[r], xi[r]);
 }
 
 // Explicit part xi from the node value p and the sum over axes of its two
@@ -197,6 +203,14 @@ __device__ __forceinline__ double explicit_fex(double p, double nsum, const Step
     return fma(-c.dt, f, t);
 }
 
+// The part of the step before the root: xi, or with ROOT_FEX the explicit
+// scheme's new value (which needs none).
+template <int D, int RV>
+__device__ __forceinline__ double explicit_n(double p, double nsum, const StepCoef &c)
+{
+    return RV == ROOT_FEX ? explicit_fex<D>(p, nsum, c) : explicit_part<D>(p, nsum, c);
+}
+
 template <int D>
 __device__ __forceinline__ double update(double p, double nsum, const StepCoef &c)
 {
@@ -204,12 +218,11 @@ __device__ __forceinline__ double update(double p, double nsum, const StepCoef &
     return cubic_root(explicit_part<D>(p, nsum, c), c);
 }
 
-// (RV > 0 implies the implicit scheme: root_variant gives 0 for the explicit
-// one, so only RV = 0 tests c.fex.)
+// (a launcher may also give the explicit scheme the run-time variant)
 template <int D, int RV>
 __device__ __forceinline__ double update_n(double p, double nsum, const StepCoef &c)
 {
-    if (RV <= 0 && c.fex) return explicit_fex<D>(p, nsum, c);
+    if (RV == ROOT_FEX || (RV == 0 && c.fex)) return explicit_fex<D>(p, nsum, c);
     return cubic_root_n<RV>(explicit_part<D>(p, nsum, c), c);
 }
 

@@ -10,9 +10,12 @@ enum { BC_HN = 0, BC_HD = 1, BC_P = 2 };
 
 // Per-problem coefficients of one step (Sec. 2): kappa = eps^2 dt/dx^2,
 // h = dt/2, omh = 1 - h, oph = 1 + h, h3 = 3 h (the cubic's derivative is
-// 1 - h + 3 h theta^2), nit = Newton steps for |xi| <= 1, start2 = 1 when
-// the root iteration starts from its second-order expansion in h, hs = the h
-// of that expansion (h, or 0 when h > 1/2: the start is then |xi| itself).
+// 1 - h + 3 h theta^2), rv = the root variant (ROOT_*), q = the coefficients
+// of the root's polynomial, lowest power first (variants 1..ROOT_POLYS), nit
+// = Newton steps for |xi| <= 1 without a polynomial, start2 = 1 when that
+// iteration starts from its second-order expansion in h, hs = the h of that
+// expansion (h, or 0 when h > 1/2: the start is then |xi| itself).
+constexpr int ROOT_MAX_DEG = 14;
 struct StepCoef {
     double kappa;
     double h;
@@ -23,8 +26,46 @@ struct StepCoef {
     int nit;
     int start2;
     int fex;    // 1: the fully explicit comparison scheme (no cubic solve)
+    int rv;
     double dt;  // 2h, used by the explicit scheme
+    double q[ROOT_MAX_DEG + 1];
 };
+
+// Root variants, fixed at compile time in the kernels: 1..ROOT_POLYS a
+// polynomial of degree ROOT_DEG[rv] and then ROOT_NEWTON[rv] Newton steps,
+// the first of them that reaches the root's accuracy at the problem's h (up
+// to dt = 5e-4, 2e-3, 0.01, 0.02, 0.05 without a Newton step, 0.3 and 0.45
+// with one); ROOT_FEX the explicit scheme, without a root; 0 Newton with start
+// and step count from the coefficients at run time (larger dt).  Above
+// dt = 0.05 a polynomial alone would take as many instructions as the shorter
+// one and its Newton step, and be less accurate: its correction reaches a
+// tenth of the root there, and with it the correction's own roundings
+// (largest error 0.60 ulp at dt = 0.1, degree 13, against 0.53).
+constexpr int ROOT_POLYS = 7;
+constexpr int ROOT_DEG[ROOT_POLYS + 1] = {0, 3, 4, 6, 8, 10, 10, 14};
+constexpr int ROOT_NEWTON[ROOT_POLYS + 1] = {0, 0, 0, 0, 0, 0, 1, 1};
+constexpr int ROOT_FEX = 8;
+
+// f(integral_constant<int, RV>) with the compiled root variant of c.
+template <int V>
+struct RootTag {
+    static constexpr int value = V;
+};
+template <class F>
+inline __host__ __device__ auto with_root(int rv, F &&f)
+{
+    switch (rv) {
+    case 1: return f(RootTag<1>());
+    case 2: return f(RootTag<2>());
+    case 3: return f(RootTag<3>());
+    case 4: return f(RootTag<4>());
+    case 5: return f(RootTag<5>());
+    case 6: return f(RootTag<6>());
+    case 7: return f(RootTag<7>());
+    case ROOT_FEX: return f(RootTag<ROOT_FEX>());
+    default: return f(RootTag<0>());
+    }
+}
 
 // Shape of one field: M[0] x M[1] x M[2] stored nodes in C order (unused
 // leading axes are 1: a 2D field is 1 x M1 x M2, a 1D field 1 x 1 x M2).

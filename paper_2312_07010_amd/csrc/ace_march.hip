@@ -59,7 +59,7 @@ __device__ __forceinline__ double load_at(const double *__restrict__ in, int64_t
     return (base < 0 || off < 0) ? 0.0 : in[base + off];
 }
 
-template <int BC, bool MON>
+template <int BC, bool MON, int RV>
 __global__ __launch_bounds__(NT) void k_march3d(Shape s, StepCoef c, const double *__restrict__ in,
                                                 double *__restrict__ out,
                                                 double *__restrict__ partials, int tiles_x,
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(NT) void k_march3d(Shape s, StepCoef c, const doubl
             const double nsum = ((q0[r] + q2[r]) + (ym + yp)) + (xm + xp);
             const int64_t y = ybase + r;
             if (xin && y < s.M1) {
-                orow[y * s.M2 + x] = update<3>(p, nsum, c);
+                orow[y * s.M2 + x] = update_n<3, RV>(p, nsum, c);
                 if (MON) {
                     const double dz = q2[r] - p, dy = yp - p, dx = xp - p;
                     double g = fma(dz, dz, fma(dy, dy, dx * dx));
@@ -207,16 +207,18 @@ hipError_t launch_step_march(const Shape &s, const StepCoef &c, const double *in
     const int nchunks = (int)((s.M0 + ZCHUNK - 1) / ZCHUNK);
     const int64_t nblk = (int64_t)tiles_x * tiles_y * nchunks;
     if (nparts) *nparts = nblk;
-#define ACE_MARCH(BB)                                                                          \
-    if (s.bc == BB) {                                                                          \
-        if (partials)                                                                          \
-            hipLaunchKernelGGL((k_march3d<BB, true>), dim3((unsigned)nblk), dim3(NT), 0, st, s, \
-                               c, in, out, partials, tiles_x, tiles_y, nchunks);               \
-        else                                                                                   \
-            hipLaunchKernelGGL((k_march3d<BB, false>), dim3((unsigned)nblk), dim3(NT), 0, st,   \
-                               s, c, in, out, partials, tiles_x, tiles_y, nchunks);            \
-        return hipGetLastError();                                                              \
-    }
+#define ACE_MARCH(BB)                                                                                  \
+    if (s.bc == BB)                                                                                    \
+        return with_root(c.rv, [&](auto RVc) {                                                         \
+            constexpr int RV = decltype(RVc)::value;                                                   \
+            if (partials)                                                                              \
+                hipLaunchKernelGGL((k_march3d<BB, true, RV>), dim3((unsigned)nblk), dim3(NT), 0, st, s, c, \
+                                   in, out, partials, tiles_x, tiles_y, nchunks);                      \
+            else                                                                                       \
+                hipLaunchKernelGGL((k_march3d<BB, false, RV>), dim3((unsigned)nblk), dim3(NT), 0, st, s, c, \
+                                   in, out, partials, tiles_x, tiles_y, nchunks);                      \
+            return hipGetLastError();                                                                  \
+        });
     ACE_MARCH(BC_HN) ACE_MARCH(BC_HD) ACE_MARCH(BC_P)
 #undef ACE_MARCH
     return hipErrorInvalidValue;

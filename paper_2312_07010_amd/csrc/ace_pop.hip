@@ -46,7 +46,7 @@ namespace ace {
 namespace {
 
 struct PopCoef {
-    StepCoef sc;  // root of the cubic (h, omh, h3, nit)
+    StepCoef sc;  // root of the cubic
     double w0, w1;
     double A;     // w_1 (1 - s)/s
     int64_t ps;   // stride between population arrays
@@ -425,17 +425,13 @@ hipError_t launch_pop_t(const Shape &s, const PopCoef &c, const double *fin, dou
 }
 
 template <int D, int BC>
-hipError_t launch_pop_nit(const Shape &s, const PopCoef &c, const double *fin, double *fout, int mode,
+hipError_t launch_pop_root(const Shape &s, const PopCoef &c, const double *fin, double *fout, int mode,
                           double *phi, double *phi_next, hipStream_t st)
 {
-    switch (root_variant(c.sc)) {
-    case 1: return launch_pop_t<D, BC, 1>(s, c, fin, fout, mode, phi, phi_next, st);
-    case 2: return launch_pop_t<D, BC, 2>(s, c, fin, fout, mode, phi, phi_next, st);
-    case 3: return launch_pop_t<D, BC, 3>(s, c, fin, fout, mode, phi, phi_next, st);
-    case 5: return launch_pop_t<D, BC, 5>(s, c, fin, fout, mode, phi, phi_next, st);
-    case 6: return launch_pop_t<D, BC, 6>(s, c, fin, fout, mode, phi, phi_next, st);
-    default: return launch_pop_t<D, BC, 0>(s, c, fin, fout, mode, phi, phi_next, st);
-    }
+    return with_root(c.sc.rv, [&](auto RVc) {
+        constexpr int RV = decltype(RVc)::value;  // (the populations have no explicit scheme)
+        return launch_pop_t<D, BC, RV == ROOT_FEX ? 0 : RV>(s, c, fin, fout, mode, phi, phi_next, st);
+    });
 }
 
 template <int D>
@@ -443,9 +439,9 @@ hipError_t launch_pop_bc(const Shape &s, const PopCoef &c, const double *fin, do
                          double *phi, double *phi_next, hipStream_t st)
 {
     switch (s.bc) {
-    case BC_HN: return launch_pop_nit<D, BC_HN>(s, c, fin, fout, mode, phi, phi_next, st);
-    case BC_HD: return launch_pop_nit<D, BC_HD>(s, c, fin, fout, mode, phi, phi_next, st);
-    case BC_P: return launch_pop_nit<D, BC_P>(s, c, fin, fout, mode, phi, phi_next, st);
+    case BC_HN: return launch_pop_root<D, BC_HN>(s, c, fin, fout, mode, phi, phi_next, st);
+    case BC_HD: return launch_pop_root<D, BC_HD>(s, c, fin, fout, mode, phi, phi_next, st);
+    case BC_P: return launch_pop_root<D, BC_P>(s, c, fin, fout, mode, phi, phi_next, st);
     default: return hipErrorInvalidValue;
     }
 }

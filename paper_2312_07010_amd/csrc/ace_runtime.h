@@ -15,6 +15,8 @@ struct Problem {
     double dx, dt, eps, kappa, h;
     int nit;
     int start2;  // second-order start of the root iteration
+    int rv;      // root variant of the implicit scheme (ROOT_*), and its polynomial
+    double q[ROOT_MAX_DEG + 1];
     int cond_ok;
     int scheme;  // ACE_SCHEME_*
 };
@@ -25,9 +27,8 @@ struct Problem {
 bool log_enabled();
 int hip_status(hipError_t e);
 int64_t nodes_per_axis(int64_t N, int bc);
-// Newton steps that bring the root iteration (first- or second-order start)
-// within 2^-60 of the root for every |xi| in (0, 1].
-int newton_iters_for(double h, int start2);
+// Fills p.nit, p.start2, p.rv and p.q from p.h.
+void choose_root(Problem &p);
 // ACE_OK, ACE_W_CONDITIONS or a negative error.
 int derive(int d, const int64_t *N, const double *L, const double *R, double eps, double dt,
            int bc, Problem &p);

@@ -141,7 +141,7 @@ constexpr int kResThreads = 1024;
 constexpr int kResNodes = (int)((RESIDENT_MAX + kResThreads - 1) / kResThreads);
 
 // The field alternates between two LDS buffers (one barrier per step); RV
-// is the root variant of update_n (0: start and Newton count at run time).
+// is the root variant.
 template <int D, int BC, int RV>
 __global__ __launch_bounds__(kResThreads) void k_resident(Shape s, StepCoef c,
                                                           double *__restrict__ field,
@@ -545,26 +545,17 @@ hipError_t launch_resident(const Shape &s, const StepCoef &c, double *field, int
     if (threads > kResThreads) threads = kResThreads;
     // every node index tid + k * threads must fit in kResNodes slots
     if ((total + threads - 1) / threads > kResNodes) return hipErrorInvalidValue;
-#define ACE_RES_N(DD, BB, NN)                                                                    \
-    hipLaunchKernelGGL((k_resident<DD, BB, NN>), dim3(1), dim3(threads), 0, st, s, c, field, nsteps, \
-                       every, mon);                                                              \
-    return hipGetLastError();
-#define ACE_RES(DD, BB)                          \
-    if (s.d == DD && s.bc == BB) {               \
-        switch (root_variant(c)) {               \
-        case 1: { ACE_RES_N(DD, BB, 1) }         \
-        case 2: { ACE_RES_N(DD, BB, 2) }         \
-        case 3: { ACE_RES_N(DD, BB, 3) }         \
-        case 5: { ACE_RES_N(DD, BB, 5) }         \
-        case 6: { ACE_RES_N(DD, BB, 6) }         \
-        default: { ACE_RES_N(DD, BB, 0) }        \
-        }                                        \
-    }
+#define ACE_RES(DD, BB)                                                                                  \
+    if (s.d == DD && s.bc == BB)                                                                         \
+        return with_root(c.rv, [&](auto RVc) {                                                           \
+            hipLaunchKernelGGL((k_resident<DD, BB, decltype(RVc)::value>), dim3(1), dim3(threads), 0, st, s, \
+                               c, field, nsteps, every, mon);                                            \
+            return hipGetLastError();                                                                    \
+        });
     ACE_RES(1, BC_HN) ACE_RES(1, BC_HD) ACE_RES(1, BC_P)
     ACE_RES(2, BC_HN) ACE_RES(2, BC_HD) ACE_RES(2, BC_P)
     ACE_RES(3, BC_HN) ACE_RES(3, BC_HD) ACE_RES(3, BC_P)
 #undef ACE_RES
-#undef ACE_RES_N
     return hipErrorInvalidValue;
 }
 

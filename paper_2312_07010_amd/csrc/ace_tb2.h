@@ -200,7 +200,7 @@ struct Region {
                 }
                 const double nsum = (ym + yp) + (xm + xp);
                 if constexpr (JOINT) {
-                    xi[r] = explicit_part<2>(p, nsum, c);
+                    xi[r] = explicit_n<2, RV>(p, nsum, c);
                 } else {
                     const double val = update_n<2, RV>(p, nsum, c);
                     nv[r] = val;
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(RX * TRW) void k_tb2(Shape s, StepCoef c, const dou
     g.load(s, in, v);
     MonAcc m;
     mon_zero(m);
-    g.template advance<MON, LEVELS, RV>(s, coef_vgpr(c), v, out, level_stride, EB, m);
+    g.template advance<MON, LEVELS, RV>(s, coef_vgpr<RV>(c), v, out, level_stride, EB, m);
     if (MON) block_reduce_store(m, red, partials + 3 * blockIdx.x);
 }
 
@@ -270,7 +270,6 @@ hipError_t launch_any(const Shape &s, const StepCoef &c, const double *in, doubl
     tiles<TRW, RYT>(s, K, tiles_x, ntiles);
     if (nparts) *nparts = ntiles;
     const bool levels = level_stride > 0;
-    const int rv = root_variant(c);
     auto go = [&](auto BCc, auto RVc) {
         constexpr int B = decltype(BCc)::value, R = decltype(RVc)::value;
         if (partials)
@@ -285,14 +284,7 @@ hipError_t launch_any(const Shape &s, const StepCoef &c, const double *in, doubl
         return hipGetLastError();
     };
     auto by_rv = [&](auto BCc) {
-        switch (rv) {
-        case 1: return go(BCc, std::integral_constant<int, 1>());
-        case 2: return go(BCc, std::integral_constant<int, 2>());
-        case 3: return go(BCc, std::integral_constant<int, 3>());
-        case 5: return go(BCc, std::integral_constant<int, 5>());
-        case 6: return go(BCc, std::integral_constant<int, 6>());
-        default: return go(BCc, std::integral_constant<int, 0>());
-        }
+        return with_root(c.rv, [&](auto RVc) { return go(BCc, RVc); });
     };
     switch (s.bc) {
     case BC_HN: return by_rv(std::integral_constant<int, BC_HN>());

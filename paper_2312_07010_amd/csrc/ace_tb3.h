@@ -127,7 +127,7 @@ __global__ __launch_bounds__(RX * TRW) __attribute__((amdgpu_waves_per_eu(OCC)))
     double *__restrict__ partials, int tiles_x, int tiles_y, int zchunk)
 {
     using G = Geom<K, TRW, RYT>;
-    const StepCoef c = coef_vgpr(c0);
+    const StepCoef c = coef_vgpr<RV>(c0);
     constexpr int NT = G::NT, RH = G::RH, OX = G::OX, OY = G::OY;
     __shared__ double EB[K * 2 * 2 * TRW * RX];  // [level][parity][top|bottom][wavefront][lane]
     __shared__ double red[3 * (NT / 64)];
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(RX * TRW) __attribute__((amdgpu_waves_per_eu(OCC)))
                 }
                 const double nsum = ((zm + zp) + (ym + yp)) + (xmv + xpv);
                 if constexpr (RV > 0) {
-                    xi[r] = explicit_part<3>(p, nsum, c);
+                    xi[r] = explicit_n<3, RV>(p, nsum, c);
                 } else {
                     const double v = update_n<3, RV>(p, nsum, c);
                     if (J < K) dst[r] = v;
@@ -434,25 +434,18 @@ hipError_t launch(const Shape &s, const StepCoef &c, const double *in, double *o
     return hipGetLastError();
 }
 
-// Dispatch over the boundary condition, the monitor flag and the root
-// variants instantiated for this kernel (1: one Newton step, the benchmark's
-// time step; 0: start and step count from the coefficients at run time,
-// with the same rounding).
+// Dispatch over the boundary condition, the monitor flag and the root variant.
 template <int K, int TRW, int RYT, int OCC>
 hipError_t launch_any(const Shape &s, const StepCoef &c, const double *in, double *out,
                       double *partials, int64_t *nparts, int zchunk, hipStream_t st)
 {
-    const int rv = root_variant(c);
     auto go = [&](auto BCc, auto RVc) {
         constexpr int B = decltype(BCc)::value, R = decltype(RVc)::value;
         return partials ? launch<B, true, R, K, TRW, RYT, OCC>(s, c, in, out, partials, nparts, zchunk, st)
                         : launch<B, false, R, K, TRW, RYT, OCC>(s, c, in, out, partials, nparts, zchunk, st);
     };
     auto by_rv = [&](auto BCc) {
-        switch (rv) {
-        case 1: return go(BCc, std::integral_constant<int, 1>());
-        default: return go(BCc, std::integral_constant<int, 0>());
-        }
+        return with_root(c.rv, [&](auto RVc) { return go(BCc, RVc); });
     };
     switch (s.bc) {
     case BC_HN: return by_rv(std::integral_constant<int, BC_HN>());

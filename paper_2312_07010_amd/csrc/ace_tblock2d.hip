@@ -34,8 +34,7 @@ constexpr int BTR = 8;           // thread rows
 constexpr int BRT = BH / BTR;    // rows per thread
 constexpr int BNT = BX * BTR;    // 512 threads
 
-// RV: the root variant of cubic_root_n (start and Newton count fixed at
-// compile time, identical rounding to the run-time path; 0: run time).
+// RV: the root variant (ROOT_*).
 template <int BC, bool MON, bool LEVELS, int RV>
 __global__ __launch_bounds__(BNT) void k_tblock2d(Shape s, StepCoef c, const double *__restrict__ in,
                                                   double *__restrict__ out,
@@ -255,23 +254,14 @@ hipError_t launch_t2(const Shape &s, const StepCoef &c, const double *in, double
 }
 
 template <int BC>
-hipError_t launch_t2_nit(const Shape &s, const StepCoef &c, const double *in, double *out,
+hipError_t launch_t2_root(const Shape &s, const StepCoef &c, const double *in, double *out,
                          double *partials, int K, int tiles_x, int ntiles, int64_t level_stride,
                          bool levels, hipStream_t st)
 {
-    const int rv = root_variant(c);
-    auto go = [&](auto tag) {
-        return launch_t2<BC, decltype(tag)::value>(s, c, in, out, partials, K, tiles_x, ntiles, level_stride,
+    return with_root(c.rv, [&](auto RVc) {
+        return launch_t2<BC, decltype(RVc)::value>(s, c, in, out, partials, K, tiles_x, ntiles, level_stride,
                                                    levels, st);
-    };
-    switch (rv) {
-    case 1: return go(std::integral_constant<int, 1>());
-    case 2: return go(std::integral_constant<int, 2>());
-    case 3: return go(std::integral_constant<int, 3>());
-    case 5: return go(std::integral_constant<int, 5>());
-    case 6: return go(std::integral_constant<int, 6>());
-    default: return go(std::integral_constant<int, 0>());
-    }
+    });
 }
 
 }  // namespace
@@ -287,11 +277,11 @@ hipError_t launch_step_tblock2d(const Shape &s, const StepCoef &c, const double 
     const bool levels = level_stride > 0;
     switch (s.bc) {
     case BC_HN:
-        return launch_t2_nit<BC_HN>(s, c, in, out, partials, K, tiles_x, ntiles, level_stride, levels, st);
+        return launch_t2_root<BC_HN>(s, c, in, out, partials, K, tiles_x, ntiles, level_stride, levels, st);
     case BC_HD:
-        return launch_t2_nit<BC_HD>(s, c, in, out, partials, K, tiles_x, ntiles, level_stride, levels, st);
+        return launch_t2_root<BC_HD>(s, c, in, out, partials, K, tiles_x, ntiles, level_stride, levels, st);
     case BC_P:
-        return launch_t2_nit<BC_P>(s, c, in, out, partials, K, tiles_x, ntiles, level_stride, levels, st);
+        return launch_t2_root<BC_P>(s, c, in, out, partials, K, tiles_x, ntiles, level_stride, levels, st);
     default:
         return hipErrorInvalidValue;
     }
