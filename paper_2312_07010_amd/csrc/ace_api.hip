@@ -279,6 +279,16 @@ double energy_from(const Problem &p, const double *trip)
     return dxd * (trip[0] + cg * trip[1]);
 }
 
+void leave_stream(hipStream_t old, hipStream_t next)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(next, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (hipStreamSynchronize(old) != hipSuccess) (void)hipGetLastError();
+}
+
 int grow(double **ptr, int64_t *cap, int64_t need)
 {
     if (*cap >= need && *ptr) return ACE_OK;
@@ -805,8 +815,10 @@ int ace_params(const ace_solver *s, ace_params_t *q)
 int ace_set_stream(ace_solver *s, void *st)
 {
     if (!s) return ACE_E_ARG;
-    // a replay on the old stream may still use a captured graph
-    if ((hipStream_t)st != s->stream) drop_graphs(s);
+    if ((hipStream_t)st != s->stream) {
+        leave_stream(s->stream, (hipStream_t)st);
+        drop_graphs(s);  // a replay on the old stream may still use a captured graph
+    }
     s->stream = (hipStream_t)st;
     return ACE_OK;
 }
