@@ -86,6 +86,13 @@ hipError_t launch_step_direct(const Shape &s, const StepCoef &c, const double *i
 
 int64_t direct_partials_needed(const Shape &s);  // blocks of launch_step_direct
 
+// 3D: one step with several planes per thread (planes of fewer than 2^28
+// nodes); what launch_step_direct runs in 3D wherever it applies.
+bool col3d_supported(const Shape &s);
+int64_t col3d_partials_needed(const Shape &s);
+hipError_t launch_step_col3d(const Shape &s, const StepCoef &c, const double *in, double *out,
+                             double *partials, int64_t *nparts, hipStream_t st);
+
 // Monitor partials of a field without stepping.
 hipError_t launch_monitor(const Shape &s, const double *in, double *partials,
                           int64_t *nparts, hipStream_t st);

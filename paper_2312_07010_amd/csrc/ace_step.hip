@@ -293,6 +293,7 @@ __global__ __launch_bounds__(1024) void k_sum(const double *__restrict__ x, int6
 hipError_t launch_step_direct(const Shape &s, const StepCoef &c, const double *in, double *out,
                               double *partials, int64_t *nparts, hipStream_t st)
 {
+    if (col3d_supported(s)) return launch_step_col3d(s, c, in, out, partials, nparts, st);
     dim3 grid, block;
     direct_grid(s, grid, block);
     if (nparts) *nparts = (int64_t)grid.x * grid.y * grid.z;
@@ -446,6 +447,7 @@ void monitor_tiles_grid(const Shape &s, int &tiles_x, int &tiles_y, int64_t &nbl
 
 int64_t direct_partials_needed(const Shape &s)
 {
+    if (col3d_supported(s)) return col3d_partials_needed(s);
     dim3 grid, block;
     direct_grid(s, grid, block);
     return (int64_t)grid.x * grid.y * grid.z;
