@@ -384,9 +384,15 @@ struct ace_solver {
     int kernel = ACE_KERNEL_AUTO;
     int depth = 0;
     int zchunk = 32;  // planes per workgroup of the 3D temporal-blocking kernel (0: persistent)
-    int depth2 = 5;   // steps per launch of the 2D temporal-blocking kernel (fastest on 1024^2)
+    int zchunk_fixed = 0;  // 1: zchunk was set or tuned; 0: it follows the variant (tb3_chunks)
+    int depth2 = 5;   // steps per launch of the 2D temporal-blocking kernel
     int tb3 = -1;     // variant of the configurable 3D blocked kernel (-1: the two-step kernel)
     int tb2 = -1;     // variant of the register-resident 2D blocked kernel (-1: the LDS-plane kernel)
+    struct Tail {
+        int v = -1, zchunk = 0;
+    } tail[5];  // 3D: variant and plane chunk of a rest of [i] steps shorter than the handle's depth
+    int rule_kernel = ACE_KERNEL_DIRECT;  // ACE_KERNEL_AUTO without an autotuned choice
+    int plan_fixed = 0;  // 1: a kernel, region or depth was set or tuned, the rule no longer applies
     int tuned_kernel = 0;  // autotuned choice for ACE_KERNEL_AUTO (0: none)
     // reverse mode
     double *ckpt = nullptr;
@@ -418,6 +424,78 @@ struct ace_solver {
 
 namespace {
 
+// ---------------------------------------------------------------------------
+// Launch shape as a rule of the field's size (no timing).  Every choice gives
+// the same result bit for bit; ace_autotune measures instead.
+// ---------------------------------------------------------------------------
+
+// Modelled time (us) of one launch of a blocked kernel: the workgroups of the
+// busiest of 256 CUs, in rounds of those that fit on it together, each round
+// `n` march positions (3D) or levels (2D) and `fill` more to start, at the
+// time of one measured with one workgroup alone on its CU and with two.
+struct BlockModel {
+    int per_cu;
+    double one, two, fill, launch;
+    double us(int64_t workgroups, double n) const
+    {
+        const int64_t busiest = (workgroups + 255) / 256;
+        const int64_t rounds = busiest / per_cu, rest = busiest % per_cu;
+        return launch + (n + fill) * ((double)rounds * (per_cu == 2 ? two : one) + (rest ? one : 0.0));
+    }
+};
+
+// k_tb3: fitted to launches of 64^3 to 512^3 fields at 16 plane chunks
+// (deviation 4 to 7%, 10% for the first variant).
+constexpr BlockModel TB3_MODEL[TB3_VARIANTS] = {{2, 0.93, 1.68, 1.7, 3.6}, {1, 1.78, 0, 2.7, 0.2}, {1, 1.84, 0, 2.1, 0.2},
+                                                {1, 1.33, 0, 2.6, 2.0},    {2, 1.61, 3.23, 0.1, 1.7}, {1, 1.63, 0, 1.0, 2.3},
+                                                {1, 2.19, 0, 1.5, 2.3}};
+constexpr int TB3_CHUNKS[] = {8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 64, 80, 96, 128, 176, 256, 352, 512};
+
+// Modelled us per step of variant v at plane chunk zc: the larger of the
+// march and, on fields past the caches (20 million nodes), 18 bytes of HBM
+// per node and launch at 4.6 TB/s; a tenth of the march orders ties.  The
+// explicit scheme has a quarter fewer instructions.
+double tb3_us(int v, const Shape &s, int zc, bool fex)
+{
+    const int K = TB3_TABLE[v].depth;
+    const double march = TB3_MODEL[v].us(tb3_partials_needed(v, s, zc),
+                                         std::min<double>(zc, (double)s.M0) + 2 * K - 2) * (fex ? 0.8 : 1.0);
+    const double nodes = (double)s.M0 * (double)s.M1 * (double)s.M2;
+    const double hbm = nodes > 2e7 ? nodes * 18.0 / 4.6e6 : 0.0;
+    return (std::max(march, hbm) + 0.1 * march) / K;
+}
+
+// Plane chunks of variant v, the least modelled time first.
+std::vector<int> tb3_chunks(int v, const Shape &s, bool fex)
+{
+    std::vector<std::pair<double, int>> t;
+    for (int zc : TB3_CHUNKS)
+        if (zc <= std::max<int64_t>(s.M0, 8)) t.push_back({tb3_us(v, s, zc, fex), zc});
+    std::stable_sort(t.begin(), t.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
+    std::vector<int> out;
+    for (const auto &x : t) out.push_back(x.second);
+    return out;
+}
+
+// One step of a 3D field: the column kernel (its time is 2.4 us and 16 bytes
+// per node from the caches at 4.4 TB/s: 5.9 us at 96^3, 10.8 at 130^3, 16 at
+// 160^3), or past 20 million nodes, where the marching kernel reads each
+// plane of HBM once, that one (232 against 324 us at 400^3, 430 against 667
+// at 512^3; 72 against 58 at 256^3).
+constexpr double kColumnUs = 2.4, kColumnUsPerNode = 3.6e-6;
+
+int one_step_kernel(const Shape &s)
+{
+    if (s.d == 3 && march_supported(s) && s.M0 * s.M1 * s.M2 > 20000000) return ACE_KERNEL_MARCH;
+    return ACE_KERNEL_DIRECT;
+}
+
+// k_tb2: fitted to 19 fields from 30 x 30 to 3000 x 3000 at depths 2 to 12
+// (deviation 4 to 7%); a level of the 32-row regions is bound by the rows of
+// one CU (0.28 us), so small fields take the deepest launch.
+constexpr BlockModel TB2_MODEL[TB2_VARIANTS] = {{2, 0.295, 0.452, 2.7, 3.45}, {1, 0.281, 0, 2.9, 3.28},
+                                                {1, 0.622, 0, 1.2, 3.73}, {2, 0.133, 0.225, 3.8, 3.02}};
+
 bool tblock_applies(const ace_solver *s)
 {
     return (s->p.d == 3 && tblock_supported(s->shape)) || (s->p.d == 2 && tblock2d_supported(s->shape));
@@ -427,11 +505,7 @@ int effective_kernel(const ace_solver *s)
 {
     int k = s->kernel;
     if (k == ACE_KERNEL_AUTO) k = s->tuned_kernel;
-    if (k == ACE_KERNEL_AUTO) {
-        if (s->p.total <= RESIDENT_MAX) k = ACE_KERNEL_RESIDENT;
-        else if (s->p.d >= 2) k = ACE_KERNEL_TBLOCK;
-        else k = ACE_KERNEL_DIRECT;
-    }
+    if (k == ACE_KERNEL_AUTO) k = s->rule_kernel;
     if (k == ACE_KERNEL_RESIDENT && s->p.total > RESIDENT_MAX) k = ACE_KERNEL_DIRECT;
     if (k == ACE_KERNEL_TBLOCK && !tblock_applies(s)) k = ACE_KERNEL_DIRECT;
     if (k == ACE_KERNEL_MARCH && !march_supported(s->shape)) k = ACE_KERNEL_DIRECT;
@@ -463,10 +537,66 @@ int64_t blocked2d_blocks(const ace_solver *s, int K)
     return use_tb2(s) ? tb2_blocks(s->tb2, s->shape, K) : tblock2d_blocks(s->shape, K);
 }
 
-bool use_tb3(const ace_solver *s, int kernel, int64_t remaining)
+// The plane chunk of the handle's variant, unless it was set or tuned.
+void follow_chunk(ace_solver *s)
 {
-    return kernel == ACE_KERNEL_TBLOCK && s->p.d == 3 && s->tb3 >= 0 && tb3_supported(s->shape) &&
-           remaining >= TB3_TABLE[s->tb3].depth;
+    if (s->p.d != 3 || s->zchunk_fixed) return;
+    s->zchunk = (s->tb3 >= 0 && tb3_supported(s->shape)) ? tb3_chunks(s->tb3, s->shape, s->coef.fex)[0] : 32;
+}
+
+// The rule's kernel and launch shape for a new handle.
+// (Called again when the scheme changes: then only the tails, if the launch
+// shape was set or tuned since.)
+void plan_launch(ace_solver *s)
+{
+    const Shape &f = s->shape;
+    if (!s->plan_fixed) s->rule_kernel = s->p.total <= RESIDENT_MAX ? ACE_KERNEL_RESIDENT : ACE_KERNEL_DIRECT;
+    double best = 1e300;
+    if (f.d == 2 && tb2_supported(f) && !s->plan_fixed) {
+        for (int v = 0; v < TB2_VARIANTS; ++v)
+            for (int K = 2; K <= std::min(tb2_max_depth(v), tblock2d_max_depth()); ++K) {
+                const double us = TB2_MODEL[v].us(tb2_blocks(v, f, K), K) / K;
+                if (tb2_max_depth(v) < tblock2d_max_depth() || us >= best) continue;  // (any depth stays settable)
+                best = us;
+                s->tb2 = v;
+                s->depth2 = K;
+            }
+    }
+    // (2D: the LDS-resident kernel takes 0.52 us per step at 40 x 40 and 1.03
+    // at 64 x 64, the blocked one 0.65 at both)
+    if (f.d == 2 && s->p.total > 2048 && tblock2d_supported(f)) s->rule_kernel = ACE_KERNEL_TBLOCK;
+    if (f.d == 3 && tb3_supported(f)) {
+        double of_depth[5] = {1e300, 1e300, 1e300, 1e300, 1e300};
+        for (int v = 0; v < TB3_VARIANTS; ++v) {
+            const int zc = tb3_chunks(v, f, s->coef.fex)[0], K = TB3_TABLE[v].depth;
+            const double us = tb3_us(v, f, zc, s->coef.fex);
+            if (us < of_depth[K]) {
+                of_depth[K] = us;
+                s->tail[K].v = v;
+                s->tail[K].zchunk = zc;
+            }
+            if (us >= best || s->plan_fixed) continue;
+            best = us;
+            s->tb3 = v;
+            if (!s->zchunk_fixed) s->zchunk = zc;
+        }
+    }
+    if (s->plan_fixed) return;
+    if (f.d == 3 && s->rule_kernel == ACE_KERNEL_DIRECT &&
+        kColumnUs + kColumnUsPerNode * (double)s->p.total > best)
+        s->rule_kernel = ACE_KERNEL_TBLOCK;
+}
+
+// The k_tb3 variant for a launch of `kernel` with `remaining` steps to go (-1:
+// none): the handle's, or for a shorter rest of the run the fastest of that
+// depth at its own plane chunk.
+int tb3_for(const ace_solver *s, int kernel, int64_t remaining, int *zc)
+{
+    if (kernel != ACE_KERNEL_TBLOCK || s->p.d != 3 || s->tb3 < 0 || !tb3_supported(s->shape)) return -1;
+    *zc = s->zchunk;
+    if (remaining >= TB3_TABLE[s->tb3].depth) return s->tb3;
+    *zc = s->tail[remaining].zchunk;
+    return s->tail[remaining].v;
 }
 
 // One launch from buf[cur] into buf[cur^1] advancing 1 step, or up to
@@ -479,9 +609,12 @@ int64_t partials_for(const ace_solver *s, int kernel, int64_t remaining)
 {
     if (kernel == ACE_KERNEL_TBLOCK && s->p.d == 2)
         return blocked2d_blocks(s, (int)std::min<int64_t>(steps_per_launch_of(s, kernel), remaining));
-    if (use_tb3(s, kernel, remaining)) return tb3_partials_needed(s->tb3, s->shape, s->zchunk);
+    int zc = 0;
+    const int v = tb3_for(s, kernel, remaining, &zc);
+    if (v >= 0) return tb3_partials_needed(v, s->shape, zc);
     if (kernel == ACE_KERNEL_TBLOCK && remaining >= 2) return tblock_partials_needed(s->shape, s->zchunk);
-    if (kernel == ACE_KERNEL_MARCH || kernel == ACE_KERNEL_TBLOCK) return march_partials_needed(s->shape);
+    if (kernel == ACE_KERNEL_TBLOCK) kernel = one_step_kernel(s->shape);
+    if (kernel == ACE_KERNEL_MARCH) return march_partials_needed(s->shape);
     return direct_partials_needed(s->shape);
 }
 
@@ -492,17 +625,19 @@ int launch_steps(ace_solver *s, int kernel, int64_t remaining, bool want_mon, in
     double *parts = want_mon ? s->partials : nullptr;
     if (want_mon && 3 * partials_for(s, kernel, remaining) > s->partials_cap) return ACE_E_STATE;
     hipError_t e;
-    int taken = 1;
+    int taken = 1, zc = 0;
+    const int v3 = tb3_for(s, kernel, remaining, &zc);
     if (kernel == ACE_KERNEL_TBLOCK && s->p.d == 2) {
         taken = (int)std::min<int64_t>(steps_per_launch_of(s, kernel), remaining);
         e = launch_blocked2d(s, in, out, parts, nparts, taken, 0, s->stream);
-    } else if (use_tb3(s, kernel, remaining)) {
-        e = launch_step_tb3(s->tb3, s->shape, s->coef, in, out, parts, nparts, s->zchunk, s->stream);
-        taken = TB3_TABLE[s->tb3].depth;
+    } else if (v3 >= 0) {
+        e = launch_step_tb3(v3, s->shape, s->coef, in, out, parts, nparts, zc, s->stream);
+        taken = TB3_TABLE[v3].depth;
     } else if (kernel == ACE_KERNEL_TBLOCK && remaining >= 2) {
         e = launch_step_tblock2(s->shape, s->coef, in, out, parts, nparts, s->zchunk, s->stream);
         taken = 2;
-    } else if (kernel == ACE_KERNEL_MARCH || kernel == ACE_KERNEL_TBLOCK) {
+    } else if (kernel == ACE_KERNEL_MARCH ||
+               (kernel == ACE_KERNEL_TBLOCK && one_step_kernel(s->shape) == ACE_KERNEL_MARCH)) {
         e = launch_step_march(s->shape, s->coef, in, out, parts, nparts, s->stream);
     } else {
         e = launch_step_direct(s->shape, s->coef, in, out, parts, nparts, s->stream);
@@ -676,6 +811,8 @@ void load_tuning(ace_solver *s)
             v3 < TB3_VARIANTS && v2 >= -1 && v2 < TB2_VARIANTS) {
             s->tuned_kernel = k;
             s->zchunk = zc;
+            s->zchunk_fixed = 1;
+            s->plan_fixed = 1;
             s->depth2 = k2;
             s->tb3 = v3;
             s->tb2 = v2;
@@ -730,6 +867,7 @@ int ace_create(int d, const int64_t *N, const double *L, const double *R, double
         ace_destroy(s);
         return arc;
     }
+    plan_launch(s);
     load_tuning(s);
     hipError_t e = hipMalloc((void **)&s->gsum, 4 * sizeof(double));
     if (e != hipSuccess) {
@@ -871,6 +1009,7 @@ int ace_set_scheme(ace_solver *s, int scheme)
     s->p.scheme = scheme;
     set_conditions(s->p);
     s->coef = coef_of(s->p);
+    plan_launch(s);
     s->ck_count = 0;
     drop_graphs(s);
     return s->p.cond_ok ? ACE_OK : ACE_W_CONDITIONS;
@@ -884,6 +1023,8 @@ int ace_set_kernel(ace_solver *s, int kernel, int depth)
         if (s->p.d == 2 && depth > tblock2d_max_depth()) return ACE_E_ARG;
         if (s->p.d == 2) s->depth2 = depth;
         if (s->p.d == 3) s->tb3 = (depth == 2) ? -1 : (depth == 3 ? TB3_DEFAULT_DEPTH3 : TB3_DEFAULT_DEPTH4);
+        s->plan_fixed = 1;
+        follow_chunk(s);
     }
     s->kernel = kernel;
     s->depth = depth;
@@ -895,11 +1036,15 @@ int ace_set_region3d(ace_solver *s, int depth, int rows, int rows_per_thread)
     if (!s || s->p.d != 3) return ACE_E_ARG;
     if (depth == 2 && rows == 0 && rows_per_thread == 0) {
         s->tb3 = -1;
+        s->plan_fixed = 1;
+        follow_chunk(s);
         return ACE_OK;
     }
     const int v = tb3_find(depth, rows, rows_per_thread);
     if (v < 0) return ACE_E_ARG;
     s->tb3 = v;
+    s->plan_fixed = 1;
+    follow_chunk(s);
     return ACE_OK;
 }
 
@@ -923,11 +1068,13 @@ int ace_set_region2d(ace_solver *s, int rows, int rows_per_thread)
     if (!s || s->p.d != 2) return ACE_E_ARG;
     if (rows == 0 && rows_per_thread == 0) {
         s->tb2 = -1;
+        s->plan_fixed = 1;
         return ACE_OK;
     }
     const int v = tb2_find(rows, rows_per_thread);
     if (v < 0) return ACE_E_ARG;
     s->tb2 = v;
+    s->plan_fixed = 1;
     return ACE_OK;
 }
 
@@ -944,6 +1091,7 @@ int ace_set_plane_chunk(ace_solver *s, int planes)
     if (!s || s->p.d != 3 || (planes != 0 && (planes < TBLOCK_MIN_ZCHUNK || planes > 4096)))
         return ACE_E_ARG;
     s->zchunk = planes;
+    s->zchunk_fixed = 1;
     return ACE_OK;
 }
 
@@ -1154,16 +1302,20 @@ int ace_autotune(ace_solver *s, int64_t trial_steps, char *json, size_t cap)
     if (s->p.total <= RESIDENT_MAX) cands.push_back({ACE_KERNEL_RESIDENT, z0c, k0, v30, v20});
     if (march_supported(s->shape)) cands.push_back({ACE_KERNEL_MARCH, z0c, k0, v30, v20});
     if (s->p.d == 3 && tblock_supported(s->shape))
-        for (int zc : {0, 16, 24, 32, 40, 48, 64, 128})  // 0: persistent grid
+        for (int zc : {0, 32})  // 0: persistent grid
             if (zc <= std::max<int64_t>(s->shape.M0, 16)) cands.push_back({ACE_KERNEL_TBLOCK, zc, k0, -1, v20});
-    // the configurable 3D kernel: every depth and region shape, fewer plane
-    // chunks.  Long chunks matter when a chunk count leaves the last round of
-    // one-workgroup-per-CU launches half empty (512^3 at depth 3: 117 tiles x
-    // 8 chunks of 64 = 936 workgroups on 256 CUs, against 234 of 256 planes).
+    // the configurable 3D kernel: every depth and region shape, as a
+    // persistent grid and at the three plane chunks with the least modelled
+    // time.  The deep 48-row region is timed where it has workgroups for half
+    // of the CUs (on smaller fields it never came near the others).
     if (s->p.d == 3 && tb3_supported(s->shape))
-        for (int v = 0; v < TB3_VARIANTS; ++v)
-            for (int zc : {0, 16, 32, 64, 128, 256})
-                if (zc <= std::max<int64_t>(s->shape.M0, 16)) cands.push_back({ACE_KERNEL_TBLOCK, zc, k0, v, v20});
+        for (int v = 0; v < TB3_VARIANTS; ++v) {
+            if (v >= TB3_NAMED && tb3_partials_needed(v, s->shape, 16) < 128) continue;
+            std::vector<int> zcs = tb3_chunks(v, s->shape, s->coef.fex);
+            zcs.resize(std::min<size_t>(zcs.size(), 3));
+            zcs.push_back(0);
+            for (int zc : zcs) cands.push_back({ACE_KERNEL_TBLOCK, zc, k0, v, v20});
+        }
     if (s->p.d == 2 && tblock2d_supported(s->shape)) {
         for (int k2 : {1, 2, 3, 4, 5, 6, 8, 10, 12})
             if (k2 <= tblock2d_max_depth()) cands.push_back({ACE_KERNEL_TBLOCK, z0c, k2, v30, -1});
@@ -1256,6 +1408,8 @@ int ace_autotune(ace_solver *s, int64_t trial_steps, char *json, size_t cap)
     if (rc < 0) return rc;
     s->tuned_kernel = best.kernel;
     s->zchunk = best.zchunk;
+    s->zchunk_fixed = 1;
+    s->plan_fixed = 1;
     s->depth2 = best.depth2;
     s->tb3 = best.tb3;
     s->tb2 = best.tb2;
@@ -1368,7 +1522,7 @@ int ace_backward(ace_solver *s, const double *lambdaT, double *dphi0, double *de
     int k = effective_kernel(s);
     if (k == ACE_KERNEL_RESIDENT) k = ACE_KERNEL_DIRECT;
     const bool blocked2d = (k == ACE_KERNEL_TBLOCK && s->p.d == 2);
-    if (k == ACE_KERNEL_TBLOCK && !blocked2d) k = ACE_KERNEL_MARCH;
+    if (k == ACE_KERNEL_TBLOCK && !blocked2d) k = one_step_kernel(s->shape);
     for (int64_t j = s->ck_count - 1; j >= 0; --j) {
         const int b = (int)(j & 1);
         double *seg = s->seg + b * (every + 1) * total;
@@ -1400,12 +1554,14 @@ int ace_backward(ace_solver *s, const double *lambdaT, double *dphi0, double *de
         ACE_HIP(hipStreamWaitEvent(s->stream, s->ev_rec[b], 0));
         int64_t parts = 0;  // partial sums of dL/dkappa written for this segment
         if (blocked2d) {
-            const int64_t nb = tblock2d_blocks(s->shape, s->depth2);
+            // (deeper launches leave the 32-row regions of the reverse sweep small tiles)
+            const int rev = std::min(s->depth2, 8);
+            const int64_t nb = tblock2d_blocks(s->shape, rev);
             for (int64_t i = n; i > 0;) {  // K transposed steps per launch
-                const int K = (int)std::min<int64_t>(s->depth2, i);
+                const int K = (int)std::min<int64_t>(rev, i);
                 ACE_HIP(launch_adjoint_tblock2d(s->shape, s->coef, lam[lc], seg + (i - K) * total, total,
                                                 lam[lc ^ 1], s->gpart + parts, K, s->stream));
-                parts += (K == s->depth2) ? nb : tblock2d_blocks(s->shape, K);
+                parts += (K == rev) ? nb : tblock2d_blocks(s->shape, K);
                 lc ^= 1;
                 i -= K;
             }

@@ -142,9 +142,11 @@ constexpr int TBLOCK_MIN_ZCHUNK = 8;
 struct Tb3Variant {
     int depth, rows, rpt;
 };
-constexpr int TB3_VARIANTS = 6;
-constexpr Tb3Variant TB3_TABLE[TB3_VARIANTS] = {{2, 32, 4}, {3, 48, 3}, {3, 48, 4},
-                                                {3, 32, 2}, {4, 32, 4}, {4, 32, 2}};
+// The last one is not named by ace_set_region3d: only the library's own choice
+// takes it.
+constexpr int TB3_VARIANTS = 7, TB3_NAMED = 6;
+constexpr Tb3Variant TB3_TABLE[TB3_VARIANTS] = {{2, 32, 4}, {3, 48, 3}, {3, 48, 4}, {3, 32, 2},
+                                                {4, 32, 4}, {4, 32, 2}, {4, 48, 3}};
 constexpr int TB3_DEFAULT_DEPTH3 = 1, TB3_DEFAULT_DEPTH4 = 5;  // variants ace_set_kernel picks
 hipError_t launch_step_tb3(int v, const Shape &s, const StepCoef &c, const double *in, double *out,
                            double *partials, int64_t *nparts, int zchunk, hipStream_t st);

@@ -19,12 +19,15 @@ hipError_t launch_tb3_v4(const Shape &, const StepCoef &, const double *, double
                          int, hipStream_t);
 hipError_t launch_tb3_v5(const Shape &, const StepCoef &, const double *, double *, double *, int64_t *,
                          int, hipStream_t);
+hipError_t launch_tb3_v6(const Shape &, const StepCoef &, const double *, double *, double *, int64_t *,
+                         int, hipStream_t);
 int64_t tb3_partials_v0(const Shape &, int);
 int64_t tb3_partials_v1(const Shape &, int);
 int64_t tb3_partials_v2(const Shape &, int);
 int64_t tb3_partials_v3(const Shape &, int);
 int64_t tb3_partials_v4(const Shape &, int);
 int64_t tb3_partials_v5(const Shape &, int);
+int64_t tb3_partials_v6(const Shape &, int);
 
 bool tb3_supported(const Shape &s)
 {
@@ -36,7 +39,7 @@ bool tb3_supported(const Shape &s)
 
 int tb3_find(int depth, int rows, int rpt)
 {
-    for (int v = 0; v < TB3_VARIANTS; ++v)
+    for (int v = 0; v < TB3_NAMED; ++v)
         if (TB3_TABLE[v].depth == depth && TB3_TABLE[v].rows == rows && TB3_TABLE[v].rpt == rpt) return v;
     return -1;
 }
@@ -52,6 +55,7 @@ hipError_t launch_step_tb3(int v, const Shape &s, const StepCoef &c, const doubl
     case 3: return launch_tb3_v3(s, c, in, out, partials, nparts, zchunk, st);
     case 4: return launch_tb3_v4(s, c, in, out, partials, nparts, zchunk, st);
     case 5: return launch_tb3_v5(s, c, in, out, partials, nparts, zchunk, st);
+    case 6: return launch_tb3_v6(s, c, in, out, partials, nparts, zchunk, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -65,6 +69,7 @@ int64_t tb3_partials_needed(int v, const Shape &s, int zchunk)
     case 3: return tb3_partials_v3(s, zchunk);
     case 4: return tb3_partials_v4(s, zchunk);
     case 5: return tb3_partials_v5(s, zchunk);
+    case 6: return tb3_partials_v6(s, zchunk);
     default: return 0;
     }
 }
