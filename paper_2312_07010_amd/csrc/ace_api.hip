@@ -365,6 +365,12 @@ double *scratch_of(int dev)
 // solver handle
 // ---------------------------------------------------------------------------
 
+// 1D: nodes per lane and steps per launch (or per exchange).
+struct Shape1 {
+    int R = 1, K = 8;
+    double ns = 1e300;  // modelled time per step
+};
+
 struct ace_solver {
     Problem p;
     Shape shape;
@@ -391,6 +397,7 @@ struct ace_solver {
     struct Tail {
         int v = -1, zchunk = 0;
     } tail[5];  // 3D: variant and plane chunk of a rest of [i] steps shorter than the handle's depth
+    Shape1 tb1, res1;  // 1D: the blocked and the one-workgroup kernel's shapes
     int rule_kernel = ACE_KERNEL_DIRECT;  // ACE_KERNEL_AUTO without an autotuned choice
     int plan_fixed = 0;  // 1: a kernel, region or depth was set or tuned, the rule no longer applies
     int tuned_kernel = 0;  // autotuned choice for ACE_KERNEL_AUTO (0: none)
@@ -496,8 +503,57 @@ int one_step_kernel(const Shape &s)
 constexpr BlockModel TB2_MODEL[TB2_VARIANTS] = {{2, 0.295, 0.452, 2.7, 3.45}, {1, 0.281, 0, 2.9, 3.28},
                                                 {1, 0.622, 0, 1.2, 3.73}, {2, 0.133, 0.225, 3.8, 3.02}};
 
+// ns per step of a wavefront of R = 1, 2, 4 nodes per lane: alone on its SIMD
+// (the dependent chain of a node) and each of several (their instructions).
+constexpr double TB1_CHAIN[3] = {64, 86, 140}, TB1_ISSUE[3] = {43, 68, 120};
+
+template <class F>
+Shape1 best_shape1(F &&ns)
+{
+    Shape1 best;
+    for (int i = 0; i < 3; ++i)
+        for (int R = 1 << i, K = 8; K <= 32 * R - 4; K += 4) {
+            const double t = ns(i, R, K);
+            if (t < best.ns) best = Shape1{R, K, t};
+        }
+    return best;
+}
+
+// One wavefront per workgroup, launches 2 us apart.  With more than about 700
+// wavefronts some of the 1024 SIMDs hold two.  (Measured: 1000 to 8000 nodes
+// 122 to 130 ns at 2 nodes and 56 steps, 20011 138 at 2 / 48, 10^5 185 at
+// 4 / 56, 10^6 692 at 4 / 28; the one-node-per-thread kernel takes 2.2 us.)
+Shape1 tb1_shape(const Shape &s)
+{
+    return best_shape1([&](int i, int R, int K) {
+        const double waves = (double)tb1_blocks(s, R, K);
+        const double per = waves <= 700 ? 1.0 : ceil(waves / 1024.0 + (waves < 1024 ? 1.0 : 0.0));
+        return 2000.0 / K + std::max(TB1_CHAIN[i], per * TB1_ISSUE[i]);
+    });
+}
+
+// All in one workgroup of up to 16 wavefronts on four SIMDs, an exchange
+// 320 ns (256 nodes: 101 ns per step at 1 node and 16 steps; 1500: 250).
+Shape1 resident1_shape(const Shape &s)
+{
+    return best_shape1([&](int i, int R, int K) {
+        const int64_t waves = tb1_blocks(s, R, K);
+        if (waves > 16) return 1e300;
+        return 320.0 / K + std::max(TB1_CHAIN[i] + 10.0, (double)((waves + 3) / 4) * TB1_ISSUE[i]);
+    });
+}
+
+// Whether run_monitored of a 1D field at this interval is better in one
+// workgroup (a monitor costs it about 1.2 us, the launches of their own 5).
+bool monitor_resident1(const ace_solver *s, int64_t every)
+{
+    if (s->p.total > RESIDENT_MAX || s->res1.ns >= 1e300) return false;
+    return 1200.0 + (double)every * s->res1.ns < 5000.0 + (double)every * s->tb1.ns;
+}
+
 bool tblock_applies(const ace_solver *s)
 {
+    if (s->p.d == 1) return tb1_supported(s->shape);
     return (s->p.d == 3 && tblock_supported(s->shape)) || (s->p.d == 2 && tblock2d_supported(s->shape));
 }
 
@@ -519,6 +575,7 @@ bool use_tb2(const ace_solver *s) { return s->p.d == 2 && s->tb2 >= 0 && tb2_sup
 int steps_per_launch_of(const ace_solver *s, int kernel)
 {
     if (kernel != ACE_KERNEL_TBLOCK) return 1;
+    if (s->p.d == 1) return s->tb1.K;
     if (s->p.d == 3) return (s->tb3 >= 0 && tb3_supported(s->shape)) ? TB3_TABLE[s->tb3].depth : 2;
     return use_tb2(s) ? std::min(s->depth2, tb2_max_depth(s->tb2)) : s->depth2;
 }
@@ -561,6 +618,12 @@ void plan_launch(ace_solver *s)
                 s->tb2 = v;
                 s->depth2 = K;
             }
+    }
+    if (f.d == 1 && tb1_supported(f)) {
+        s->tb1 = tb1_shape(f);
+        if (f.M2 <= RESIDENT_MAX) s->res1 = resident1_shape(f);
+        if (!s->plan_fixed)
+            s->rule_kernel = s->res1.ns <= s->tb1.ns ? ACE_KERNEL_RESIDENT : ACE_KERNEL_TBLOCK;
     }
     // (2D: the LDS-resident kernel takes 0.52 us per step at 40 x 40 and 1.03
     // at 64 x 64, the blocked one 0.65 at both)
@@ -607,6 +670,8 @@ int tb3_for(const ace_solver *s, int kernel, int64_t remaining, int *zc)
 // launch_steps makes for `remaining` steps).
 int64_t partials_for(const ace_solver *s, int kernel, int64_t remaining)
 {
+    if (kernel == ACE_KERNEL_TBLOCK && s->p.d == 1)
+        return tb1_blocks(s->shape, s->tb1.R, (int)std::min<int64_t>(s->tb1.K, remaining));
     if (kernel == ACE_KERNEL_TBLOCK && s->p.d == 2)
         return blocked2d_blocks(s, (int)std::min<int64_t>(steps_per_launch_of(s, kernel), remaining));
     int zc = 0;
@@ -627,7 +692,10 @@ int launch_steps(ace_solver *s, int kernel, int64_t remaining, bool want_mon, in
     hipError_t e;
     int taken = 1, zc = 0;
     const int v3 = tb3_for(s, kernel, remaining, &zc);
-    if (kernel == ACE_KERNEL_TBLOCK && s->p.d == 2) {
+    if (kernel == ACE_KERNEL_TBLOCK && s->p.d == 1) {
+        taken = (int)std::min<int64_t>(s->tb1.K, remaining);
+        e = launch_step_tb1(s->shape, s->coef, in, out, parts, nparts, s->tb1.R, taken, s->stream);
+    } else if (kernel == ACE_KERNEL_TBLOCK && s->p.d == 2) {
         taken = (int)std::min<int64_t>(steps_per_launch_of(s, kernel), remaining);
         e = launch_blocked2d(s, in, out, parts, nparts, taken, 0, s->stream);
     } else if (v3 >= 0) {
@@ -646,6 +714,15 @@ int launch_steps(ace_solver *s, int kernel, int64_t remaining, bool want_mon, in
     s->cur ^= 1;
     s->steps += taken;
     return taken;
+}
+
+// The whole run of `nsteps` in one workgroup (total <= RESIDENT_MAX).
+hipError_t run_resident(const ace_solver *s, int64_t nsteps, int64_t every)
+{
+    double *f = s->buf[s->cur], *mon = every > 0 ? s->mon : nullptr;
+    if (s->res1.ns < 1e300)
+        return launch_resident1(s->shape, s->coef, f, nsteps, every, mon, s->res1.R, s->res1.K, s->stream);
+    return launch_resident(s->shape, s->coef, f, nsteps, every, mon, s->stream);
 }
 
 void drop_graphs(ace_solver *s)
@@ -714,7 +791,7 @@ int advance(ace_solver *s, int64_t nsteps)
     if (nsteps <= 0) return ACE_OK;
     const int k = effective_kernel(s);
     if (k == ACE_KERNEL_RESIDENT) {
-        ACE_HIP(launch_resident(s->shape, s->coef, s->buf[s->cur], nsteps, 0, nullptr, s->stream));
+        ACE_HIP(run_resident(s, nsteps, 0));
         s->steps += nsteps;
         return ACE_OK;
     }
@@ -748,6 +825,10 @@ int alloc_fields(ace_solver *s)
     // one partial triple per workgroup of any monitored launch
     int64_t need2 = 3 * std::max<int64_t>(
         std::max<int64_t>(monitor_partials_needed(s->shape), direct_partials_needed(s->shape)), 1);
+    if (tb1_supported(s->shape)) {
+        const Shape1 t = tb1_shape(s->shape);
+        need2 = std::max<int64_t>(need2, 3 * tb1_blocks(s->shape, t.R, t.K));
+    }
     if (march_supported(s->shape)) need2 = std::max<int64_t>(need2, 3 * march_partials_needed(s->shape));
     if (tblock_supported(s->shape))
         need2 = std::max<int64_t>(need2, 3 * tblock_partials_needed(s->shape, TBLOCK_MIN_ZCHUNK));
@@ -1145,9 +1226,11 @@ int ace_run_monitored(ace_solver *s, int64_t nsteps, int64_t every, double *E, d
     if (!s || nsteps < 0 || every < 1 || !E || !maxn) return ACE_E_ARG;
     const int64_t nmon = nsteps / every + 1;
     ACE_TRY(grow(&s->mon, &s->mon_cap, 3 * nmon));
-    const int k = effective_kernel(s);
+    int k = effective_kernel(s);
+    if (s->p.d == 1 && s->kernel == ACE_KERNEL_AUTO && s->tuned_kernel == ACE_KERNEL_AUTO && monitor_resident1(s, every))
+        k = ACE_KERNEL_RESIDENT;
     if (k == ACE_KERNEL_RESIDENT) {
-        ACE_HIP(launch_resident(s->shape, s->coef, s->buf[s->cur], nsteps, every, s->mon, s->stream));
+        ACE_HIP(run_resident(s, nsteps, every));
         s->steps += nsteps;
     } else {
         int64_t j = 0;
@@ -1300,6 +1383,7 @@ int ace_autotune(ace_solver *s, int64_t trial_steps, char *json, size_t cap)
     const int z0c = s->zchunk, k0 = s->depth2, v30 = s->tb3, v20 = s->tb2;
     cands.push_back({ACE_KERNEL_DIRECT, z0c, k0, v30, v20});
     if (s->p.total <= RESIDENT_MAX) cands.push_back({ACE_KERNEL_RESIDENT, z0c, k0, v30, v20});
+    if (s->p.d == 1 && tb1_supported(s->shape)) cands.push_back({ACE_KERNEL_TBLOCK, z0c, k0, v30, v20});
     if (march_supported(s->shape)) cands.push_back({ACE_KERNEL_MARCH, z0c, k0, v30, v20});
     if (s->p.d == 3 && tblock_supported(s->shape))
         for (int zc : {0, 32})  // 0: persistent grid

@@ -177,6 +177,19 @@ inline int tb2_max_depth(int v) { return TB2_TABLE[v].rows / 2 - 4; }
 int tb2_find(int rows, int rpt);  // variant index, or -1
 bool tb2_supported(const Shape &s);  // d == 2 with fewer than 2^31 nodes
 
+// 1D: K steps per launch (1 <= K < 32 R) with one wavefront per 64 R - 2 K
+// output nodes, R nodes per lane (1, 2 or 4); same partials contract as the
+// one-step kernels.
+bool tb1_supported(const Shape &s);  // d == 1 with fewer than 2^30 nodes
+int64_t tb1_blocks(const Shape &s, int R, int K);
+hipError_t launch_step_tb1(const Shape &s, const StepCoef &c, const double *in, double *out, double *partials,
+                           int64_t *nparts, int R, int K, hipStream_t st);
+// 1D: all steps of up to RESIDENT_MAX nodes in one workgroup of tb1_blocks()
+// wavefronts (at most 16), which exchange every K steps; same contract as
+// launch_resident.
+hipError_t launch_resident1(const Shape &s, const StepCoef &c, double *field, int64_t nsteps, int64_t every,
+                            double *mon, int R, int K, hipStream_t st);
+
 // K transposed steps: states[i * stride] = phi^{m+i}, i = 0..K; lam_in =
 // lambda^{m+K}; writes lambda^m and one partial of dL/dkappa per block.
 hipError_t launch_adjoint_tblock2d(const Shape &s, const StepCoef &c, const double *lam_in,
