@@ -53,11 +53,12 @@ extern "C" {
 
 /* ---- kernel selection (ace_set_kernel) --------------------------------- */
 #define ACE_KERNEL_AUTO 0    /* the autotuned / default choice                */
-#define ACE_KERNEL_DIRECT 1  /* one thread per node, neighbours from cache    */
+#define ACE_KERNEL_DIRECT 1  /* neighbours from cache: one thread per node, or
+                                in 3D per column of a few planes              */
 #define ACE_KERNEL_MARCH 2   /* 3D: tiles marching along axis 0, LDS planes    */
 #define ACE_KERNEL_RESIDENT 3 /* whole field in LDS, many steps per launch    */
 #define ACE_KERNEL_TBLOCK 4  /* temporal blocking: 3D 2..4 steps per launch,
-                                2D 1..12 steps per launch                     */
+                                2D 1..12, 1D up to 124                        */
 
 /* ---- schemes (ace_set_scheme) ------------------------------------------ */
 #define ACE_SCHEME_RLB_MIE 0 /* the paper's scheme (default)                   */
@@ -81,7 +82,8 @@ typedef struct {
     double s;           /* relaxation parameter omega1 / kappa              */
     int conditions_ok;  /* 1 if dt <= (1 - 2 d kappa)(1 + 1e-12) and
                            0 < kappa < 1/(2d)                                 */
-    int newton_iters;   /* Newton steps of the pointwise cubic solve         */
+    int newton_iters;   /* Newton steps of the pointwise cubic solve where no
+                           polynomial of the root applies (large dt, |xi| > 1) */
     int scheme;         /* ACE_SCHEME_*                                      */
 } ace_params_t;
 
@@ -145,10 +147,13 @@ int ace_set_graph_launches(ace_solver *s, int64_t launches);
 int ace_set_scheme(ace_solver *s, int scheme);
 
 /* Kernel choice for ace_step (ACE_KERNEL_*) and its temporal depth (steps
- * per launch; 0 = default).  ACE_KERNEL_TBLOCK accepts 0, 2, 3 or 4 in 3D
- * (2: the two-step kernel; 3, 4: the configurable kernel on its default
- * region for that depth, see ace_set_region3d) and 0..12 in 2D.  A choice
- * that does not apply to the handle's dimension or size falls back to
+ * per launch; 0 = default).  Without a choice, and for what it leaves open
+ * (depth, region, plane chunk), a handle takes the launch with the least
+ * modelled time for its size; ace_autotune measures instead.
+ * ACE_KERNEL_TBLOCK accepts 0, 2, 3 or 4 in 3D (2: the two-step kernel; 3, 4:
+ * the configurable kernel on its default region for that depth, see
+ * ace_set_region3d) and 0..12 in 2D; in 1D the depth is the library's.  A
+ * choice that does not apply to the handle's dimension or size falls back to
  * ACE_KERNEL_DIRECT.  Every choice computes the same result bit for bit.
  * Error: ACE_E_ARG for an unknown kernel or depth. */
 int ace_set_kernel(ace_solver *s, int kernel, int depth);
@@ -408,11 +413,9 @@ typedef struct {
 
 /* Creates a batch of count instances (each validated as ace_create does;
  * status[i] receives each instance's status when status is not NULL).
- * Allocates one device arena for all fields.  Instances of one batch run in
- * persistent launches: each workgroup takes whole instances, one at a time,
- * from a queue ordered by decreasing cost, and runs all their steps (with
- * register-resident regions, the large 2D instances first in a kernel of
- * their own, then the rest; see ace_batch_set_region). */
+ * Allocates two device arenas for all fields.  The instances advance together
+ * in rounds of several steps, each round one launch over the regions of all
+ * 2D instances and one over the segments of all 1D ones. */
 int ace_batch_create(int count, const ace_instance_desc *desc,
                      ace_batch **out, int *status);
 int ace_batch_destroy(ace_batch *b);
@@ -432,34 +435,34 @@ int ace_batch_set_all(ace_batch *b, const double *phi0_all, int where);
 int ace_batch_step(ace_batch *b, int64_t nsteps);
 /* Energy and max-norm of every instance (host arrays of count doubles). */
 int ace_batch_monitor(ace_batch *b, double *E, double *maxn);
-/* enable = 1 (default): each ace_batch_step replays a HIP graph holding the
- * queue reset and the persistent launches (captured once per step count);
- * 0: they are issued directly on the stream (e.g. for tools that do not
+/* enable = 1 (default): each ace_batch_step replays a HIP graph holding its
+ * launches (captured once per step count); 0: they are issued directly on the stream (e.g. for tools that do not
  * follow graph launches).  Results are identical either way. */
 int ace_batch_set_graphs(ace_batch *b, int enable);
 int ace_batch_get_phi(ace_batch *b, int i, double *out, int where);
 int ace_batch_get_all(ace_batch *b, double *out_all, int where);
-/* Instances with at most `limit` stored nodes are stepped entirely in LDS
- * (limit is capped at the LDS capacity, 8000 doubles); larger ones stream
- * through their two arena slots.  Results do not depend on the choice. */
+/* With LDS-plane regions (ace_batch_set_region 0), 2D instances with at most
+ * `limit` stored nodes are stepped entirely in LDS (limit is capped at the LDS
+ * capacity, 8000 doubles); all others alternate between their two arena
+ * slots.  Results do not depend on the choice. */
 int ace_batch_set_resident_limit(ace_batch *b, int64_t limit);
-/* Steps per round (temporal-blocking depth, 1..8, default 4) of the 2D
- * instances too large for LDS, which advance over the regions of
+/* Steps per round (temporal-blocking depth, 1..8, by default chosen from the
+ * instances' sizes) of the 2D instances, which advance over the regions of
  * ace_batch_set_region with a ring of `depth` nodes recomputed.  Results do
  * not depend on the choice.  Error: ACE_E_ARG outside 1..8. */
 int ace_batch_set_depth(ace_batch *b, int depth);
-/* Region of the 2D instances too large for LDS: rows = 0 (default) the
- * 32 x 64 regions kept in LDS level by level; 32 or 64 the register-resident
+/* Region of the 2D instances: 32 or 64 (default) the register-resident
  * regions of that many rows by 64 columns (each thread two or four rows of a
  * column; nodes outside the instance are its boundary images), the region
- * shape of ace_set_region2d, stepped by a kernel of their own launched before
- * the one for the other instances.  Results do not depend on the choice.
+ * shape of ace_set_region2d, one workgroup per region of any instance; rows = 0
+ * one workgroup per instance for all steps, over the 32 x 64 regions kept in
+ * LDS level by level.  Results do not depend on the choice.
  * Error: ACE_E_ARG for other values. */
 int ace_batch_set_region(ace_batch *b, int rows);
 /* Times one batch step of trial_steps steps on the current fields (which are
- * restored): first for every region (0, 32, 64) and depth 2..6 at the
- * current resident limit, then for several resident limits at the fastest
- * pair.  Keeps the fastest and writes a JSON record of the timings into json
+ * restored): first for the register regions (32, 64) at depths 2..6 and the
+ * LDS-plane ones at depth 4 at the current resident limit, then for several
+ * resident limits at the fastest pair.  Keeps the fastest and writes a JSON record of the timings into json
  * (capacity cap, may be NULL). */
 int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap);
 

@@ -431,7 +431,7 @@ def monitor_status(E, maxn, conditions_ok=True):
 
 
 class Batch:
-    """Many independent 1D/2D instances stepped by one persistent launch.
+    """Many independent 1D/2D instances stepped together, several steps per launch.
 
     instances: sequence of (d, N, L, R, eps, dt, bc) tuples (N, L, R per axis).
     """

@@ -1,24 +1,19 @@
-// Batches of independent 1D/2D instances in one persistent launch.
+// Batches of independent 1D/2D instances.
 //
-// Each workgroup repeatedly takes the next task from a queue (a global
-// counter; tasks are instances ordered by decreasing cost, so the largest
-// start first) and runs every step of that instance before taking another.
-// Instances whose field fits in LDS are stepped entirely in LDS (one global
-// read and one write per launch).  Larger 2D ones advance in rounds of up to
-// `depth` steps (1..8, autotuned; 4 by default) over 32 x 64 LDS regions or
-// register-resident regions of 32 or 64 rows (autotuned; temporal blocking,
-// one global read and write per round); larger 1D ones
-// ping-pong between their two arena slots with a workgroup barrier between
-// steps.  Every instance carries its own shape, boundary condition, kappa, h
-// and Newton count, and every update uses the same arithmetic as the
-// single-instance kernels, so each instance's result equals ace_step on that
-// instance bit for bit.
-//
-// With register-resident regions the large 2D instances are queued for a
-// kernel of their own (launched first, on the same stream), so that neither
-// kernel carries the other's register pressure.  The launches (counter reset
-// by a one-thread kernel, then the persistent kernels) are captured once per
-// step count into a HIP graph and replayed.
+// Three kinds of work, each in launches over all its instances:
+//   * 2D instances advance together in rounds of up to `depth` steps over
+//     register-resident regions (ace_tb2.h), one launch per round, the fields
+//     alternating between the two arenas.  (One workgroup per whole instance
+//     left the largest one's time as the launch's: 66 ms for the 1024
+//     instances whose rounds take 22.)
+//   * 1D instances likewise, one wavefront per segment (ace_tb1.h).
+//   * with LDS-plane regions chosen, 2D instances: one workgroup each for all
+//     steps, a small field in LDS, others over 32 x 64 LDS regions.
+// Every instance carries its own shape, boundary condition, kappa, h and root
+// variant, and every update uses the same arithmetic as the single-instance
+// kernels, so each instance's result equals ace_step on that instance bit for
+// bit.  The launches of a step call are captured once per step count into a
+// HIP graph and replayed.
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -33,6 +28,7 @@
 #include "../../include/ace.h"
 #include "ace_device.h"
 #include "ace_runtime.h"
+#include "ace_tb1.h"
 #include "ace_tb2.h"
 #include "ace_tile2d.h"
 
@@ -52,10 +48,11 @@ namespace {
 constexpr int kBT = 1024;                       // threads per workgroup
 constexpr int kBNodes = (int)((RESIDENT_MAX + kBT - 1) / kBT);
 
-template <int D, int BC>
-__device__ void batch_resident(const BatchInst &I, double *__restrict__ fa, int64_t nsteps,
-                               double *f)
+// Small 2D instance, the field in LDS for all its steps.
+template <int BC, int RV>
+__device__ void batch_resident(const BatchInst &I, double *__restrict__ fa, int64_t nsteps, double *f)
 {
+    const StepCoef c = I.c;
     const int total = (int)I.total;
     const int tid = threadIdx.x;
     const int M1 = (int)I.M1, M2 = (int)I.M2;
@@ -68,7 +65,7 @@ __device__ void batch_resident(const BatchInst &I, double *__restrict__ fa, int6
         const int n[2] = {M1, M2};
         const int st[2] = {M2, 1};
 #pragma unroll
-        for (int a = 2 - D; a < 2; ++a) {
+        for (int a = 0; a < 2; ++a) {
             int lo, hi;
             if (cc[a] > 0) lo = j - st[a];
             else lo = (BC == BC_HN) ? j : (BC == BC_HD ? total : j + (n[a] - 1) * st[a]);
@@ -90,8 +87,8 @@ __device__ void batch_resident(const BatchInst &I, double *__restrict__ fa, int6
             if (j < total) {
                 double nsum = 0.0;
 #pragma unroll
-                for (int a = 2 - D; a < 2; ++a) nsum += f[nb_lo[k][a]] + f[nb_hi[k][a]];
-                nv[k] = update<D>(f[j], nsum, I.c);
+                for (int a = 0; a < 2; ++a) nsum += f[nb_lo[k][a]] + f[nb_hi[k][a]];
+                nv[k] = update_n<2, RV>(f[j], nsum, c);
             }
         }
         __syncthreads();
@@ -103,55 +100,6 @@ __device__ void batch_resident(const BatchInst &I, double *__restrict__ fa, int6
         __syncthreads();
     }
     for (int j = tid; j < total; j += kBT) fa[j] = f[j];
-    __syncthreads();
-}
-
-// Instance too large for LDS: one wavefront per 64-node segment of a row,
-// neighbours through the cache, workgroup barrier (with its memory fence)
-// between steps; the field ping-pongs between its two arena slots.
-template <int D, int BC>
-__device__ void batch_stream(const BatchInst &I, double *__restrict__ fa, double *__restrict__ fb,
-                             int64_t nsteps)
-{
-    const int64_t M1 = I.M1, M2 = I.M2;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int nw = kBT / 64;
-    const int64_t nseg = (M2 + 63) / 64;
-    for (int64_t step = 0; step < nsteps; ++step) {
-        const double *__restrict__ in = (step & 1) ? fb : fa;
-        double *__restrict__ out = (step & 1) ? fa : fb;
-        for (int64_t r = wave; r < M1 * nseg; r += nw) {
-            const int64_t i1 = r / nseg;
-            const int64_t i2 = (r - i1 * nseg) * 64 + lane;
-            if (i2 >= M2) continue;
-            const int64_t idx = i1 * M2 + i2;
-            const double p = in[idx];
-            double nsum = 0.0;
-            if (D == 2) {
-                double ylo, yhi;
-                if (i1 > 0) ylo = in[idx - M2];
-                else ylo = outside<BC>(p, BC == BC_P ? in[idx + (M1 - 1) * M2] : 0.0);
-                if (i1 < M1 - 1) yhi = in[idx + M2];
-                else yhi = outside<BC>(p, BC == BC_P ? in[idx - (M1 - 1) * M2] : 0.0);
-                nsum += ylo + yhi;
-            }
-            double xlo, xhi;
-            if (i2 > 0) xlo = in[idx - 1];
-            else xlo = outside<BC>(p, BC == BC_P ? in[idx + (M2 - 1)] : 0.0);
-            if (i2 < M2 - 1) xhi = in[idx + 1];
-            else xhi = outside<BC>(p, BC == BC_P ? in[idx - (M2 - 1)] : 0.0);
-            nsum += xlo + xhi;
-            out[idx] = update<D>(p, nsum, I.c);
-        }
-        __threadfence_block();
-        __syncthreads();
-    }
-    if (nsteps & 1) {  // result back into the first arena
-        for (int64_t j = threadIdx.x; j < M1 * M2; j += kBT) fa[j] = fb[j];
-        __threadfence_block();
-        __syncthreads();
-    }
 }
 
 // 2D instance too large for LDS, advanced in rounds of up to tk steps (the
@@ -242,155 +190,192 @@ __device__ void batch_tiles2d(const BatchInst &I, double *__restrict__ fa, doubl
     }
 }
 
-// The same rounds over register-resident regions (ace_tb2.h): each thread
-// holds RYT consecutive rows of a column of a (16 RYT) x 64 region, nodes
-// outside the instance are its boundary images, and the workgroup's LDS array
-// holds the regions' edge rows.  The next region's values are loaded while
-// the current one advances.  RV: the instance's root variant (ace_device.h).
-template <int BC, int RYT, int RV>
-__device__ void batch_regions(const BatchInst &I, double *__restrict__ fa, double *__restrict__ fb,
-                              int64_t nsteps, double *lds, int tk)
+// f with the instance's boundary condition and root variant (batches have no
+// explicit scheme).
+template <class F>
+__device__ __forceinline__ void with_instance(const BatchInst &I, F &&f)
+{
+    auto by_rv = [&](auto BCc) {
+        with_root(I.c.rv, [&](auto RVc) {
+            constexpr int RV = decltype(RVc)::value;
+            f(BCc, RootTag<RV == ROOT_FEX ? 0 : RV>());
+        });
+    };
+    if (I.bc == BC_HN) by_rv(RootTag<BC_HN>());
+    else if (I.bc == BC_HD) by_rv(RootTag<BC_HD>());
+    else by_rv(RootTag<BC_P>());
+}
+
+// One workgroup's piece of a launch over many instances: the instance, and
+// its tile row and column (regions), segment or chunk number.
+struct Piece {
+    int inst, a, b;
+};
+
+// One region of a 2D instance per workgroup, S steps from src to dst (a ring
+// of K >= S nodes).  Two workgroups fit on a CU, so one's loads overlap the
+// other's levels: 225 us per round of 5 steps on 512 instances of 24.5 million
+// nodes, where the region levels take 150 and the field's bytes 110 at the
+// rate of a copy.  (A persistent grid that loads the next region while it
+// advances the current one needs 71 vector registers and spills at the 64 of
+// two workgroups: 325 us.)
+template <int RYT>
+__global__ __launch_bounds__(kBT) void k_batch_regions(const BatchInst *__restrict__ inst,
+                                                      const Piece *__restrict__ pieces, const double *__restrict__ src,
+                                                      double *__restrict__ dst, int K, int S)
 {
     constexpr int TRW = kBT / 64;  // 16 wavefronts
-    using Rg = tb2::Region<BC, TRW, RYT>;
-    Shape s;
-    s.d = 2;
-    s.bc = BC;
-    s.M0 = 1;
-    s.M1 = I.M1;
-    s.M2 = I.M2;
-    MonAcc m;
-    mon_zero(m);
-    const StepCoef c = coef_vgpr<RV>(I.c);
-    int64_t done = 0;
-    int par = 0;  // 0: the field is in fa
-    while (done < nsteps) {
-        const int K = (int)std::min<int64_t>(tk, nsteps - done);
-        const double *__restrict__ in = par ? fb : fa;
-        double *__restrict__ out = par ? fa : fb;
-        const int oy = Rg::RH - 2 * K, ox = 64 - 2 * K;
-        const int tiles_x = ((int)s.M2 + ox - 1) / ox, tiles_y = ((int)s.M1 + oy - 1) / oy;
-        double v[RYT], vn[RYT];
-        Rg(s, K, 0, 0).load(s, in, v);
+    __shared__ double EB[2 * 2 * TRW * 64];
+    const Piece p = pieces[xcd_tile(blockIdx.x, gridDim.x)];
+    const BatchInst &I = inst[p.inst];
+    with_instance(I, [&](auto BCc, auto RVc) {
+        constexpr int RV = decltype(RVc)::value;
+        Shape s;
+        s.d = 2;
+        s.bc = decltype(BCc)::value;
+        s.M0 = 1;
+        s.M1 = I.M1;
+        s.M2 = I.M2;
+        MonAcc m;
+        mon_zero(m);
+        const tb2::Region<decltype(BCc)::value, TRW, RYT> g(s, K, p.a, p.b);
+        double v[RYT];
+        g.load(s, src + I.off, v);
+        g.template advance<false, false, RV>(s, coef_vgpr<RV>(I.c), v, dst + I.off, 0, EB, m, S);
+    });
+}
+
+// One segment of a 1D instance, S steps from src to dst
+// (kSegR nodes per lane, a ring of kSegK >= S nodes on each side).
+constexpr int kSegR = 4, kSegK = 32, kSegOut = 64 * kSegR - 2 * kSegK;
+
+__global__ __launch_bounds__(64) void k_batch_segments(const BatchInst *__restrict__ inst,
+                                                       const Piece *__restrict__ pieces,
+                                                       const double *__restrict__ src, double *__restrict__ dst, int S)
+{
+    const Piece p = pieces[blockIdx.x];
+    const BatchInst &I = inst[p.inst];
+    with_instance(I, [&](auto BCc, auto RVc) {
+        constexpr int BC = decltype(BCc)::value, RV = decltype(RVc)::value;
+        const StepCoef c = coef_vgpr<RV>(I.c);
+        const int n = (int)I.total, o0 = p.a * kSegOut, o1 = o0 + kSegOut < n ? o0 + kSegOut : n;
+        const int first = o0 - kSegK + (int)threadIdx.x * kSegR;
+        double v[kSegR];
 #pragma unroll
-        for (int r = 0; r < RYT; ++r) vn[r] = 0.0;
-        // regions row by row; the next one's values load while this one advances
-        for (int ty = 0, tx = 0; ty < tiles_y;) {
-            const Rg g(s, K, ty, tx);
-            int nty = ty, ntx = tx + 1;
-            if (ntx == tiles_x) {
-                ntx = 0;
-                ++nty;
-            }
-            if (nty < tiles_y) Rg(s, K, nty, ntx).load(s, in, vn);
-            g.template advance<false, false, RV>(s, c, v, out, 0, lds, m);
-            __syncthreads();  // every wavefront is past the edge rows before the next region writes them
+        for (int r = 0; r < kSegR; ++r) {
+            int sg;
+            const double x = src[I.off + tb1::source<BC>(first + r, n, sg)];
+            v[r] = (BC != BC_HD || sg > 0) ? x : (sg < 0 ? -x : 0.0);
+        }
+        for (int k = 0; k < S; ++k) tb1::step<kSegR, RV>(v, c);
 #pragma unroll
-            for (int r = 0; r < RYT; ++r) v[r] = vn[r];
-            ty = nty;
-            tx = ntx;
-        }
-        __threadfence_block();
-        __syncthreads();
-        done += K;
-        par ^= 1;
-    }
-    if (par) {  // result back into the first arena
-        for (int64_t j = threadIdx.x; j < s.M1 * s.M2; j += kBT) fa[j] = fb[j];
-        __threadfence_block();
-        __syncthreads();
-    }
+        for (int r = 0; r < kSegR; ++r)
+            if (first + r >= o0 && first + r < o1) dst[I.off + first + r] = v[r];
+    });
 }
 
-__global__ void k_batch_reset(int *counter)
+// All steps of one 2D instance per workgroup: small ones in LDS, others over
+// LDS-plane regions.
+__global__ __launch_bounds__(kBT) void k_batch(const BatchInst *__restrict__ inst, const int *__restrict__ order,
+                                               double *__restrict__ arena_a, double *__restrict__ arena_b,
+                                               int64_t nsteps, int tk)
 {
-    if (threadIdx.x < 2 && blockIdx.x == 0) counter[threadIdx.x] = 0;
-}
-
-// The tasks order[first .. last) taken from the queue counter.  REGION = 0:
-// every kind of instance (large 2D ones over LDS-plane regions); 32 or 64:
-// large 2D instances only, over register-resident regions of that height.
-template <int REGION>
-__global__ __launch_bounds__(kBT) void k_batch(const BatchInst *__restrict__ inst,
-                                               const int *__restrict__ order, int first, int last,
-                                               int *__restrict__ counter, double *__restrict__ arena_a,
-                                               double *__restrict__ arena_b, int64_t nsteps, int tk)
-{
-    __shared__ double f[REGION ? 2 * 2 * (kBT / 64) * 64 : RESIDENT_MAX + 1];
-    __shared__ int task;
-    for (;;) {
-        if (threadIdx.x == 0) task = first + atomicAdd(counter, 1);
-        __syncthreads();
-        const int t = __builtin_amdgcn_readfirstlane(task);
-        __syncthreads();  // all threads read the task before the next fetch
-        if (t >= last) break;
-        const BatchInst I = inst[order[t]];
-        double *fa = arena_a + I.off;
-        double *fb = arena_b + I.off;
-        if (REGION != 0) {
-            constexpr int RYT = REGION == 64 ? 4 : 2;
-            auto by_rv = [&](auto BCc) {
-                constexpr int B = decltype(BCc)::value;
-                with_root(I.c.rv, [&](auto RVc) {  // (batches have no explicit scheme)
-                    constexpr int RV = decltype(RVc)::value;
-                    batch_regions<B, RYT, RV == ROOT_FEX ? 0 : RV>(I, fa, fb, nsteps, f, tk);
-                });
-            };
-            if (I.bc == BC_HN) by_rv(std::integral_constant<int, BC_HN>());
-            else if (I.bc == BC_HD) by_rv(std::integral_constant<int, BC_HD>());
-            else by_rv(std::integral_constant<int, BC_P>());
-        } else if (I.resident) {
-            if (I.d == 1) {
-                if (I.bc == BC_HN) batch_resident<1, BC_HN>(I, fa, nsteps, f);
-                else if (I.bc == BC_HD) batch_resident<1, BC_HD>(I, fa, nsteps, f);
-                else batch_resident<1, BC_P>(I, fa, nsteps, f);
-            } else {
-                if (I.bc == BC_HN) batch_resident<2, BC_HN>(I, fa, nsteps, f);
-                else if (I.bc == BC_HD) batch_resident<2, BC_HD>(I, fa, nsteps, f);
-                else batch_resident<2, BC_P>(I, fa, nsteps, f);
-            }
-        } else if (I.d == 1) {
-            if (I.bc == BC_HN) batch_stream<1, BC_HN>(I, fa, fb, nsteps);
-            else if (I.bc == BC_HD) batch_stream<1, BC_HD>(I, fa, fb, nsteps);
-            else batch_stream<1, BC_P>(I, fa, fb, nsteps);
-        } else {
-            if (I.bc == BC_HN) batch_tiles2d<BC_HN>(I, fa, fb, nsteps, f, tk);
-            else if (I.bc == BC_HD) batch_tiles2d<BC_HD>(I, fa, fb, nsteps, f, tk);
-            else batch_tiles2d<BC_P>(I, fa, fb, nsteps, f, tk);
-        }
+    __shared__ double f[RESIDENT_MAX + 1];
+    const BatchInst &I = inst[order[blockIdx.x]];
+    double *fa = arena_a + I.off;
+    double *fb = arena_b + I.off;
+    if (I.resident) {
+        with_instance(I, [&](auto BCc, auto RVc) {
+            batch_resident<decltype(BCc)::value, decltype(RVc)::value>(I, fa, nsteps, f);
+        });
+    } else if (I.bc == BC_HN) {
+        batch_tiles2d<BC_HN>(I, fa, fb, nsteps, f, tk);
+    } else if (I.bc == BC_HD) {
+        batch_tiles2d<BC_HD>(I, fa, fb, nsteps, f, tk);
+    } else {
+        batch_tiles2d<BC_P>(I, fa, fb, nsteps, f, tk);
     }
 }
 
-// Monitor triple (bulk, grad, max) of each instance: one workgroup each.
-__global__ __launch_bounds__(256) void k_batch_monitor(const BatchInst *__restrict__ inst,
-                                                       const double *__restrict__ arena_a,
-                                                       double *__restrict__ trip)
+// Chunks of kChunk nodes of every instance, for the copies and the monitor.
+constexpr int kChunk = 4096;
+constexpr int kChunkThreads = 256;
+
+// dst[...] = src[...] over each chunk: between the arenas (packed = nullptr),
+// or from (to_packed) or to the fields back to back in instance order,
+// instance i at packed[i].
+__global__ __launch_bounds__(kChunkThreads) void k_batch_copy(const BatchInst *__restrict__ inst,
+                                                              const Piece *__restrict__ pieces,
+                                                              const int64_t *__restrict__ packed, int to_packed,
+                                                              const double *__restrict__ src, double *__restrict__ dst)
 {
-    __shared__ double lds[3 * 4];
-    const BatchInst I = inst[blockIdx.x];
+    const Piece p = pieces[blockIdx.x];
+    const int64_t off = inst[p.inst].off, total = inst[p.inst].total;
+    const int64_t lo = (int64_t)p.a * kChunk, hi = lo + kChunk < total ? lo + kChunk : total;
+    const int64_t so = packed && !to_packed ? packed[p.inst] : off, to = packed && to_packed ? packed[p.inst] : off;
+#pragma unroll 4
+    for (int64_t j = lo + threadIdx.x; j < hi; j += kChunkThreads) dst[to + j] = src[so + j];
+}
+
+// Monitor partial (bulk, grad, max) of each chunk.
+__global__ __launch_bounds__(kChunkThreads) void k_batch_monitor(const BatchInst *__restrict__ inst,
+                                                                 const Piece *__restrict__ pieces,
+                                                                 const double *__restrict__ arena_a,
+                                                                 double *__restrict__ partials)
+{
+    __shared__ double lds[3 * (kChunkThreads / 64)];
+    const Piece p = pieces[blockIdx.x];
+    const BatchInst &I = inst[p.inst];
     const double *f = arena_a + I.off;
+    const int64_t lo = (int64_t)p.a * kChunk, hi = lo + kChunk < I.total ? lo + kChunk : I.total;
+    const int d = I.d, bc = I.bc;
+    const int64_t M1 = I.M1, M2 = I.M2;
+    int64_t i1 = (lo + threadIdx.x) / M2, i2 = (lo + threadIdx.x) - i1 * M2;
     MonAcc m;
     mon_zero(m);
-    for (int64_t j = threadIdx.x; j < I.total; j += blockDim.x) {
-        const int64_t i1 = j / I.M2, i2 = j - i1 * I.M2;
-        const double p = f[j];
+    for (int64_t j = lo + threadIdx.x; j < hi; j += kChunkThreads) {
+        const double v = f[j];
         double g = 0.0;
-        const int64_t cc[2] = {i1, i2};
-        const int64_t n[2] = {I.M1, I.M2};
-        const int64_t st[2] = {I.M2, 1};
-        for (int a = 2 - I.d; a < 2; ++a) {
-            double hi;
-            if (cc[a] < n[a] - 1) hi = f[j + st[a]];
-            else hi = (I.bc == BC_HN) ? p : (I.bc == BC_HD ? 0.0 : f[j - (n[a] - 1) * st[a]]);
-            const double dh = hi - p;
+        auto axis = [&](int64_t c, int64_t n, int64_t st) {
+            double nx;
+            if (c < n - 1) nx = f[j + st];
+            else nx = (bc == BC_HN) ? v : (bc == BC_HD ? 0.0 : f[j - (n - 1) * st]);
+            const double dh = nx - v;
             g = fma(dh, dh, g);
-            if (I.bc == BC_HD && cc[a] == 0) g = fma(p, p, g);
-        }
-        m.bulk += bulk_term(p);
+            if (bc == BC_HD && c == 0) g = fma(v, v, g);
+        };
+        if (d == 2) axis(i1, M1, M2);
+        axis(i2, M2, 1);
+        m.bulk += bulk_term(v);
         m.grad += g;
-        m.mx = nan_max(m.mx, fabs(p));
+        m.mx = nan_max(m.mx, fabs(v));
+        i2 += kChunkThreads;
+        while (i2 >= M2) {
+            i2 -= M2;
+            ++i1;
+        }
     }
-    block_reduce_store(m, lds, trip + 3 * blockIdx.x);
+    block_reduce_store(m, lds, partials + 3 * blockIdx.x);
+}
+
+// The chunks' partials of instance i (first[i] .. first[i + 1]) in order.
+__global__ __launch_bounds__(64) void k_batch_monitor_sum(const int *__restrict__ first,
+                                                          const double *__restrict__ partials,
+                                                          double *__restrict__ trip)
+{
+    MonAcc m;
+    mon_zero(m);
+    for (int j = first[blockIdx.x] + threadIdx.x; j < first[blockIdx.x + 1]; j += 64) {
+        m.bulk += partials[3 * (int64_t)j + 0];
+        m.grad += partials[3 * (int64_t)j + 1];
+        m.mx = nan_max(m.mx, partials[3 * (int64_t)j + 2]);
+    }
+    const double b = wave_sum(m.bulk), g = wave_sum(m.grad), x = wave_max(m.mx);
+    if (threadIdx.x == 0) {
+        trip[3 * blockIdx.x + 0] = b;
+        trip[3 * blockIdx.x + 1] = g;
+        trip[3 * blockIdx.x + 2] = x;
+    }
 }
 
 }  // namespace
@@ -403,22 +388,30 @@ struct ace_batch {
     std::vector<Problem> prob;
     std::vector<BatchInst> host_inst;
     std::vector<int> order;
-    int64_t arena_total = 0;
+    std::vector<int64_t> packed;  // offsets of the fields back to back
+    int64_t arena_total = 0, packed_total = 0;
     int64_t resident_limit = RESIDENT_MAX;  // tuned: largest field stepped in LDS
-    int depth = 4;  // tuned: steps per round of the 2D instances stepped over LDS regions
-    int region = 0;  // tuned: 0 LDS-plane 32 x 64 regions; 32 or 64: register-resident regions of that height
+    int depth = 4;    // steps per round of the large 2D instances (set or tuned, or by rule)
+    int depth_fixed = 0;
+    int region = 64;  // tuned: 0 LDS-plane 32 x 64 regions; 32 or 64: register-resident regions of that height
     int device = 0;
     hipStream_t stream = nullptr;   // caller's stream (graph launches go here)
     hipStream_t capture = nullptr;  // private stream used only for graph capture
     BatchInst *inst = nullptr;
     int *order_dev = nullptr;
-    int *counter = nullptr;  // [0] queue of the first kernel, [1] of the second
-    int n_large = 0;         // order[0 .. n_large): 2D instances too large for LDS (32-bit indexable)
+    int64_t *packed_dev = nullptr;
+    // pieces of every launch kind, one device array: regions of the 2D
+    // instances at the current depth and region, segments of the 1D ones,
+    // chunks of all instances (for the copies and the monitor), and those of
+    // the instances in regions and in segments
+    Piece *pieces = nullptr;
+    int64_t pieces_cap = 0;
+    int n_regions = 0, n_segments = 0, n_chunks = 0, n_chunks2 = 0, n_chunks1 = 0;
+    int *chunk_first = nullptr;  // count + 1
+    int n_single = 0;  // order[]: the 2D instances of k_batch
     double *arena_a = nullptr, *arena_b = nullptr;
-    double *trip = nullptr;
-    int grid = 0;     // workgroups of the queue kernel
-    int grid_rg = 0;  // workgroups of the register-region kernels
-    int use_graphs = 1;  // 0: the launch pair is issued directly on every step call
+    double *trip = nullptr, *partials = nullptr;
+    int use_graphs = 1;  // 0: the launches are issued directly on every step call
     std::map<int64_t, hipGraphExec_t> graphs;
     std::map<int64_t, hipGraph_t> graph_defs;
 };
@@ -442,51 +435,145 @@ void drop_graphs(ace_batch *b)
     b->graph_defs.clear();
 }
 
-// Cost model for the queue order: node updates, with streaming instances
-// weighted by their extra memory traffic.
-int64_t task_cost(const BatchInst &I) { return I.total * (I.resident ? 1 : 3); }
-
+// Sorts the instances into their kinds of work and uploads the tables of the
+// launches (at the current limit, depth and region).
 int upload_tasks(ace_batch *b)
 {
     // the tables below are read by any launch still running on the stream
     BT_HIP(hipStreamSynchronize(b->stream));
-    for (auto &I : b->host_inst) I.resident = (I.total <= b->resident_limit) ? 1 : 0;
-    // the large 2D instances first (the register-region kernel's queue; the
-    // regions index a field with 32 bits), then the rest, each by cost
-    auto large = [&](int x) {
-        const BatchInst &I = b->host_inst[x];
-        return I.d == 2 && !I.resident && I.total <= INT32_MAX;
-    };
-    b->order.resize(b->count);
-    std::iota(b->order.begin(), b->order.end(), 0);
-    std::stable_sort(b->order.begin(), b->order.end(), [&](int x, int y) {
-        if (large(x) != large(y)) return large(x);
-        return task_cost(b->host_inst[x]) > task_cost(b->host_inst[y]);
-    });
-    b->n_large = (int)std::count_if(b->order.begin(), b->order.end(), large);
-    BT_HIP(hipMemcpy(b->inst, b->host_inst.data(), sizeof(BatchInst) * b->count,
-                     hipMemcpyHostToDevice));
-    BT_HIP(hipMemcpy(b->order_dev, b->order.data(), sizeof(int) * b->count, hipMemcpyHostToDevice));
     drop_graphs(b);
+    std::vector<int> large2, large1, single;
+    for (int i = 0; i < b->count; ++i) {
+        BatchInst &I = b->host_inst[i];
+        // (in LDS, a small instance takes longer than as its few regions or
+        // segments: 200 of 16^2 to 60^2 and of 128 to 4096 nodes x 500 steps
+        // 1.97 against 0.97 ms)
+        I.resident = I.d == 2 && b->region == 0 && I.total <= b->resident_limit;
+        if (I.d == 1) large1.push_back(i);
+        else if (b->region != 0 && I.total <= INT32_MAX) large2.push_back(i);  // (regions index with 32 bits)
+        else single.push_back(i);
+    }
+    // workgroups that take a whole instance: the costly ones first
+    std::stable_sort(single.begin(), single.end(),
+                     [&](int x, int y) { return b->host_inst[x].total > b->host_inst[y].total; });
+    b->order = single;
+    b->n_single = (int)single.size();
+    // regions of one code path (boundary condition, root variant) next to each other
+    std::stable_sort(large2.begin(), large2.end(), [&](int x, int y) {
+        const BatchInst &X = b->host_inst[x], &Y = b->host_inst[y];
+        return X.bc != Y.bc ? X.bc < Y.bc : X.c.rv < Y.c.rv;
+    });
+    if (!b->depth_fixed && b->region == 64) {
+        // the least modelled time per step: workgroups of the busiest of 256
+        // CUs times the levels (0.62 us each, 1.2 levels to start), and 3.7
+        // us per launch, as for one field
+        double best = 1e300;
+        for (int K = 2; K <= kMaxDepth; ++K) {
+            int64_t n = 0;
+            for (int i : large2) {
+                const BatchInst &I = b->host_inst[i];
+                n += ((I.M1 + 63 - 2 * K) / (64 - 2 * K)) * ((I.M2 + 63 - 2 * K) / (64 - 2 * K));
+            }
+            const double us = (3.7 + 0.62 * (K + 1.2) * (double)((n + 255) / 256)) / K;
+            if (us >= best) continue;
+            best = us;
+            b->depth = K;
+        }
+    }
+    std::vector<Piece> p;
+    const int oy = std::max(1, b->region - 2 * b->depth), ox = 64 - 2 * b->depth;
+    for (int i : large2) {
+        const BatchInst &I = b->host_inst[i];
+        for (int y = 0; y < (I.M1 + oy - 1) / oy; ++y)
+            for (int x = 0; x < (I.M2 + ox - 1) / ox; ++x) p.push_back({i, y, x});
+    }
+    b->n_regions = (int)p.size();
+    for (int i : large1)
+        for (int64_t a = 0; a * kSegOut < b->host_inst[i].total; ++a) p.push_back({i, (int)a, 0});
+    b->n_segments = (int)p.size() - b->n_regions;
+    std::vector<int> first(b->count + 1, 0);
+    for (int i = 0; i < b->count; ++i) {
+        for (int64_t a = 0; a * kChunk < b->host_inst[i].total; ++a) p.push_back({i, (int)a, 0});
+        first[i + 1] = (int)p.size() - b->n_regions - b->n_segments;
+    }
+    b->n_chunks = first[b->count];
+    auto chunks_of = [&](const std::vector<int> &v) {
+        const size_t before = p.size();
+        for (int i : v)
+            for (int64_t a = 0; a * kChunk < b->host_inst[i].total; ++a) p.push_back({i, (int)a, 0});
+        return (int)(p.size() - before);
+    };
+    b->n_chunks2 = chunks_of(large2);
+    b->n_chunks1 = chunks_of(large1);
+    if (p.size() > (size_t)INT32_MAX) return ACE_E_NOMEM;
+    if ((int64_t)p.size() > b->pieces_cap) {
+        if (b->pieces) (void)hipFree(b->pieces);
+        b->pieces = nullptr;
+        b->pieces_cap = 0;
+        BT_HIP(hipMalloc((void **)&b->pieces, sizeof(Piece) * p.size()));
+        b->pieces_cap = (int64_t)p.size();
+    }
+    if (!b->partials) {  // (the chunks do not depend on the choices)
+        BT_HIP(hipMalloc((void **)&b->partials, sizeof(double) * 3 * (size_t)b->n_chunks));
+        BT_HIP(hipMalloc((void **)&b->chunk_first, sizeof(int) * first.size()));
+        BT_HIP(hipMemcpy(b->chunk_first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice));
+    }
+    BT_HIP(hipMemcpy(b->pieces, p.data(), sizeof(Piece) * p.size(), hipMemcpyHostToDevice));
+    BT_HIP(hipMemcpy(b->inst, b->host_inst.data(), sizeof(BatchInst) * b->count, hipMemcpyHostToDevice));
+    if (!b->order.empty())
+        BT_HIP(hipMemcpy(b->order_dev, b->order.data(), sizeof(int) * b->order.size(), hipMemcpyHostToDevice));
     return ACE_OK;
 }
 
-// The batch kernels for the chosen region, on stream st (the counters must
-// be zero): the register-region kernel over the large 2D instances, then the
-// queue kernel over the rest; or the queue kernel over every instance.
-void launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
+const Piece *chunk_pieces(const ace_batch *b) { return b->pieces + b->n_regions + b->n_segments; }
+
+// f(steps, from, to) for each of an even number of rounds of at most `most`
+// steps (so that the fields end in the arena they began in), of equal length
+// to one step; only an odd number of one-step rounds stays odd.  Returns the
+// rounds.
+template <class F>
+int64_t in_rounds(const ace_batch *b, int64_t nsteps, int most, F &&f)
 {
-    auto go = [&](auto kern, int grid, int first, int last, int q) {
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kBT), 0, st, b->inst, b->order_dev, first, last, b->counter + q,
-                           b->arena_a, b->arena_b, nsteps, b->depth);
-    };
-    int first = 0;
-    if (b->region != 0 && b->n_large > 0) {
-        if (b->region == 64) go(k_batch<64>, b->grid_rg, 0, b->n_large, 0);
-        else go(k_batch<32>, b->grid_rg, 0, b->n_large, 0);
-        first = b->n_large;
+    int64_t rounds = (nsteps + most - 1) / most;
+    if ((rounds & 1) && rounds < nsteps) ++rounds;
+    int64_t done = 0;
+    for (int64_t r = 0; r < rounds; ++r) {
+        const int64_t upto = nsteps * (r + 1) / rounds;
+        f((int)(upto - done), (r & 1) ? b->arena_b : b->arena_a, (r & 1) ? b->arena_a : b->arena_b);
+        done = upto;
     }
-    if (first < b->count) go(k_batch<0>, b->grid, first, b->count, 1);
+    return rounds;
+}
+
+// Every launch of a step call on stream st.
+hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
+{
+    // the result of an odd number of rounds back into the first arena
+    auto copy_back = [&](const Piece *pieces, int n) {
+        hipLaunchKernelGGL(k_batch_copy, dim3(n), dim3(kChunkThreads), 0, st, b->inst, pieces, nullptr, 0, b->arena_b,
+                           b->arena_a);
+    };
+    if (b->n_regions > 0) {
+        auto go = [&](auto kern) {
+            return in_rounds(b, nsteps, b->depth, [&](int S, const double *src, double *dst) {
+                hipLaunchKernelGGL(kern, dim3(b->n_regions), dim3(kBT), 0, st, b->inst, b->pieces, src, dst, b->depth,
+                                   S);
+            });
+        };
+        const int64_t rounds = b->region == 64 ? go(k_batch_regions<4>) : go(k_batch_regions<2>);
+        if (rounds & 1) copy_back(chunk_pieces(b) + b->n_chunks, b->n_chunks2);
+    }
+    if (b->n_segments > 0) {
+        const int64_t rounds = in_rounds(b, nsteps, kSegK, [&](int S, const double *src, double *dst) {
+            hipLaunchKernelGGL(k_batch_segments, dim3(b->n_segments), dim3(64), 0, st, b->inst,
+                               b->pieces + b->n_regions, src, dst, S);
+        });
+        if (rounds & 1) copy_back(chunk_pieces(b) + b->n_chunks + b->n_chunks2, b->n_chunks1);
+    }
+    if (b->n_single > 0)
+        hipLaunchKernelGGL(k_batch, dim3(b->n_single), dim3(kBT), 0, st, b->inst,
+                           b->order_dev, b->arena_a, b->arena_b, nsteps, b->depth);
+    return hipGetLastError();
 }
 
 int get_graph(ace_batch *b, int64_t nsteps, hipGraphExec_t *out)
@@ -499,9 +586,7 @@ int get_graph(ace_batch *b, int64_t nsteps, hipGraphExec_t *out)
     hipGraph_t g = nullptr;
     hipGraphExec_t e = nullptr;
     BT_HIP(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
-    hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, b->capture, b->counter);
-    launch_batch(b, b->capture, nsteps);
-    hipError_t le = hipGetLastError();
+    hipError_t le = launch_batch(b, b->capture, nsteps);
     hipError_t ce = hipStreamEndCapture(b->capture, &g);
     BT_HIP(le);
     BT_HIP(ce);
@@ -516,6 +601,10 @@ int get_graph(ace_batch *b, int64_t nsteps, hipGraphExec_t *out)
     return ACE_OK;
 }
 
+// Longer step calls replay a graph of this many steps (a graph holds a node
+// per round).
+constexpr int64_t kGraphSteps = 1024;
+
 }  // namespace
 
 extern "C" {
@@ -529,6 +618,7 @@ int ace_batch_create(int count, const ace_instance_desc *desc, ace_batch **out, 
     b->count = count;
     b->prob.resize(count);
     b->host_inst.resize(count);
+    b->packed.resize(count);
     int worst = ACE_OK, warn = ACE_OK;
     int64_t off = 0;
     for (int i = 0; i < count; ++i) {
@@ -550,6 +640,8 @@ int ace_batch_create(int count, const ace_instance_desc *desc, ace_batch **out, 
         I.c = coef_of(p);
         I.resident = 0;
         off += (p.total + 31) / 32 * 32;  // 256-byte aligned fields
+        b->packed[i] = b->packed_total;
+        b->packed_total += p.total;
     }
     if (worst < 0) {
         delete b;
@@ -567,21 +659,12 @@ int ace_batch_create(int count, const ace_instance_desc *desc, ace_batch **out, 
     if ((rc = hip_status(hipMemset(b->arena_a, 0, sizeof(double) * off))) < 0) return fail(rc);
     if ((rc = hip_status(hipMalloc((void **)&b->inst, sizeof(BatchInst) * count))) < 0) return fail(rc);
     if ((rc = hip_status(hipMalloc((void **)&b->order_dev, sizeof(int) * count))) < 0) return fail(rc);
-    if ((rc = hip_status(hipMalloc((void **)&b->counter, sizeof(int) * 64))) < 0) return fail(rc);
+    if ((rc = hip_status(hipMalloc((void **)&b->packed_dev, sizeof(int64_t) * count))) < 0) return fail(rc);
+    if ((rc = hip_status(hipMemcpy(b->packed_dev, b->packed.data(), sizeof(int64_t) * count,
+                                   hipMemcpyHostToDevice))) < 0)
+        return fail(rc);
     if ((rc = hip_status(hipMalloc((void **)&b->trip, sizeof(double) * 3 * count))) < 0) return fail(rc);
     if ((rc = hip_status(hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking))) < 0) return fail(rc);
-    int cus = 0, per_cu = 0;
-    if ((rc = hip_status(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount,
-                                               b->device))) < 0)
-        return fail(rc);
-    if ((rc = hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch<0>, kBT, 0))) < 0)
-        return fail(rc);
-    b->grid = std::max(1, cus * std::max(1, per_cu));
-    int per_cu_rg = 0, per_cu_rg32 = 0;
-    if ((rc = hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_rg, k_batch<64>, kBT, 0))) < 0 ||
-        (rc = hip_status(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_rg32, k_batch<32>, kBT, 0))) < 0)
-        return fail(rc);
-    b->grid_rg = std::max(1, cus * std::max(1, std::min(per_cu_rg, per_cu_rg32)));
     if ((rc = upload_tasks(b)) < 0) return fail(rc);
     *out = b;
     return warn;
@@ -591,7 +674,8 @@ int ace_batch_destroy(ace_batch *b)
 {
     if (!b) return ACE_E_ARG;
     drop_graphs(b);
-    void *ptrs[] = {b->arena_a, b->arena_b, b->inst, b->order_dev, b->counter, b->trip};
+    void *ptrs[] = {b->arena_a, b->arena_b, b->inst,   b->order_dev, b->packed_dev,
+                    b->pieces,  b->trip,    b->partials, b->chunk_first};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (b->capture) (void)hipStreamDestroy(b->capture);
@@ -643,14 +727,21 @@ int ace_batch_set_phi0(ace_batch *b, int i, const double *phi0, int where)
 int ace_batch_set_all(ace_batch *b, const double *all, int where)
 {
     if (!b || !all || (where != ACE_HOST && where != ACE_DEVICE)) return ACE_E_ARG;
-    int64_t src = 0;
     int warn = ACE_OK;
-    for (int i = 0; i < b->count; ++i) {
-        const int rc = ace_batch_set_phi0(b, i, all + src, where);
-        if (rc < 0) return rc;
-        if (rc > 0) warn = rc;
-        src += b->host_inst[i].total;
+    const double *src = all;
+    if (where == ACE_HOST) {
+        for (int64_t j = 0; j < b->packed_total; ++j) {
+            if (!isfinite(all[j])) return ACE_E_NONFINITE;
+            if (fabs(all[j]) > 1.0) warn = ACE_W_PHI0_GT1;
+        }
+        // one copy into the second arena (scratch between steps), spread out from there
+        BT_HIP(hipMemcpyAsync(b->arena_b, all, sizeof(double) * b->packed_total, hipMemcpyHostToDevice, b->stream));
+        src = b->arena_b;
     }
+    hipLaunchKernelGGL(k_batch_copy, dim3(b->n_chunks), dim3(kChunkThreads), 0, b->stream, b->inst, chunk_pieces(b),
+                       b->packed_dev, 0, src, b->arena_a);
+    BT_HIP(hipGetLastError());
+    if (where == ACE_HOST) BT_HIP(hipStreamSynchronize(b->stream));
     return warn;
 }
 
@@ -658,15 +749,17 @@ int ace_batch_step(ace_batch *b, int64_t nsteps)
 {
     if (!b || nsteps < 0) return ACE_E_ARG;
     if (nsteps == 0) return ACE_OK;
-    if (!b->use_graphs) {
-        hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, b->stream, b->counter);
-        launch_batch(b, b->stream, nsteps);
-        BT_HIP(hipGetLastError());
-        return ACE_OK;
+    while (nsteps > 0) {
+        const int64_t n = nsteps > 2 * kGraphSteps ? kGraphSteps : nsteps;
+        if (b->use_graphs) {
+            hipGraphExec_t e = nullptr;
+            BT_TRY(get_graph(b, n, &e));
+            BT_HIP(hipGraphLaunch(e, b->stream));
+        } else {
+            BT_HIP(launch_batch(b, b->stream, n));
+        }
+        nsteps -= n;
     }
-    hipGraphExec_t e = nullptr;
-    BT_TRY(get_graph(b, nsteps, &e));
-    BT_HIP(hipGraphLaunch(e, b->stream));
     return ACE_OK;
 }
 
@@ -675,7 +768,7 @@ int ace_batch_set_region(ace_batch *b, int rows)
     if (!b || (rows != 0 && rows != 32 && rows != 64)) return ACE_E_ARG;
     if (rows != b->region) {
         b->region = rows;
-        drop_graphs(b);  // the captured launches carry the old region
+        return upload_tasks(b);
     }
     return ACE_OK;
 }
@@ -690,8 +783,10 @@ int ace_batch_set_graphs(ace_batch *b, int enable)
 int ace_batch_monitor(ace_batch *b, double *E, double *maxn)
 {
     if (!b || !E || !maxn) return ACE_E_ARG;
-    hipLaunchKernelGGL(k_batch_monitor, dim3(b->count), dim3(256), 0, b->stream, b->inst,
-                       b->arena_a, b->trip);
+    hipLaunchKernelGGL(k_batch_monitor, dim3(b->n_chunks), dim3(kChunkThreads), 0, b->stream, b->inst,
+                       chunk_pieces(b), b->arena_a, b->partials);
+    hipLaunchKernelGGL(k_batch_monitor_sum, dim3(b->count), dim3(64), 0, b->stream, b->chunk_first, b->partials,
+                       b->trip);
     BT_HIP(hipGetLastError());
     std::vector<double> t(3 * (size_t)b->count);
     BT_HIP(hipMemcpyAsync(t.data(), b->trip, sizeof(double) * t.size(), hipMemcpyDeviceToHost,
@@ -720,12 +815,15 @@ int ace_batch_get_phi(ace_batch *b, int i, double *out, int where)
 
 int ace_batch_get_all(ace_batch *b, double *out, int where)
 {
-    if (!b || !out) return ACE_E_ARG;
-    int64_t dst = 0;
-    for (int i = 0; i < b->count; ++i) {
-        const int rc = ace_batch_get_phi(b, i, out + dst, where);
-        if (rc < 0) return rc;
-        dst += b->host_inst[i].total;
+    if (!b || !out || (where != ACE_HOST && where != ACE_DEVICE)) return ACE_E_ARG;
+    // gathered back to back: in the caller's memory, or in the second arena for one copy to the host
+    double *dst = where == ACE_DEVICE ? out : b->arena_b;
+    hipLaunchKernelGGL(k_batch_copy, dim3(b->n_chunks), dim3(kChunkThreads), 0, b->stream, b->inst, chunk_pieces(b),
+                       b->packed_dev, 1, b->arena_a, dst);
+    BT_HIP(hipGetLastError());
+    if (where == ACE_HOST) {
+        BT_HIP(hipMemcpyAsync(out, dst, sizeof(double) * b->packed_total, hipMemcpyDeviceToHost, b->stream));
+        BT_HIP(hipStreamSynchronize(b->stream));
     }
     return ACE_OK;
 }
@@ -740,9 +838,10 @@ int ace_batch_set_resident_limit(ace_batch *b, int64_t limit)
 int ace_batch_set_depth(ace_batch *b, int depth)
 {
     if (!b || depth < 1 || depth > kMaxDepth) return ACE_E_ARG;
+    b->depth_fixed = 1;
     if (depth != b->depth) {
         b->depth = depth;
-        drop_graphs(b);  // the captured launches carry the old depth
+        return upload_tasks(b);
     }
     return ACE_OK;
 }
@@ -769,18 +868,22 @@ int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap
     int best_depth = b->depth;
     int best_region = b->region;
     std::string rec = "{\"kind\": \"batch\", \"trial_steps\": " + std::to_string(trial_steps) +
-                      ", \"workgroups\": " + std::to_string(b->grid) +
-                      ", \"workgroups_regions\": " + std::to_string(b->grid_rg) + ", \"candidates\": [";
+                      ", \"instances\": " + std::to_string(b->count) + ", \"candidates\": [";
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (rc >= 0) rc = hip_status(hipEventCreate(&e0));
     if (rc >= 0) rc = hip_status(hipEventCreate(&e1));
     bool first = true;
+    auto choose = [&](int64_t lim, int depth, int region) {
+        b->resident_limit = lim;
+        b->depth = depth;
+        b->depth_fixed = 1;
+        b->region = region;
+        return upload_tasks(b);
+    };
     // times one batch step of trial_steps for (lim, depth, region); returns ms or a negative error
     auto trial = [&](int64_t lim, int depth, int region, double *ms_out) -> int {
         int r;
-        if ((r = ace_batch_set_resident_limit(b, lim)) < 0) return r;
-        if ((r = ace_batch_set_depth(b, depth)) < 0) return r;
-        if ((r = ace_batch_set_region(b, region)) < 0) return r;
+        if ((r = choose(lim, depth, region)) < 0) return r;
         if ((r = restore()) < 0) return r;
         if ((r = ace_batch_step(b, trial_steps)) < 0) return r;  // builds the graph, warms up
         if ((r = restore()) < 0) return r;
@@ -802,6 +905,7 @@ int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap
     for (int region : regions)
         for (int depth : depths) {
             if (rc < 0) break;
+            if (region == 0 && depth != 4) continue;  // (a whole instance per workgroup: only where all are small)
             double ms = 0.0;
             if ((rc = trial(lim0, depth, region, &ms)) < 0) break;
             if (ms < best_ms) {
@@ -823,9 +927,7 @@ int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    if (rc >= 0) rc = ace_batch_set_resident_limit(b, best_lim);
-    if (rc >= 0) rc = ace_batch_set_depth(b, best_depth);
-    if (rc >= 0) rc = ace_batch_set_region(b, best_region);
+    if (rc >= 0) rc = choose(best_lim, best_depth, best_region);
     if (rc >= 0) rc = restore();
     if (rc >= 0) rc = hip_status(hipStreamSynchronize(b->stream));
     (void)hipFree(save);

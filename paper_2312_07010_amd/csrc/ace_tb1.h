@@ -59,5 +59,76 @@ __device__ __forceinline__ void monitor(const double (&v)[R], int first, Own own
     }
 }
 
+// All `nsteps` steps of a field of n nodes in one workgroup of
+// ceil(n / (64 R - 2 K)) wavefronts (at most; further ones only keep the
+// barriers), in place: each wavefront advances its segment up to K steps in
+// registers, then the wavefronts exchange their output nodes through the two
+// LDS buffers fb[0 .. stride) and fb[stride .. 2 stride), stride > n.  MON:
+// the monitor triple of steps 0, every, ... to mon[3 j ...] (red: LDS of
+// block_reduce_store).
+template <int BC, int RV, int R, bool MON>
+__device__ __forceinline__ void resident(int n, const StepCoef &c, double *__restrict__ field, int64_t nsteps,
+                                         int64_t every, double *__restrict__ mon, int K, double *fb, int stride,
+                                         double *red)
+{
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int o0 = wave * (64 * R - 2 * K);
+    const int o1 = o0 + 64 * R - 2 * K < n ? o0 + 64 * R - 2 * K : n;
+    const int first = o0 - K + lane * R;
+    // where this lane's nodes come from: slot n of the buffers holds 0, the
+    // Dirichlet wall
+    int src[R], sgn[R];
+    double v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        src[r] = source<BC>(first + r, n, sgn[r]);
+        const double x = field[src[r]];
+        v[r] = (BC != BC_HD || sgn[r] > 0) ? x : (sgn[r] < 0 ? -x : 0.0);
+        if (BC == BC_HD && sgn[r] == 0) src[r] = n;
+    }
+    if (threadIdx.x == 0) {
+        fb[n] = 0.0;
+        fb[stride + n] = 0.0;
+    }
+    auto own = [&](int i) { return i >= o0 && i < o1; };
+    int64_t jm = 0, done = 0;
+    int64_t due = MON ? 0 : nsteps + 1;  // next monitored step
+    double *f = fb, *g = fb + stride;
+    for (;;) {
+        if (MON && done == due) {
+            MonAcc m;
+            mon_zero(m);
+            monitor<BC>(v, first, own, m);
+            __syncthreads();  // every thread is past the last use of red
+            block_reduce_store(m, red, mon + 3 * jm);
+            ++jm;
+            due += every;
+        }
+        if (done >= nsteps) break;
+        // up to the next monitor in rounds of equal length
+        const int64_t left = (due < nsteps ? due : nsteps) - done;
+        const int rounds = (int)((left + K - 1) / K);
+        const int kb = (int)((left + rounds - 1) / rounds);
+        for (int k = 0; k < kb; ++k) step<R, RV>(v, c);
+        done += kb;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (own(first + r)) f[first + r] = v[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double x = f[src[r]];
+            v[r] = (BC == BC_HD && sgn[r] < 0) ? -x : x;
+        }
+        double *const t = f;
+        f = g;
+        g = t;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (own(first + r)) field[first + r] = v[r];
+}
+
 }  // namespace tb1
 }  // namespace ace

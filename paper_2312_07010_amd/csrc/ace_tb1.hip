@@ -57,65 +57,11 @@ __global__ __launch_bounds__(64 * R1_WAVES) void k_resident1(int n, StepCoef c0,
                                                             int64_t nsteps, int64_t every, double *__restrict__ mon,
                                                             int K)
 {
-    __shared__ double fb[2][RESIDENT_MAX + 1];
+    __shared__ double fb[2 * (RESIDENT_MAX + 1)];
     __shared__ double red[3 * R1_WAVES];
     const StepCoef c = coef_vgpr<RV>(c0);
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int o0 = wave * (64 * R - 2 * K);
-    const int o1 = o0 + 64 * R - 2 * K < n ? o0 + 64 * R - 2 * K : n;
-    const int first = o0 - K + lane * R;
-    // where this lane's nodes come from: slot n of the buffers holds 0, the
-    // Dirichlet wall
-    int src[R], sgn[R];
-    double v[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        src[r] = tb1::source<BC>(first + r, n, sgn[r]);
-        const double x = field[src[r]];
-        v[r] = (BC != BC_HD || sgn[r] > 0) ? x : (sgn[r] < 0 ? -x : 0.0);
-        if (BC == BC_HD && sgn[r] == 0) src[r] = n;
-    }
-    if (threadIdx.x == 0) {
-        fb[0][n] = 0.0;
-        fb[1][n] = 0.0;
-    }
-    auto own = [&](int i) { return i >= o0 && i < o1; };
-    int64_t jm = 0, step = 0;
-    int64_t due = every > 0 ? 0 : nsteps + 1;  // next monitored step
-    int cb = 0;
-    for (;;) {
-        if (step == due) {
-            MonAcc m;
-            mon_zero(m);
-            tb1::monitor<BC>(v, first, own, m);
-            __syncthreads();  // every thread is past the last use of red
-            block_reduce_store(m, red, mon + 3 * jm);
-            ++jm;
-            due += every;
-        }
-        if (step >= nsteps) break;
-        // up to the next monitor in rounds of equal length
-        const int64_t left = (due < nsteps ? due : nsteps) - step;
-        const int rounds = (int)((left + K - 1) / K);
-        const int kb = (int)((left + rounds - 1) / rounds);
-        for (int k = 0; k < kb; ++k) tb1::step<R, RV>(v, c);
-        step += kb;
-        double *f = fb[cb];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (own(first + r)) f[first + r] = v[r];
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const double x = f[src[r]];
-            v[r] = (BC == BC_HD && sgn[r] < 0) ? -x : x;
-        }
-        cb ^= 1;
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (own(first + r)) field[first + r] = v[r];
+    if (every > 0) tb1::resident<BC, RV, R, true>(n, c, field, nsteps, every, mon, K, fb, RESIDENT_MAX + 1, red);
+    else tb1::resident<BC, RV, R, false>(n, c, field, nsteps, 0, nullptr, K, fb, RESIDENT_MAX + 1, red);
 }
 
 template <class F>

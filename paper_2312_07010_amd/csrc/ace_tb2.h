@@ -13,8 +13,9 @@
 //     and below its last row, which come from the neighbouring wavefronts
 //     through two LDS edge rows per wavefront, double-buffered by level
 //     parity (one workgroup barrier per level).
-// After level k only region rows k .. RH-1-k are still needed, so the rows
-// outside are skipped (wave-uniform tests).
+// After level k only region rows k .. RH-1-k are still needed, and of a tile
+// that reaches past the field's last row only those up to S - k past it, so
+// the rows outside are skipped (wave-uniform tests).
 //
 // Nodes outside the domain are loaded as the images the boundary condition
 // makes of the field: periodic wraps; Neumann reflects about the wall half a
@@ -133,15 +134,15 @@ struct Region {
         }
     }
 
-    // Advances v (level 0, loaded) K levels; MON accumulates the monitor
-    // terms of level 0 over the tile interior into m; level K (LEVELS: every
+    // Advances v (level 0, loaded) S <= K levels; MON accumulates the monitor
+    // terms of level 0 over the tile interior into m; level S (LEVELS: every
     // level k at out + (k - 1) * level_stride) goes to the tile interior.
     // Ends with every wavefront past its last read of EB only if the caller
     // adds a barrier before EB is written again.
     template <bool MON, bool LEVELS, int RV>
     __device__ __forceinline__ void advance(const Shape &s, const StepCoef &c, double (&v)[RYT],
                                             double *__restrict__ out, int64_t level_stride, double *EB,
-                                            MonAcc &m) const
+                                            MonAcc &m, int S) const
     {
         auto eb = [&](int par, int side, int w) -> double * { return EB + ((par * 2 + side) * TRW + w) * RX; };
         // per row: the output offset of a tile-interior node in the domain (-1
@@ -155,6 +156,8 @@ struct Region {
             oof[r] = (xin && ry >= K && ry < RH - K && yg >= 0 && yg < M1) ? yg * M2 + xg : -1;
             yb0[r] = (yg == 0);
         }
+        // rows from H - k on are not needed at level k
+        const int H = M1 - yr0 + S < RH ? M1 - yr0 + S : RH;
         eb(0, 0, tr)[tx] = v[0];
         eb(0, 1, tr)[tx] = v[RYT - 1];
         __syncthreads();
@@ -178,7 +181,7 @@ struct Region {
             for (int r = 0; r < RYT; ++r) {
                 nv[r] = v[r];
                 const int ry = tr * RYT + r;
-                if (!FULL && (ry < k || ry >= RH - k)) continue;  // wave-uniform: a ring row of this level
+                if (!FULL && (ry < k || ry >= H - k)) continue;  // wave-uniform: a ring row of this level
                 const double p = v[r];
                 const double ym = (r > 0) ? v[r > 0 ? r - 1 : 0] : eT;
                 const double yp = (r < RYT - 1) ? v[r < RYT - 1 ? r + 1 : 0] : eB;
@@ -219,16 +222,16 @@ struct Region {
         using T = std::true_type;
         using F = std::false_type;
         const int row0 = tr * RYT;
-        for (int k = 1; k < K; ++k) {
-            const bool full = row0 >= k && row0 + RYT <= RH - k;
+        for (int k = 1; k < S; ++k) {
+            const bool full = row0 >= k && row0 + RYT <= H - k;
             if (full) level(k, T(), std::integral_constant<bool, LEVELS>());
             else level(k, F(), std::integral_constant<bool, LEVELS>());
             eb(k & 1, 0, tr)[tx] = v[0];
             eb(k & 1, 1, tr)[tx] = v[RYT - 1];
             __syncthreads();
         }
-        if (row0 >= K && row0 + RYT <= RH - K) level(K, T(), T());
-        else level(K, F(), T());
+        if (row0 >= S && row0 + RYT <= H - S) level(S, T(), T());
+        else level(S, F(), T());
     }
 };
 
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(RX * TRW) void k_tb2(Shape s, StepCoef c, const dou
     g.load(s, in, v);
     MonAcc m;
     mon_zero(m);
-    g.template advance<MON, LEVELS, RV>(s, coef_vgpr<RV>(c), v, out, level_stride, EB, m);
+    g.template advance<MON, LEVELS, RV>(s, coef_vgpr<RV>(c), v, out, level_stride, EB, m, K);
     if (MON) block_reduce_store(m, red, partials + 3 * blockIdx.x);
 }
 
