@@ -374,9 +374,10 @@ int ace_pop_set_stream(ace_pop *p, void *hip_stream);
  * tiled update, which also writes phi of the new populations (the sum over
  * k in the fixed order every moment here uses), so the next step reads phi
  * alone: the regularized update depends on the populations only through
- * phi (Sec. 2), and a step moves 8 (2d+1) + 16 bytes per node (one moment
- * pass after ace_pop_set_phi0 / ace_pop_set_populations or another kernel's
- * step; d >= 2, two more fields of device memory);
+ * phi (Sec. 2), and a call's last step moves 8 (2d+1) + 16 bytes per node,
+ * the steps before it 16 (their populations are never read; one moment pass
+ * after ace_pop_set_populations or another kernel's step; d >= 2, two more
+ * fields of device memory);
  * ACE_POP_AUTO: the carried form for d >= 2, direct for d = 1. */
 #define ACE_POP_AUTO 0
 #define ACE_POP_DIRECT 1

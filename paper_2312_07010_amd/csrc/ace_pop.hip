@@ -30,7 +30,11 @@
 // same tiled update reading phi (16 (2d+1) + 16 bytes); and the carried
 // form, in which each update also writes phi of its new populations (summed
 // in the same order as every moment here, so it equals a moment pass bit
-// for bit) and the next update reads only that (8 (2d+1) + 16 bytes).
+// for bit) and the next update reads only that (8 (2d+1) + 16 bytes).  Within
+// one ace_pop_step call of several steps only the last one's populations are
+// ever read, so the carried form's steps before it write phi alone (16 bytes
+// per node update): at 512^3 the call's inner steps took 1.84 ms each with the
+// populations.
 #include <math.h>
 #include <string.h>
 
@@ -38,7 +42,7 @@
 #include <new>
 
 #include "../../include/ace.h"
-#include "ace_device.h"
+#include "ace_col.h"
 #include "ace_runtime.h"
 
 namespace ace {
@@ -169,8 +173,9 @@ using PopTileDefault = PopTile<128, 4, 4>;  // 16 x 128, 512 threads
 // FUSED: `src` holds the populations and phi of every node the tile needs is
 // summed here from its 2d+1 arrays (k = 0..2d in order, as everywhere);
 // otherwise `src` is phi (written by k_pop_moment or carried).  CARRY: phi of
-// the new populations (k = 0..2d in order) also goes to phi_out.
-template <class T, int D, int BC, int RV, bool FUSED, bool CARRY>
+// the new populations (k = 0..2d in order) also goes to phi_out.  POPS:
+// the populations are written.
+template <class T, int D, int BC, int RV, bool FUSED, bool CARRY, bool POPS>
 __global__ __launch_bounds__(T::UNT) void k_pop_update(Shape s, PopCoef c, const double *__restrict__ src,
                                                        double *__restrict__ fout, double *__restrict__ phi_out,
                                                        int tiles_x, int tiles_y, int zchunk)
@@ -302,8 +307,10 @@ __global__ __launch_bounds__(T::UNT) void k_pop_update(Shape s, PopCoef c, const
             // the new populations are not read again by this launch:
             // streaming (non-temporal) stores keep them out of the way of the
             // inputs in L2
+            if (POPS) {
 #pragma unroll
-            for (int k = 0; k < Q; ++k) __builtin_nontemporal_store(outv[r][k], fout + k * c.ps + o);
+                for (int k = 0; k < Q; ++k) __builtin_nontemporal_store(outv[r][k], fout + k * c.ps + o);
+            }
             if (CARRY) {
                 // the zeroth moment of the new populations, in the order of phi_at
                 double v = outv[r][0];
@@ -366,6 +373,62 @@ __global__ __launch_bounds__(T::UNT) void k_pop_update(Shape s, PopCoef c, const
     }
 }
 
+// ---- carried update through the cache (fields that fit there) ---------------
+// The carried form with a thread per column of Z planes (in 2D: of Z rows; the
+// slowest axis is the one the column runs along), all its phi in flight at
+// once, as the FD step's column kernel.  The tiled march above has one
+// workgroup per 16 x 128 tile and 128 planes: 2 of them on 34 x 29 x 33, where
+// a step took 64 us.
+template <int D, int BC, int RV, int Z, bool POPS>
+__global__ __launch_bounds__(col::CNT) void k_pop_col(int M0, int M1, int M2, int nb, PopCoef c,
+                                                      const double *__restrict__ phi, double *__restrict__ fout,
+                                                      double *__restrict__ phi_out)
+{
+    constexpr int Q = 2 * D + 1;
+    const int t = (int)xcd_tile(blockIdx.x, gridDim.x);
+    const int PS = M1 * M2;
+    const int z0 = (t / nb) * Z;
+    const int nz = M0 - z0 < Z ? M0 - z0 : Z;
+    const col::Col k = col::column<BC>((t - (t / nb) * nb) * col::CNT + (int)threadIdx.x, M1, M2);
+    double q[Z + 2], ym[Z], yp[Z], xm[Z], xp[Z];
+    q[0] = col::load(col::plane_at<BC>(phi, z0 - 1, M0, PS), k.o);
+#pragma unroll
+    for (int i = 0; i < Z; ++i) {
+        // (planes past the last one repeat it: loaded, not used)
+        const __amdgpu_buffer_rsrc_t r = col::plane_at<BC>(phi, i < nz ? z0 + i : z0 + nz, M0, PS);
+        q[i + 1] = col::load(r, k.o);
+        if (D == 3) {
+            ym[i] = col::load(r, k.ym);
+            yp[i] = col::load(r, k.yp);
+        }
+        xm[i] = col::load(r, k.xm);
+        xp[i] = col::load(r, k.xp);
+    }
+    q[Z + 1] = col::load(col::plane_at<BC>(phi, z0 + nz, M0, PS), k.o);
+    const bool in = k.o != col::kNone;
+#pragma unroll
+    for (int i = 0; i < Z; ++i) {
+        if (i >= nz || !in) break;
+        double out[Q];
+        if constexpr (D == 3) {
+            const double lo[3] = {q[i], ym[i], xm[i]}, hi[3] = {q[i + 2], yp[i], xp[i]};
+            pop_update<3, RV>(q[i + 1], lo, hi, c, out);
+        } else {
+            const double lo[2] = {q[i], xm[i]}, hi[2] = {q[i + 2], xp[i]};
+            pop_update<2, RV>(q[i + 1], lo, hi, c, out);
+        }
+        const int64_t o = (int64_t)(z0 + i) * PS + (k.o >> 3);
+        if (POPS) {
+#pragma unroll
+            for (int n = 0; n < Q; ++n) __builtin_nontemporal_store(out[n], fout + n * c.ps + o);
+        }
+        double v = out[0];
+#pragma unroll
+        for (int n = 1; n < Q; ++n) v += out[n];
+        phi_out[o] = v;
+    }
+}
+
 __global__ void k_pop_moment(int q, int64_t ps, int64_t n, const double *__restrict__ f,
                              double *__restrict__ phi)
 {
@@ -376,14 +439,21 @@ __global__ void k_pop_moment(int q, int64_t ps, int64_t n, const double *__restr
     phi[i] = v;
 }
 
+// Equilibrium populations of phi, and (carry not null) their sum in the order
+// of phi_at.
 __global__ void k_pop_equilibrium(int q, int64_t ps, int64_t n, double w0, double w1,
-                                  const double *__restrict__ phi, double *__restrict__ f)
+                                  const double *__restrict__ phi, double *__restrict__ f, double *__restrict__ carry)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double p = phi[i];
     f[i] = w0 * p;
-    for (int k = 1; k < q; ++k) f[k * ps + i] = w1 * p;
+    double v = w0 * p;
+    for (int k = 1; k < q; ++k) {
+        f[k * ps + i] = w1 * p;
+        v += w1 * p;
+    }
+    if (carry) carry[i] = v;
 }
 
 constexpr int POP_ZCHUNK = 128;  // planes per workgroup in 3D
@@ -391,10 +461,40 @@ constexpr int POP_ZCHUNK = 128;  // planes per workgroup in 3D
 // mode: 0 one thread per node; 1 tiled, phi summed in the tile (fused);
 // 2 split: k_pop_moment writes phi to `phi`, then the tiled update reads it;
 // 3 carried: the tiled update reads phi from `phi` and writes phi of the new
-// populations to phi_next.
+// populations to phi_next, and the populations themselves if `pops`.
+template <int D, int BC, int RV>
+hipError_t launch_pop_col(const Shape &s, const PopCoef &c, double *fout, const double *phi, double *phi_next,
+                          bool pops, hipStream_t st)
+{
+    // the column runs along axis 0 (3D) or the rows (2D)
+    const int M0 = (int)(D == 3 ? s.M0 : s.M1), M1 = (int)(D == 3 ? s.M1 : 1), M2 = (int)s.M2;
+    const int nb = (int)(((int64_t)M1 * M2 + col::CNT - 1) / col::CNT);
+    // as many planes as keep two workgroups on each of 256 CUs, at least 2
+    const int Z = (int64_t)nb * ((M0 + 3) / 4) >= 512 ? 4 : 2;
+    const dim3 grid((unsigned)(nb * ((M0 + Z - 1) / Z)));
+    auto go = [&](auto Zc) {
+        constexpr int ZZ = decltype(Zc)::value;
+        if (pops)
+            hipLaunchKernelGGL((k_pop_col<D, BC, RV, ZZ, true>), grid, dim3(col::CNT), 0, st, M0, M1, M2, nb, c, phi,
+                               fout, phi_next);
+        else
+            hipLaunchKernelGGL((k_pop_col<D, BC, RV, ZZ, false>), grid, dim3(col::CNT), 0, st, M0, M1, M2, nb, c, phi,
+                               fout, phi_next);
+        return hipGetLastError();
+    };
+    return Z == 4 ? go(RootTag<4>()) : go(RootTag<2>());
+}
+
+// Fields the column kernel takes: up to 20 million nodes (past the caches the
+// tiled march reads each plane once), with 32-bit plane offsets.
+bool pop_col_applies(const Shape &s)
+{
+    return s.d >= 2 && s.M0 * s.M1 * s.M2 <= 20000000 && s.M1 * s.M2 < ((int64_t)1 << 28);
+}
+
 template <int D, int BC, int RV>
 hipError_t launch_pop_t(const Shape &s, const PopCoef &c, const double *fin, double *fout, int mode,
-                        double *phi, double *phi_next, hipStream_t st)
+                        double *phi, double *phi_next, bool pops, hipStream_t st)
 {
     const int64_t n = s.M0 * s.M1 * s.M2;
     if (mode == 0 || D == 1) {
@@ -403,21 +503,26 @@ hipError_t launch_pop_t(const Shape &s, const PopCoef &c, const double *fin, dou
         return hipGetLastError();
     }
     if constexpr (D >= 2) {
+        if (mode == 3 && pop_col_applies(s)) return launch_pop_col<D, BC, RV>(s, c, fout, phi, phi_next, pops, st);
         using T = PopTileDefault;
         const int64_t chunks = (D == 3) ? (s.M0 + POP_ZCHUNK - 1) / POP_ZCHUNK : 1;
         const int utx = (int)((s.M2 + T::UX - 1) / T::UX);
         const int uty = (int)((s.M1 + T::UOY - 1) / T::UOY);
         const int64_t ublk = (int64_t)utx * uty * chunks;
         if (mode == 1) {
-            hipLaunchKernelGGL((k_pop_update<T, D, BC, RV, true, false>), dim3((unsigned)ublk), dim3(T::UNT), 0,
+            hipLaunchKernelGGL((k_pop_update<T, D, BC, RV, true, false, true>), dim3((unsigned)ublk), dim3(T::UNT), 0,
                                st, s, c, fin, fout, nullptr, utx, uty, POP_ZCHUNK);
         } else if (mode == 3) {
-            hipLaunchKernelGGL((k_pop_update<T, D, BC, RV, false, true>), dim3((unsigned)ublk), dim3(T::UNT), 0,
-                               st, s, c, phi, fout, phi_next, utx, uty, POP_ZCHUNK);
+            if (pops)
+                hipLaunchKernelGGL((k_pop_update<T, D, BC, RV, false, true, true>), dim3((unsigned)ublk), dim3(T::UNT),
+                                   0, st, s, c, phi, fout, phi_next, utx, uty, POP_ZCHUNK);
+            else
+                hipLaunchKernelGGL((k_pop_update<T, D, BC, RV, false, true, false>), dim3((unsigned)ublk),
+                                   dim3(T::UNT), 0, st, s, c, phi, fout, phi_next, utx, uty, POP_ZCHUNK);
         } else {
             hipLaunchKernelGGL(k_pop_moment, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, 2 * D + 1,
                                c.ps, n, fin, phi);
-            hipLaunchKernelGGL((k_pop_update<T, D, BC, RV, false, false>), dim3((unsigned)ublk), dim3(T::UNT), 0,
+            hipLaunchKernelGGL((k_pop_update<T, D, BC, RV, false, false, true>), dim3((unsigned)ublk), dim3(T::UNT), 0,
                                st, s, c, phi, fout, nullptr, utx, uty, POP_ZCHUNK);
         }
     }
@@ -426,33 +531,33 @@ hipError_t launch_pop_t(const Shape &s, const PopCoef &c, const double *fin, dou
 
 template <int D, int BC>
 hipError_t launch_pop_root(const Shape &s, const PopCoef &c, const double *fin, double *fout, int mode,
-                          double *phi, double *phi_next, hipStream_t st)
+                          double *phi, double *phi_next, bool pops, hipStream_t st)
 {
     return with_root(c.sc.rv, [&](auto RVc) {
         constexpr int RV = decltype(RVc)::value;  // (the populations have no explicit scheme)
-        return launch_pop_t<D, BC, RV == ROOT_FEX ? 0 : RV>(s, c, fin, fout, mode, phi, phi_next, st);
+        return launch_pop_t<D, BC, RV == ROOT_FEX ? 0 : RV>(s, c, fin, fout, mode, phi, phi_next, pops, st);
     });
 }
 
 template <int D>
 hipError_t launch_pop_bc(const Shape &s, const PopCoef &c, const double *fin, double *fout, int mode,
-                         double *phi, double *phi_next, hipStream_t st)
+                         double *phi, double *phi_next, bool pops, hipStream_t st)
 {
     switch (s.bc) {
-    case BC_HN: return launch_pop_root<D, BC_HN>(s, c, fin, fout, mode, phi, phi_next, st);
-    case BC_HD: return launch_pop_root<D, BC_HD>(s, c, fin, fout, mode, phi, phi_next, st);
-    case BC_P: return launch_pop_root<D, BC_P>(s, c, fin, fout, mode, phi, phi_next, st);
+    case BC_HN: return launch_pop_root<D, BC_HN>(s, c, fin, fout, mode, phi, phi_next, pops, st);
+    case BC_HD: return launch_pop_root<D, BC_HD>(s, c, fin, fout, mode, phi, phi_next, pops, st);
+    case BC_P: return launch_pop_root<D, BC_P>(s, c, fin, fout, mode, phi, phi_next, pops, st);
     default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_pop_step(const Shape &s, const PopCoef &c, const double *fin, double *fout, int mode,
-                           double *phi, double *phi_next, hipStream_t st)
+                           double *phi, double *phi_next, bool pops, hipStream_t st)
 {
     switch (s.d) {
-    case 1: return launch_pop_bc<1>(s, c, fin, fout, mode, phi, phi_next, st);
-    case 2: return launch_pop_bc<2>(s, c, fin, fout, mode, phi, phi_next, st);
-    case 3: return launch_pop_bc<3>(s, c, fin, fout, mode, phi, phi_next, st);
+    case 1: return launch_pop_bc<1>(s, c, fin, fout, mode, phi, phi_next, pops, st);
+    case 2: return launch_pop_bc<2>(s, c, fin, fout, mode, phi, phi_next, pops, st);
+    case 3: return launch_pop_bc<3>(s, c, fin, fout, mode, phi, phi_next, pops, st);
     default: return hipErrorInvalidValue;
     }
 }
@@ -588,14 +693,11 @@ int ace_pop_set_phi0(ace_pop *P, const double *phi0, int where)
         hipError_t e = hipMemcpyAsync(P->phi, phi0, bytes, hipMemcpyHostToDevice, P->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(P->stream);
         if (e != hipSuccess) return hip_status(e);
-    } else {
-        hipError_t e = hipMemcpyAsync(P->phi, phi0, bytes, hipMemcpyDeviceToDevice, P->stream);
-        if (e != hipSuccess) return hip_status(e);
     }
     hipLaunchKernelGGL(k_pop_equilibrium, dim3(blocks_for(n)), dim3(256), 0, P->stream, P->q, P->c.ps, n,
-                       P->c.w0, P->c.w1, P->phi, P->f[P->cur]);
+                       P->c.w0, P->c.w1, where == ACE_HOST ? P->phi : phi0, P->f[P->cur], P->carry[P->ccur]);
     P->steps = 0;
-    P->carry_ok = 0;
+    P->carry_ok = P->carry[P->ccur] ? 1 : 0;
     return hip_status(hipGetLastError());
 }
 
@@ -638,11 +740,13 @@ int ace_pop_step(ace_pop *P, int64_t nsteps)
         P->carry_ok = 1;
     }
     for (int64_t t = 0; t < nsteps; ++t) {
+        // (carried: the populations of the call's last step only)
+        const bool pops = mode != 3 || t == nsteps - 1;
         hipError_t e = launch_pop_step(P->shape, P->c, P->f[P->cur], P->f[P->cur ^ 1], mode,
                                        mode == 3 ? P->carry[P->ccur] : P->phi,
-                                       mode == 3 ? P->carry[P->ccur ^ 1] : nullptr, P->stream);
+                                       mode == 3 ? P->carry[P->ccur ^ 1] : nullptr, pops, P->stream);
         if (e != hipSuccess) return hip_status(e);
-        P->cur ^= 1;
+        if (pops) P->cur ^= 1;
         if (mode == 3) P->ccur ^= 1;
         ++P->steps;
     }
@@ -655,11 +759,19 @@ int ace_pop_get_phi(ace_pop *P, double *phi, int where)
     if (!P || !phi || (where != ACE_HOST && where != ACE_DEVICE)) return ACE_E_ARG;
     const int64_t n = P->p.total;
     double *dst = (where == ACE_DEVICE) ? phi : P->phi;
-    hipLaunchKernelGGL(k_pop_moment, dim3(blocks_for(n)), dim3(256), 0, P->stream, P->q, P->c.ps, n,
-                       P->f[P->cur], dst);
-    hipError_t e = hipGetLastError();
+    hipError_t e = hipSuccess;
+    const double *src = P->phi;
+    if (P->carry_ok) {  // the moment of the current populations is at hand
+        src = P->carry[P->ccur];
+        if (where == ACE_DEVICE)
+            e = hipMemcpyAsync(phi, src, sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice, P->stream);
+    } else {
+        hipLaunchKernelGGL(k_pop_moment, dim3(blocks_for(n)), dim3(256), 0, P->stream, P->q, P->c.ps, n,
+                           P->f[P->cur], dst);
+        e = hipGetLastError();
+    }
     if (e == hipSuccess && where == ACE_HOST) {
-        e = hipMemcpyAsync(phi, P->phi, sizeof(double) * (size_t)n, hipMemcpyDeviceToHost, P->stream);
+        e = hipMemcpyAsync(phi, src, sizeof(double) * (size_t)n, hipMemcpyDeviceToHost, P->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(P->stream);
     }
     return hip_status(e);
