@@ -662,10 +662,10 @@ int tb3_for(const ace_solver *s, int kernel, int64_t remaining, int *zc)
     return s->tail[remaining].v;
 }
 
-// One launch from buf[cur] into buf[cur^1] advancing 1 step, or up to
-// steps_per_launch_of() with the temporal-blocking kernels.  If want_mon,
-// the monitor partials of the input field are left in s->partials, their
-// count in *nparts.  Returns the number of steps taken (or a negative error).
+// One launch from in to out advancing 1 step, or up to steps_per_launch_of()
+// with the temporal-blocking kernels; the monitor partials of in go to parts
+// (if not null), their count to *nparts.  Returns the number of steps taken
+// (or a negative error).
 // Partial triples a monitored launch of `kernel` writes (the launch that
 // launch_steps makes for `remaining` steps).
 int64_t partials_for(const ace_solver *s, int kernel, int64_t remaining)
@@ -683,12 +683,9 @@ int64_t partials_for(const ace_solver *s, int kernel, int64_t remaining)
     return direct_partials_needed(s->shape);
 }
 
-int launch_steps(ace_solver *s, int kernel, int64_t remaining, bool want_mon, int64_t *nparts)
+int launch_between(const ace_solver *s, int kernel, const double *in, double *out, int64_t remaining, double *parts,
+                   int64_t *nparts)
 {
-    const double *in = s->buf[s->cur];
-    double *out = s->buf[s->cur ^ 1];
-    double *parts = want_mon ? s->partials : nullptr;
-    if (want_mon && 3 * partials_for(s, kernel, remaining) > s->partials_cap) return ACE_E_STATE;
     hipError_t e;
     int taken = 1, zc = 0;
     const int v3 = tb3_for(s, kernel, remaining, &zc);
@@ -711,10 +708,32 @@ int launch_steps(ace_solver *s, int kernel, int64_t remaining, bool want_mon, in
         e = launch_step_direct(s->shape, s->coef, in, out, parts, nparts, s->stream);
     }
     ACE_HIP(e);
+    return taken;
+}
+
+// The steps launch_between takes.
+int64_t steps_of_launch(const ace_solver *s, int kernel, int64_t remaining)
+{
+    int zc = 0;
+    const int v3 = tb3_for(s, kernel, remaining, &zc);
+    if (v3 >= 0) return TB3_TABLE[v3].depth;
+    if (kernel == ACE_KERNEL_TBLOCK && s->p.d == 3) return remaining >= 2 ? 2 : 1;
+    return std::min<int64_t>(steps_per_launch_of(s, kernel), remaining);
+}
+
+// One launch from buf[cur] into buf[cur^1]; if want_mon, the monitor partials
+// of the input field are left in s->partials, their count in *nparts.
+int launch_steps(ace_solver *s, int kernel, int64_t remaining, bool want_mon, int64_t *nparts)
+{
+    if (want_mon && 3 * partials_for(s, kernel, remaining) > s->partials_cap) return ACE_E_STATE;
+    const int taken = launch_between(s, kernel, s->buf[s->cur], s->buf[s->cur ^ 1], remaining,
+                                     want_mon ? s->partials : nullptr, nparts);
+    if (taken < 0) return taken;
     s->cur ^= 1;
     s->steps += taken;
     return taken;
 }
+
 
 // The whole run of `nsteps` in one workgroup (total <= RESIDENT_MAX).
 hipError_t run_resident(const ace_solver *s, int64_t nsteps, int64_t every)
@@ -852,6 +871,154 @@ int read_triple(ace_solver *s, const double *dev, double *host3)
     ACE_HIP(hipMemcpyAsync(s->pinned, dev, 3 * sizeof(double), hipMemcpyDeviceToHost, s->stream));
     ACE_HIP(hipStreamSynchronize(s->stream));
     memcpy(host3, s->pinned, 3 * sizeof(double));
+    return ACE_OK;
+}
+
+// Reverse sweep with the recompute of each segment in the launches of the one
+// after it (ace_adj2.hip).  Leaves lambda^0 in lam[*lc], dL/dkappa in gsum.
+int backward_regions(ace_solver *s, double *const lam[2], int *lc)
+{
+    const int64_t total = s->p.total, every = s->ck_every, nsteps = s->ck_steps;
+    // regions and depth with the least modelled time for a segment
+    int rows = 32, K = 8;
+    double best = 1e300;
+    for (int v = 0; v < 2; ++v)
+        for (int d = 2; d <= std::min<int64_t>(12, std::max<int64_t>(every, 2)); ++d) {
+            const int64_t launches = (std::min(every, nsteps) + d - 1) / d;
+            const double us = (double)launches * TB2_MODEL[v ? 2 : 1].us(2 * adj2_tiles(s->shape, v ? 64 : 32, d), d);
+            if (us >= best) continue;
+            best = us;
+            rows = v ? 64 : 32;
+            K = d;
+        }
+    const int n_tiles = (int)adj2_tiles(s->shape, rows, K);
+    auto seg = [&](int64_t j) { return s->seg + (j & 1) * (every + 1) * total; };  // phi^{j every + 1} ..
+    bool first = true;
+    for (int64_t j = s->ck_count; j >= 0; --j) {
+        // segment j backwards (j < ck_count) while segment j - 1 is recomputed
+        const int64_t n = j < s->ck_count ? std::min<int64_t>(every, nsteps - j * every) : 0;
+        const int64_t nf = j > 0 ? std::min<int64_t>(every, nsteps - (j - 1) * every) : 0;
+        int64_t back = n, fwd = 0;  // steps of the segment left; states recomputed
+        while (back > 0 || fwd < nf) {
+            Adj2Args a = {};
+            a.K = K;
+            a.stride = total;
+            a.Sr = (int)std::min<int64_t>(K, back);
+            a.Sf = (int)std::min<int64_t>(K, nf - fwd);
+            if (a.Sr > 0) {
+                const int64_t m = back - a.Sr;  // the launch ends at state m of the segment
+                a.n_rev = n_tiles;
+                a.mu_in = lam[*lc];
+                a.mu_out = lam[*lc ^ 1];
+                a.phi_first = m == 0 ? s->ckpt + j * total : seg(j) + (m - 1) * total;
+                a.phi_rest = seg(j) + m * total;
+                a.phi_end = first ? seg(j) + (back - 1) * total : nullptr;
+                a.last = j == 0 && m == 0;
+                a.gpart = s->gpart;
+                a.accumulate = !first;
+            }
+            if (a.Sf > 0) {
+                a.f_in = fwd == 0 ? s->ckpt + (j - 1) * total : seg(j - 1) + (fwd - 1) * total;
+                a.f_out = seg(j - 1) + fwd * total;
+            }
+            ACE_HIP(launch_adj2(rows, s->shape, s->coef, a, s->stream));
+            if (a.Sr > 0) {
+                *lc ^= 1;
+                first = false;
+            }
+            back -= a.Sr;
+            fwd += a.Sf;
+        }
+    }
+    ACE_HIP(launch_sum(s->gpart, n_tiles, s->gsum, 0, s->stream));
+    return ACE_OK;
+}
+
+// Reverse sweep step by step; the recompute of segment j-1 runs on a second
+// stream while segment j is swept backwards on the handle's, on alternating
+// segment buffers: events order each buffer's recompute after the previous
+// sweep that used it, and each sweep after its recompute.
+int backward_steps(ace_solver *s, int k, double *const lam[2], int *lc)
+{
+    const int64_t total = s->p.total, every = s->ck_every, nsteps = s->ck_steps;
+    const size_t bytes = (size_t)total * sizeof(double);
+    const int64_t npart = adjoint_partials_needed(s->shape);
+    const bool columns = col3d_supported(s->shape);  // mu form, one sum for the sweep
+    const bool blocked2d = (k == ACE_KERNEL_TBLOCK && s->p.d == 2);
+    if (k == ACE_KERNEL_TBLOCK && !blocked2d) k = one_step_kernel(s->shape);
+    if (!s->aux) ACE_HIP(hipStreamCreateWithFlags(&s->aux, hipStreamNonBlocking));
+    if (!s->ev_start) {
+        ACE_HIP(hipEventCreateWithFlags(&s->ev_start, hipEventDisableTiming));
+        for (int b = 0; b < 2; ++b) {
+            ACE_HIP(hipEventCreateWithFlags(&s->ev_rec[b], hipEventDisableTiming));
+            ACE_HIP(hipEventCreateWithFlags(&s->ev_rev[b], hipEventDisableTiming));
+        }
+    }
+    if (!columns) ACE_HIP(hipMemsetAsync(s->gsum, 0, sizeof(double), s->stream));
+    ACE_HIP(hipEventRecord(s->ev_start, s->stream));  // checkpoints are complete
+    ACE_HIP(hipStreamWaitEvent(s->aux, s->ev_start, 0));
+    bool first = true;
+    for (int64_t j = s->ck_count - 1; j >= 0; --j) {
+        const int b = (int)(j & 1);
+        double *seg = s->seg + b * (every + 1) * total;
+        const int64_t a = j * every;
+        const int64_t n = std::min<int64_t>(every, nsteps - a);
+        // --- recompute segment j on the second stream ---
+        ACE_HIP(hipStreamWaitEvent(s->aux, s->ev_rev[b], 0));
+        ACE_HIP(hipMemcpyAsync(seg, s->ckpt + j * total, bytes, hipMemcpyDeviceToDevice, s->aux));
+        if (blocked2d) {
+            const int per = steps_per_launch_of(s, ACE_KERNEL_TBLOCK);
+            for (int64_t i = 0; i < n;) {  // each launch writes its K intermediate states
+                const int K = (int)std::min<int64_t>(per, n - i);
+                ACE_HIP(launch_blocked2d(s, seg + i * total, seg + (i + 1) * total, nullptr, nullptr, K, total,
+                                         s->aux));
+                i += K;
+            }
+        } else {
+            for (int64_t i = 0; i < n; ++i) {
+                const double *in = seg + i * total;
+                double *out = seg + (i + 1) * total;
+                hipError_t e = (k == ACE_KERNEL_MARCH)
+                                   ? launch_step_march(s->shape, s->coef, in, out, nullptr, nullptr, s->aux)
+                                   : launch_step_direct(s->shape, s->coef, in, out, nullptr, nullptr, s->aux);
+                ACE_HIP(e);
+            }
+        }
+        ACE_HIP(hipEventRecord(s->ev_rec[b], s->aux));
+        // --- reverse sweep of segment j on the handle's stream ---
+        ACE_HIP(hipStreamWaitEvent(s->stream, s->ev_rec[b], 0));
+        int64_t parts = 0;  // partial sums of dL/dkappa written for this segment
+        if (blocked2d) {
+            // (deeper launches leave the 32-row regions of the reverse sweep small tiles)
+            const int rev = std::min(s->depth2, 8);
+            for (int64_t i = n; i > 0;) {  // K transposed steps per launch
+                const int K = (int)std::min<int64_t>(rev, i);
+                ACE_HIP(launch_adjoint_tblock2d(s->shape, s->coef, lam[*lc], seg + (i - K) * total, total,
+                                                lam[*lc ^ 1], s->gpart + parts, K, s->stream));
+                parts += tblock2d_blocks(s->shape, K);
+                *lc ^= 1;
+                i -= K;
+            }
+        } else {
+            for (int64_t i = n - 1; i >= 0; --i) {
+                if (columns) {
+                    ACE_HIP(launch_adjoint_col(s->shape, s->coef, lam[*lc], seg + i * total,
+                                               first ? seg + (i + 1) * total : nullptr, lam[*lc ^ 1], s->gpart,
+                                               j == 0 && i == 0, !first, s->stream));
+                    first = false;
+                } else {
+                    ACE_HIP(launch_adjoint_step(s->shape, s->coef, lam[*lc], seg + i * total,
+                                                seg + (i + 1) * total, lam[*lc ^ 1], s->gpart + parts, nullptr,
+                                                s->stream));
+                    parts += npart;
+                }
+                *lc ^= 1;
+            }
+        }
+        if (parts > 0) ACE_HIP(launch_sum(s->gpart, parts, s->gsum, 1, s->stream));
+        ACE_HIP(hipEventRecord(s->ev_rev[b], s->stream));
+    }
+    if (columns) ACE_HIP(launch_sum(s->gpart, adjoint_col_blocks(s->shape), s->gsum, 0, s->stream));
     return ACE_OK;
 }
 
@@ -1071,17 +1238,17 @@ int ace_set_graph_launches(ace_solver *s, int64_t launches)
 int ace_set_eps(ace_solver *s, double eps)
 {
     if (!s) return ACE_E_ARG;
-    Problem q;
-    int rc = derive(s->p.d, s->p.N, s->p.L, s->p.R, eps, s->p.dt, s->p.bc, q);
-    if (rc < 0) return rc;
-    q.scheme = s->p.scheme;
-    set_conditions(q);
-    rc = q.cond_ok ? ACE_OK : ACE_W_CONDITIONS;
-    s->p = q;
-    s->coef = coef_of(q);
+    if (!(eps > 0.0) || !isfinite(eps)) return ACE_E_ARG;
     s->ck_count = 0;  // checkpoints of the old eps are no longer valid
-    drop_graphs(s);   // captured launches carry the old coefficients
-    return rc;
+    if (eps != s->p.eps) {
+        // only kappa and the conditions depend on eps
+        s->p.eps = eps;
+        s->p.kappa = eps * eps * s->p.dt / (s->p.dx * s->p.dx);
+        set_conditions(s->p);
+        s->coef = coef_of(s->p);
+        drop_graphs(s);  // captured launches carry the old coefficients
+    }
+    return s->p.cond_ok ? ACE_OK : ACE_W_CONDITIONS;
 }
 
 int ace_set_scheme(ace_solver *s, int scheme)
@@ -1551,16 +1718,40 @@ int ace_forward_ckpt(ace_solver *s, const double *phi0, int where, int64_t nstep
     // size the reverse sweep's buffers now so ace_backward allocates nothing
     ACE_TRY(grow(&s->seg, &s->seg_cap, 2 * (every + 1) * total));
     ACE_TRY(grow(&s->lam, &s->lam_cap, 2 * total));
-    int64_t per_step = adjoint_partials_needed(s->shape);
-    if (tblock2d_supported(s->shape))
-        per_step = std::max<int64_t>(per_step, tblock2d_blocks(s->shape, tblock2d_max_depth()));
-    ACE_TRY(grow(&s->gpart, &s->gpart_cap, per_step * every));
+    int64_t parts = adjoint_partials_needed(s->shape) * every;
+    if (col3d_supported(s->shape)) parts = std::max(parts, adjoint_col_blocks(s->shape));
+    if (tblock2d_supported(s->shape)) {
+        parts = std::max<int64_t>(parts, tblock2d_blocks(s->shape, tblock2d_max_depth()) * every);
+        if (tb2_supported(s->shape)) parts = std::max(parts, adj2_tiles(s->shape, 32, 12));
+    }
+    ACE_TRY(grow(&s->gpart, &s->gpart_cap, parts));
     const size_t bytes = (size_t)total * sizeof(double);
+    const int k = effective_kernel(s);
+    const double *in = s->buf[s->cur];
+    ACE_HIP(hipMemcpyAsync(s->ckpt, in, bytes, hipMemcpyDeviceToDevice, s->stream));
     for (int64_t j = 0; j < nck; ++j) {
-        ACE_HIP(hipMemcpyAsync(s->ckpt + j * total, s->buf[s->cur], bytes, hipMemcpyDeviceToDevice,
-                               s->stream));
-        const int64_t n = std::min<int64_t>(every, nsteps - j * every);
-        ACE_TRY(advance(s, n));
+        int64_t left = std::min<int64_t>(every, nsteps - j * every);
+        if (k == ACE_KERNEL_RESIDENT) {  // in place
+            ACE_TRY(advance(s, left));
+            if (j + 1 < nck)
+                ACE_HIP(hipMemcpyAsync(s->ckpt + (j + 1) * total, s->buf[s->cur], bytes, hipMemcpyDeviceToDevice,
+                                       s->stream));
+            continue;
+        }
+        // a segment's last launch writes the next checkpoint, which the next
+        // segment's first launch reads
+        while (left > 0) {
+            double *out = s->buf[s->cur ^ 1];
+            const int64_t t = steps_of_launch(s, k, left);
+            if (t == left && j + 1 < nck) out = s->ckpt + (j + 1) * total;
+            const int taken = launch_between(s, k, in, out, left, nullptr, nullptr);
+            if (taken < 0) return taken;
+            if (taken != t) return ACE_E_STATE;
+            s->steps += taken;
+            left -= taken;
+            if (out == s->buf[s->cur ^ 1]) s->cur ^= 1;
+            in = out;
+        }
     }
     s->field_version++;
     s->ck_every = every;
@@ -1581,85 +1772,19 @@ int ace_backward(ace_solver *s, const double *lambdaT, double *dphi0, double *de
     const int64_t total = s->p.total, every = s->ck_every, nsteps = s->ck_steps;
     const size_t bytes = (size_t)total * sizeof(double);
     if (s->seg_cap < 2 * (every + 1) * total || s->lam_cap < 2 * total) return ACE_E_STATE;
-    const int64_t npart = adjoint_partials_needed(s->shape);
     double *lam[2] = {s->lam, s->lam + total};
     int lc = 0;
-    // The reverse sweep of segment j (on the handle's stream) and the
-    // recompute of segment j-1 (on a second stream) are independent, so they
-    // run concurrently on alternating segment buffers; events order each
-    // buffer's recompute after the previous sweep that used it, and each sweep
-    // after its recompute.
-    if (!s->aux) ACE_HIP(hipStreamCreateWithFlags(&s->aux, hipStreamNonBlocking));
-    if (!s->ev_start) {
-        ACE_HIP(hipEventCreateWithFlags(&s->ev_start, hipEventDisableTiming));
-        for (int b = 0; b < 2; ++b) {
-            ACE_HIP(hipEventCreateWithFlags(&s->ev_rec[b], hipEventDisableTiming));
-            ACE_HIP(hipEventCreateWithFlags(&s->ev_rev[b], hipEventDisableTiming));
-        }
-    }
+    int k = effective_kernel(s);
+    if (k == ACE_KERNEL_RESIDENT) k = ACE_KERNEL_DIRECT;
     ACE_HIP(hipMemcpyAsync(lam[0], lambdaT, bytes,
                            where == ACE_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice,
                            s->stream));
-    ACE_HIP(hipMemsetAsync(s->gsum, 0, sizeof(double), s->stream));
-    ACE_HIP(hipEventRecord(s->ev_start, s->stream));  // checkpoints are complete
-    ACE_HIP(hipStreamWaitEvent(s->aux, s->ev_start, 0));
-    int k = effective_kernel(s);
-    if (k == ACE_KERNEL_RESIDENT) k = ACE_KERNEL_DIRECT;
-    const bool blocked2d = (k == ACE_KERNEL_TBLOCK && s->p.d == 2);
-    if (k == ACE_KERNEL_TBLOCK && !blocked2d) k = one_step_kernel(s->shape);
-    for (int64_t j = s->ck_count - 1; j >= 0; --j) {
-        const int b = (int)(j & 1);
-        double *seg = s->seg + b * (every + 1) * total;
-        const int64_t a = j * every;
-        const int64_t n = std::min<int64_t>(every, nsteps - a);
-        // --- recompute segment j on the second stream ---
-        ACE_HIP(hipStreamWaitEvent(s->aux, s->ev_rev[b], 0));
-        ACE_HIP(hipMemcpyAsync(seg, s->ckpt + j * total, bytes, hipMemcpyDeviceToDevice, s->aux));
-        if (blocked2d) {
-            const int per = steps_per_launch_of(s, ACE_KERNEL_TBLOCK);
-            for (int64_t i = 0; i < n;) {  // each launch writes its K intermediate states
-                const int K = (int)std::min<int64_t>(per, n - i);
-                ACE_HIP(launch_blocked2d(s, seg + i * total, seg + (i + 1) * total, nullptr, nullptr, K, total,
-                                         s->aux));
-                i += K;
-            }
-        } else {
-            for (int64_t i = 0; i < n; ++i) {
-                const double *in = seg + i * total;
-                double *out = seg + (i + 1) * total;
-                hipError_t e = (k == ACE_KERNEL_MARCH)
-                                   ? launch_step_march(s->shape, s->coef, in, out, nullptr, nullptr, s->aux)
-                                   : launch_step_direct(s->shape, s->coef, in, out, nullptr, nullptr, s->aux);
-                ACE_HIP(e);
-            }
-        }
-        ACE_HIP(hipEventRecord(s->ev_rec[b], s->aux));
-        // --- reverse sweep of segment j on the handle's stream ---
-        ACE_HIP(hipStreamWaitEvent(s->stream, s->ev_rec[b], 0));
-        int64_t parts = 0;  // partial sums of dL/dkappa written for this segment
-        if (blocked2d) {
-            // (deeper launches leave the 32-row regions of the reverse sweep small tiles)
-            const int rev = std::min(s->depth2, 8);
-            const int64_t nb = tblock2d_blocks(s->shape, rev);
-            for (int64_t i = n; i > 0;) {  // K transposed steps per launch
-                const int K = (int)std::min<int64_t>(rev, i);
-                ACE_HIP(launch_adjoint_tblock2d(s->shape, s->coef, lam[lc], seg + (i - K) * total, total,
-                                                lam[lc ^ 1], s->gpart + parts, K, s->stream));
-                parts += (K == rev) ? nb : tblock2d_blocks(s->shape, K);
-                lc ^= 1;
-                i -= K;
-            }
-        } else {
-            for (int64_t i = n - 1; i >= 0; --i) {
-                ACE_HIP(launch_adjoint_step(s->shape, s->coef, lam[lc], seg + i * total,
-                                            seg + (i + 1) * total, lam[lc ^ 1], s->gpart + parts,
-                                            nullptr, s->stream));
-                parts += npart;
-                lc ^= 1;
-            }
-        }
-        if (parts > 0) ACE_HIP(launch_sum(s->gpart, parts, s->gsum, 1, s->stream));
-        ACE_HIP(hipEventRecord(s->ev_rev[b], s->stream));
+    if (nsteps == 0) {
+        ACE_HIP(hipMemsetAsync(s->gsum, 0, sizeof(double), s->stream));
+    } else if (k == ACE_KERNEL_TBLOCK && use_tb2(s)) {
+        ACE_TRY(backward_regions(s, lam, &lc));
+    } else {
+        ACE_TRY(backward_steps(s, k, lam, &lc));
     }
     ACE_HIP(hipMemcpyAsync(dphi0, lam[lc], bytes,
                            where == ACE_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice,

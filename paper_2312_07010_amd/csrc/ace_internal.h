@@ -190,6 +190,32 @@ hipError_t launch_step_tb1(const Shape &s, const StepCoef &c, const double *in, 
 hipError_t launch_resident1(const Shape &s, const StepCoef &c, double *field, int64_t nsteps, int64_t every,
                             double *mon, int R, int K, hipStream_t st);
 
+// One launch of the 2D reverse sweep (ace_adj2.hip): n_rev workgroups (0 or
+// adj2_tiles()) take Sr transposed steps from mu_in = mu^{m+Sr} (or
+// lambda^{m+Sr}, if phi_end = phi^{m+Sr} is given) to mu_out = mu^m (lambda^m if
+// `last`), with phi^m at phi_first and phi^{m+i}, i >= 1, at phi_rest + (i - 1)
+// stride, and add their sums of dL/dkappa to gpart (n_rev doubles; set them if
+// not `accumulate`); the rest take Sf forward steps from f_in, level k going
+// to f_out + (k - 1) stride.  K: the ring of the regions of `rows` x 64 nodes
+// (32 or 64), Sr, Sf <= K <= rows / 2 - 4.
+struct Adj2Args {
+    const double *mu_in, *phi_first, *phi_rest, *phi_end;
+    double *mu_out, *gpart;
+    const double *f_in;
+    double *f_out;
+    int64_t stride;
+    int K, Sr, Sf, n_rev, last, accumulate;
+};
+int64_t adj2_tiles(const Shape &s, int rows, int K);
+hipError_t launch_adj2(int rows, const Shape &s, const StepCoef &c, const Adj2Args &a, hipStream_t st);
+
+// 3D: one transposed step in the same form (planes of fewer than 2^28 nodes);
+// gpart: adjoint_col_blocks() sums.
+int64_t adjoint_col_blocks(const Shape &s);
+hipError_t launch_adjoint_col(const Shape &s, const StepCoef &c, const double *mu_in, const double *phi,
+                              const double *phi_end, double *mu_out, double *gpart, int last, int accumulate,
+                              hipStream_t st);
+
 // K transposed steps: states[i * stride] = phi^{m+i}, i = 0..K; lam_in =
 // lambda^{m+K}; writes lambda^m and one partial of dL/dkappa per block.
 hipError_t launch_adjoint_tblock2d(const Shape &s, const StepCoef &c, const double *lam_in,
