@@ -384,7 +384,9 @@ struct ace_solver {
     int64_t partials_cap = 0;
     double *mon = nullptr;  // device monitor triples
     int64_t mon_cap = 0;
-    double *pinned = nullptr;  // host pinned scratch (3 doubles)
+    double *monparts = nullptr;  // partials of several monitors of a monitored run
+    int64_t monparts_cap = 0;
+    double *pinned = nullptr;  // host pinned scratch (64 doubles, kernels may write it)
     int64_t steps = 0;
     int warn_mask = 0;  // warnings of the last monitored run (ACE_WARN_BIT)
     int kernel = ACE_KERNEL_AUTO;
@@ -543,14 +545,6 @@ Shape1 resident1_shape(const Shape &s)
     });
 }
 
-// Whether run_monitored of a 1D field at this interval is better in one
-// workgroup (a monitor costs it about 1.2 us, the launches of their own 5).
-bool monitor_resident1(const ace_solver *s, int64_t every)
-{
-    if (s->p.total > RESIDENT_MAX || s->res1.ns >= 1e300) return false;
-    return 1200.0 + (double)every * s->res1.ns < 5000.0 + (double)every * s->tb1.ns;
-}
-
 bool tblock_applies(const ace_solver *s)
 {
     if (s->p.d == 1) return tb1_supported(s->shape);
@@ -578,6 +572,23 @@ int steps_per_launch_of(const ace_solver *s, int kernel)
     if (s->p.d == 1) return s->tb1.K;
     if (s->p.d == 3) return (s->tb3 >= 0 && tb3_supported(s->shape)) ? TB3_TABLE[s->tb3].depth : 2;
     return use_tb2(s) ? std::min(s->depth2, tb2_max_depth(s->tb2)) : s->depth2;
+}
+
+// Whether run_monitored at this interval is better with the whole field in one
+// workgroup.  1D: a monitor costs it about 1.2 us, the launches of their own
+// 3.  2D: a step takes 0.18 us and 0.235 ns per node (0.52 us at 40 x 40, 1.03
+// at 64 x 64, 1.69 at 80 x 80), a monitor 1.5 us.
+bool monitor_resident(const ace_solver *s, int64_t every)
+{
+    const double n = (double)s->p.total, steps = (double)every;
+    if (n > RESIDENT_MAX) return false;
+    if (s->p.d == 1) return s->res1.ns < 1e300 && 1200.0 + steps * s->res1.ns < 3000.0 + steps * s->tb1.ns;
+    if (s->p.d != 2 || !use_tb2(s)) return false;
+    const int K = std::min(s->depth2, tb2_max_depth(s->tb2)), rest = (int)(every % K);
+    const BlockModel &m = TB2_MODEL[s->tb2];
+    const double blocked = (double)(every / K) * m.us(tb2_blocks(s->tb2, s->shape, K), K) +
+                           (rest ? m.us(tb2_blocks(s->tb2, s->shape, rest), rest) : 0.0);
+    return 1.5 + steps * (0.18 + 2.35e-4 * n) < blocked;
 }
 
 // One launch of the handle's 2D blocked kernel (K steps; level_stride > 0:
@@ -866,9 +877,22 @@ int alloc_fields(ace_solver *s)
     return ACE_OK;
 }
 
-int read_triple(ace_solver *s, const double *dev, double *host3)
+// Monitor triple of the current field into out[0..2] (device or
+// pinned host memory; stream-ordered).
+int monitor_now(ace_solver *s, double *out)
 {
-    ACE_HIP(hipMemcpyAsync(s->pinned, dev, 3 * sizeof(double), hipMemcpyDeviceToHost, s->stream));
+    int64_t np = 0;
+    if (3 * monitor_partials_needed(s->shape) > s->partials_cap) return ACE_E_STATE;
+    ACE_HIP(launch_monitor(s->shape, s->buf[s->cur], s->partials, &np, s->stream));
+    ACE_HIP(launch_reduce(s->partials, np, out, s->stream));
+    return ACE_OK;
+}
+
+// Monitor triple of the current field on the host: the reduction writes the
+// handle's pinned memory.
+int read_monitor(ace_solver *s, double *host3)
+{
+    ACE_TRY(monitor_now(s, s->pinned));
     ACE_HIP(hipStreamSynchronize(s->stream));
     memcpy(host3, s->pinned, 3 * sizeof(double));
     return ACE_OK;
@@ -1022,16 +1046,6 @@ int backward_steps(ace_solver *s, int k, double *const lam[2], int *lc)
     return ACE_OK;
 }
 
-// Monitor triple of the current field into dev_out[0..2] (stream-ordered).
-int monitor_now(ace_solver *s, double *dev_out)
-{
-    int64_t np = 0;
-    if (3 * monitor_partials_needed(s->shape) > s->partials_cap) return ACE_E_STATE;
-    ACE_HIP(launch_monitor(s->shape, s->buf[s->cur], s->partials, &np, s->stream));
-    ACE_HIP(launch_reduce(s->partials, np, dev_out, s->stream));
-    return ACE_OK;
-}
-
 // Autotuner cache: one JSON object per line and tuned problem shape,
 //   {"d": 2, "bc": 0, "M": [1024, 1024, 1], "kernel": 4, "zchunk": 32,
 //    "depth2": 5, "tb3": -1, "tb2": 0, "ms_per_step": 0.003389}
@@ -1141,7 +1155,7 @@ int ace_destroy(ace_solver *s)
         if (e) (void)hipEventDestroy(e);
     for (int i = 0; i < 2; ++i)
         if (s->own[i]) (void)hipFree(s->own[i]);
-    double *devs[] = {s->partials, s->mon, s->ckpt, s->seg, s->lam, s->gpart, s->gsum};
+    double *devs[] = {s->partials, s->mon, s->monparts, s->ckpt, s->seg, s->lam, s->gpart, s->gsum};
     for (double *p : devs)
         if (p) (void)hipFree(p);
     if (s->pinned) (void)hipHostFree(s->pinned);
@@ -1394,22 +1408,48 @@ int ace_run_monitored(ace_solver *s, int64_t nsteps, int64_t every, double *E, d
     const int64_t nmon = nsteps / every + 1;
     ACE_TRY(grow(&s->mon, &s->mon_cap, 3 * nmon));
     int k = effective_kernel(s);
-    if (s->p.d == 1 && s->kernel == ACE_KERNEL_AUTO && s->tuned_kernel == ACE_KERNEL_AUTO && monitor_resident1(s, every))
+    if (s->kernel == ACE_KERNEL_AUTO && s->tuned_kernel == ACE_KERNEL_AUTO && monitor_resident(s, every))
         k = ACE_KERNEL_RESIDENT;
     if (k == ACE_KERNEL_RESIDENT) {
         ACE_HIP(run_resident(s, nsteps, every));
         s->steps += nsteps;
     } else {
-        int64_t j = 0;
+        // The partials of up to `batch` monitors are kept and reduced together
+        // (one launch instead of one per monitor, as long as they take less
+        // than 32 MB), all of a run's equal intervals alike.  np0: the most
+        // partials of an interval's launch; a persistent grid writes fewer.
+        const int64_t np0 = partials_for(s, k, std::min<int64_t>(every, std::max<int64_t>(nsteps, 1)));
+        const int64_t batch = std::max<int64_t>(1, std::min<int64_t>(nmon, ((int64_t)1 << 22) / (3 * np0)));
+        ACE_TRY(grow(&s->monparts, &s->monparts_cap, batch * 3 * np0));
+        int64_t j = 0, kept = 0, npk = 0;  // monitors done, of them not reduced yet, and their partials
+        auto flush = [&]() -> int {
+            if (kept > 0)
+                ACE_HIP(launch_reduce_many(s->monparts, npk, 3 * np0, kept, s->mon + 3 * (j - kept), s->stream));
+            kept = 0;
+            return ACE_OK;
+        };
         for (int64_t st = 0; st <= nsteps; st += every) {
             if (st == nsteps) {
+                ACE_TRY(flush());
                 ACE_TRY(monitor_now(s, s->mon + 3 * j));
             } else {
                 const int64_t seg = std::min<int64_t>(every, nsteps - st);
+                const int64_t want = partials_for(s, k, seg);
+                if (want != np0 || kept == batch) ACE_TRY(flush());
                 int64_t np = 0;
-                int64_t done = launch_steps(s, k, seg, true, &np);
+                double *parts = want == np0 ? s->monparts + 3 * np0 * kept : s->partials;
+                if (want != np0 && 3 * want > s->partials_cap) return ACE_E_STATE;
+                int64_t done = launch_between(s, k, s->buf[s->cur], s->buf[s->cur ^ 1], seg, parts, &np);
                 if (done < 0) return (int)done;
-                ACE_HIP(launch_reduce(s->partials, np, s->mon + 3 * j, s->stream));
+                s->cur ^= 1;
+                s->steps += done;
+                if (kept > 0 && np != npk) ACE_TRY(flush());  // (their slots are read before this one's is reused)
+                if (parts == s->monparts + 3 * np0 * kept) {
+                    ++kept;
+                    npk = np;
+                } else {
+                    ACE_HIP(launch_reduce(parts, np, s->mon + 3 * j, s->stream));
+                }
                 while (done < seg) {
                     const int t = launch_steps(s, k, seg - done, false, nullptr);
                     if (t < 0) return t;
@@ -1417,7 +1457,9 @@ int ace_run_monitored(ace_solver *s, int64_t nsteps, int64_t every, double *E, d
                 }
             }
             ++j;
+            if (st == nsteps) break;
         }
+        if (kept > 0) ACE_TRY(flush());
     }
     s->field_version++;
     std::vector<double> trip((size_t)(3 * nmon));
@@ -1459,10 +1501,8 @@ int ace_monitor_status(int64_t n, const double *E, const double *maxn, int condi
 int ace_energy(ace_solver *s, double *E)
 {
     if (!s || !E) return ACE_E_ARG;
-    ACE_TRY(grow(&s->mon, &s->mon_cap, 3));
-    ACE_TRY(monitor_now(s, s->mon));
     double t[3];
-    ACE_TRY(read_triple(s, s->mon, t));
+    ACE_TRY(read_monitor(s, t));
     *E = energy_from(s->p, t);
     return isfinite(*E) ? ACE_OK : ACE_E_NONFINITE;
 }
@@ -1470,10 +1510,8 @@ int ace_energy(ace_solver *s, double *E)
 int ace_maxnorm(ace_solver *s, double *m)
 {
     if (!s || !m) return ACE_E_ARG;
-    ACE_TRY(grow(&s->mon, &s->mon_cap, 3));
-    ACE_TRY(monitor_now(s, s->mon));
     double t[3];
-    ACE_TRY(read_triple(s, s->mon, t));
+    ACE_TRY(read_monitor(s, t));
     *m = t[2];
     return isfinite(*m) ? ACE_OK : ACE_E_NONFINITE;
 }
@@ -1482,11 +1520,9 @@ int ace_phase_volume(ace_solver *s, double *V)
 {
     if (!s || !V) return ACE_E_ARG;
     ACE_TRY(grow(&s->partials, &s->partials_cap, phase_partials_needed()));
-    ACE_TRY(grow(&s->mon, &s->mon_cap, 3));
-    ACE_HIP(launch_phase_volume(s->buf[s->cur], s->p.total, s->partials, s->mon, s->stream));
-    double t[3];
-    ACE_TRY(read_triple(s, s->mon, t));
-    *V = pow(s->p.dx, s->p.d) * t[0];
+    ACE_HIP(launch_phase_volume(s->buf[s->cur], s->p.total, s->partials, s->pinned, s->stream));
+    ACE_HIP(hipStreamSynchronize(s->stream));
+    *V = pow(s->p.dx, s->p.d) * s->pinned[0];
     return isfinite(*V) ? ACE_OK : ACE_E_NONFINITE;
 }
 

@@ -105,6 +105,9 @@ hipError_t launch_monitor_finish(const double *trip, double dxd, double cg, doub
 // Fixed-order reduction of nparts triples to one triple at out[0..2].
 hipError_t launch_reduce(const double *partials, int64_t nparts, double *out,
                          hipStream_t st);
+// The same for `count` sets of nparts triples `stride` doubles apart.
+hipError_t launch_reduce_many(const double *partials, int64_t nparts, int64_t stride, int64_t count, double *out,
+                              hipStream_t st);
 
 // Whole field in LDS: nsteps steps in one launch (total <= RESIDENT_MAX).
 // When every > 0 the monitor triple of steps 0, every, ... <= nsteps is
@@ -233,11 +236,10 @@ hipError_t launch_adjoint_step(const Shape &s, const StepCoef &c, const double *
                                double *lam_out, double *gpart, int64_t *nparts,
                                hipStream_t st);
 int64_t adjoint_partials_needed(const Shape &s);
-// out[0] = sum_i (1 + f_i)/2 over n values (fixed order, two passes through
-// part, which holds phase_partials_needed() doubles).
+// out[0] (device or pinned host memory) = sum_i (1 + f_i)/2 over n values, in a
+// fixed order; part holds phase_partials_needed() doubles.
 int64_t phase_partials_needed();
-hipError_t launch_phase_volume(const double *f, int64_t n, double *part, double *out,
-                               hipStream_t st);
+hipError_t launch_phase_volume(const double *f, int64_t n, double *part, double *out, hipStream_t st);
 // Fixed-order sum of n doubles into out[0] (+= if accumulate).
 hipError_t launch_sum(const double *x, int64_t n, double *out, int accumulate,
                       hipStream_t st);

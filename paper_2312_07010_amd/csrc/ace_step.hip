@@ -1,6 +1,8 @@
 // Step kernels that need no tiling: one thread per node (any d, any BC),
 // the LDS-resident multi-step kernel for small fields, the standalone
 // monitor pass, and the fixed-order reductions.
+#include <algorithm>
+
 #include "ace_device.h"
 
 namespace ace {
@@ -226,30 +228,33 @@ __global__ __launch_bounds__(kResThreads) void k_resident(Shape s, StepCoef c,
     for (int j = tid; j < total; j += nt) field[j] = fb[cb][j];
 }
 
-__global__ __launch_bounds__(1024) void k_reduce(const double *__restrict__ partials, int64_t n,
+// The triple of `n` partial triples, in a fixed order, by a 1024-thread
+// workgroup; block b reduces the triples at partials + b * stride to out + 3 b.
+__global__ __launch_bounds__(1024) void k_reduce(const double *__restrict__ partials, int64_t n, int64_t stride,
                                                  double *__restrict__ out)
 {
     __shared__ double lds[3 * 16];
+    const double *p = partials + (int64_t)blockIdx.x * stride;
     MonAcc m;
     mon_zero(m);
     for (int64_t j = threadIdx.x; j < n; j += blockDim.x) {
-        m.bulk += partials[3 * j + 0];
-        m.grad += partials[3 * j + 1];
-        m.mx = nan_max(m.mx, partials[3 * j + 2]);
+        m.bulk += p[3 * j + 0];
+        m.grad += p[3 * j + 1];
+        m.mx = nan_max(m.mx, p[3 * j + 2]);
     }
-    block_reduce_store(m, lds, out);
+    block_reduce_store(m, lds, out + 3 * (int64_t)blockIdx.x);
 }
 
-// Per-block partial sums of (1 + phi)/2 (the smooth phase indicator), each
-// block over a contiguous range in a fixed order: every thread keeps
-// kPhaseU running sums over loads kPhaseU * 256 apart (so kPhaseU loads are
-// in flight per thread), added in order at the end.
+// Sums of (1 + phi)/2 (the smooth phase indicator) per block of T threads, each
+// block over a contiguous range in a fixed order: every thread keeps kPhaseU
+// running sums over loads kPhaseU * T apart (so kPhaseU loads are in flight
+// per thread), added in order at the end.
 constexpr int kPhaseBlocks = 4096;
 constexpr int kPhaseU = 8;
-__global__ __launch_bounds__(256) void k_phase_partials(const double *__restrict__ f, int64_t n,
-                                                        double *__restrict__ part)
+template <int T>
+__global__ __launch_bounds__(T) void k_phase(const double *__restrict__ f, int64_t n, double *__restrict__ part)
 {
-    __shared__ double lds[4];
+    __shared__ double lds[T / 64];
     const int64_t per = (n + gridDim.x - 1) / gridDim.x;
     const int64_t lo = (int64_t)blockIdx.x * per;
     const int64_t hi = (lo + per < n) ? lo + per : n;
@@ -257,18 +262,23 @@ __global__ __launch_bounds__(256) void k_phase_partials(const double *__restrict
 #pragma unroll
     for (int u = 0; u < kPhaseU; ++u) acc[u] = 0.0;
     int64_t j = lo + threadIdx.x;
-    for (; j + (kPhaseU - 1) * 256 < hi; j += kPhaseU * 256) {
+    for (; j + (kPhaseU - 1) * T < hi; j += kPhaseU * T) {
 #pragma unroll
-        for (int u = 0; u < kPhaseU; ++u) acc[u] += 0.5 * (1.0 + f[j + u * 256]);
+        for (int u = 0; u < kPhaseU; ++u) acc[u] += 0.5 * (1.0 + f[j + u * T]);
     }
-    for (; j < hi; j += 256) acc[0] += 0.5 * (1.0 + f[j]);
+    for (; j < hi; j += T) acc[0] += 0.5 * (1.0 + f[j]);
     double v = acc[0];
 #pragma unroll
     for (int u = 1; u < kPhaseU; ++u) v += acc[u];
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
     __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = ((lds[0] + lds[1]) + (lds[2] + lds[3]));
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < T / 64; ++w) t += lds[w];
+        part[blockIdx.x] = t;
+    }
 }
 
 __global__ __launch_bounds__(1024) void k_sum(const double *__restrict__ x, int64_t n,
@@ -499,7 +509,13 @@ hipError_t launch_monitor(const Shape &s, const double *in, double *partials, in
 
 hipError_t launch_reduce(const double *partials, int64_t nparts, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_reduce, dim3(1), dim3(1024), 0, st, partials, nparts, out);
+    return launch_reduce_many(partials, nparts, 0, 1, out, st);
+}
+
+hipError_t launch_reduce_many(const double *partials, int64_t nparts, int64_t stride, int64_t count, double *out,
+                              hipStream_t st)
+{
+    hipLaunchKernelGGL(k_reduce, dim3((unsigned)count), dim3(1024), 0, st, partials, nparts, stride, out);
     return hipGetLastError();
 }
 
@@ -523,13 +539,22 @@ hipError_t launch_monitor_finish(const double *trip, double dxd, double cg, doub
 
 int64_t phase_partials_needed() { return kPhaseBlocks; }
 
+// Up to 32768 nodes one 1024-thread workgroup sums the field in a single
+// launch (4 loads in a row of kPhaseU per thread); past that 256-thread ones
+// of at least kPhaseU loads a thread, at most kPhaseBlocks, and their sum.
+// (A counter by which the last workgroup adds the partials in the same launch
+// needs a device-wide fence per workgroup: 130^3 took 80 us more that way.)
 hipError_t launch_phase_volume(const double *f, int64_t n, double *part, double *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_phase_partials, dim3(kPhaseBlocks), dim3(256), 0, st, f, n, part);
+    if (n <= 32768) {
+        hipLaunchKernelGGL(k_phase<1024>, dim3(1), dim3(1024), 0, st, f, n, out);
+        return hipGetLastError();
+    }
+    const int64_t blocks = std::min<int64_t>(kPhaseBlocks, (n + 256 * kPhaseU - 1) / (256 * kPhaseU));
+    hipLaunchKernelGGL(k_phase<256>, dim3((unsigned)blocks), dim3(256), 0, st, f, n, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sum, dim3(1), dim3(1024), 0, st, part, (int64_t)kPhaseBlocks, out, 0);
-    return hipGetLastError();
+    return launch_sum(part, blocks, out, 0, st);
 }
 
 hipError_t launch_sum(const double *x, int64_t n, double *out, int accumulate, hipStream_t st)

@@ -1,0 +1,72 @@
+"""Monitored runs whose monitors are reduced together, at intervals that divide
+the steps or leave a shorter last one, from one monitor to more than fit one
+reduction, on every way of running (1D segments and one workgroup, 2D and 3D
+regions, persistent grids, one-step kernels): each value against the standalone
+energy and max-norm of the same state; and the phase volume from one block to
+its most."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _args(M, bc, dt=1e-3):
+    d = len(M)
+    N = [m + (-2, 1, 0)[bc] for m in M]
+    dx = 1.0 / N[-1]
+    return d, N, [0.0] * d, [n * dx for n in N], math.sqrt(0.1 / dt) * dx, dt, bc
+
+
+@pytest.mark.parametrize("steps,every", [(0, 3), (5, 7), (20, 4), (23, 4), (24, 1), (45, 12)])
+@pytest.mark.parametrize("M,planes", [((700,), None), ((30000,), None), ((60, 61), None), ((85, 85), None), ((300, 170), None),
+                                      ((20, 19, 20), None), ((40, 70, 66), None), ((40, 70, 66), 0), ((150, 130, 140), None)])
+def test_monitors(M, planes, steps, every):
+    from paper_2312_07010_amd import ace
+    s, r = ace.Solver(*_args(M, 1)), ace.Solver(*_args(M, 1))
+    if planes is not None:
+        s.set_kernel(ace.ACE_KERNEL_TBLOCK)
+        s.set_plane_chunk(planes)
+    phi = np.random.default_rng(steps).uniform(-1, 1, s.shape)
+    s.set_phi0(phi)
+    r.set_phi0(phi)
+    E, mx = s.run_monitored(steps, every)
+    assert len(E) == steps // every + 1
+    for j in range(len(E)):
+        assert E[j] == pytest.approx(r.energy(), rel=1e-13)
+        assert mx[j] == r.maxnorm()
+        r.step(min(every, steps - j * every))
+    assert np.array_equal(s.get_phi(), r.get_phi())
+    s.close()
+    r.close()
+
+
+def test_many_monitors():
+    """More monitors than one reduction holds (32 MB of partials)."""
+    from paper_2312_07010_amd import ace
+    s, r = ace.Solver(*_args((400, 500), 2)), ace.Solver(*_args((400, 500), 2))
+    phi = np.random.default_rng(1).uniform(-1, 1, s.shape)
+    for x in (s, r):
+        x.set_kernel(ace.ACE_KERNEL_DIRECT)  # 1000 workgroups, 3000 doubles a monitor
+        x.set_phi0(phi)
+    E, mx = s.run_monitored(1500, 1)
+    for j in (0, 1, 1396, 1397, 1398, 1399, 1499, 1500):
+        r.set_phi0(phi)
+        r.step(j)
+        assert E[j] == pytest.approx(r.energy(), rel=1e-13)
+        assert mx[j] == r.maxnorm()
+    s.close()
+    r.close()
+
+
+@pytest.mark.parametrize("M", [(3,), (2047,), (2049,), (300, 300), (130, 130, 130), (210, 210, 210)])
+def test_phase_volume_blocks(M):
+    from paper_2312_07010_amd import ace
+    s = ace.Solver(*_args(M, 2))
+    phi = np.random.default_rng(7).uniform(-1, 1, s.shape)
+    s.set_phi0(phi)
+    want = s.params["dx"] ** len(M) * math.fsum((0.5 * (1 + phi)).ravel())
+    for _ in range(3):  # (the arrival counter is left as it was found)
+        assert s.phase_volume() == pytest.approx(want, rel=1e-13)
+    s.close()
