@@ -1593,13 +1593,15 @@ int ace_autotune(ace_solver *s, int64_t trial_steps, char *json, size_t cap)
             if (zc <= std::max<int64_t>(s->shape.M0, 16)) cands.push_back({ACE_KERNEL_TBLOCK, zc, k0, -1, v20});
     // the configurable 3D kernel: every depth and region shape, as a
     // persistent grid and at the three plane chunks with the least modelled
-    // time.  The deep 48-row region is timed where it has workgroups for half
-    // of the CUs (on smaller fields it never came near the others).
+    // time (the least one where the field is so small that a launch is one
+    // round of workgroups at any of them).  The deep 48-row region is timed
+    // where it has workgroups for half of the CUs (on smaller fields it never
+    // came near the others).
     if (s->p.d == 3 && tb3_supported(s->shape))
         for (int v = 0; v < TB3_VARIANTS; ++v) {
             if (v >= TB3_NAMED && tb3_partials_needed(v, s->shape, 16) < 128) continue;
             std::vector<int> zcs = tb3_chunks(v, s->shape, s->coef.fex);
-            zcs.resize(std::min<size_t>(zcs.size(), 3));
+            zcs.resize(std::min<size_t>(zcs.size(), s->p.total < 100000 ? 1 : 3));
             zcs.push_back(0);
             for (int zc : zcs) cands.push_back({ACE_KERNEL_TBLOCK, zc, k0, v, v20});
         }
