@@ -96,21 +96,16 @@ def cpu_baseline(w, phi0_full, min_seconds=10.0):
 
 
 # Depth of the 2D blocked kernel for the adjoint workload.  On 512^2 with
-# 32-step checkpoint segments, depths 1..12 give forward / backward (ms):
-# 1: 5.41 / 8.67, 2: 3.12 / 5.54, 3: 2.46 / 4.14, 4: 2.02 / 3.44,
-# 5: 1.79 / 3.17, 6: 2.09 / 3.36, 8: 1.74 / 3.10, 10: 2.02 / 4.05,
-# 12: 2.08 / 4.63.  Depth 8 is the fastest for both halves: its 16 x 48 tiles
-# make 352 workgroups (240 at depth 5, fewer than the 256 CUs) and it divides
-# the segments evenly.  The forward-step autotuner cannot see the reverse
-# sweep and picks 5 or 8 (1.79 vs 1.73 ms).
+# 32-step checkpoint segments, depths 1..12 give forward (ms) 3.45, 2.00, 1.54,
+# 1.23, 1.15, 1.28, 1.10 (8), 1.25 (10), 1.30 (12).  The reverse sweep chooses
+# its own depth from the segment length (1.94 to 2.06 ms whatever this is).
 ADJOINT_DEPTH = 8
 
 
 def adjoint_ratio(ace, torch):
     """Backward / forward wall time: 2D Neumann 512^2, 1000 steps, checkpoints
     every 32 (forward = ace_forward_ckpt, backward = ace_backward), with the 2D
-    blocked kernel at ADJOINT_DEPTH steps per launch in the forward, the
-    recompute and the reverse sweep."""
+    blocked kernel at ADJOINT_DEPTH steps per launch in the forward."""
     from paper_2312_07010_amd import inputs
     w = inputs.WADJ
     s = ace.Solver(w.d, w.N, w.L, w.R, w.eps, w.dt, w.bc)
@@ -118,7 +113,7 @@ def adjoint_ratio(ace, torch):
     s.set_kernel(ace.ACE_KERNEL_TBLOCK, ADJOINT_DEPTH)
     phi0 = torch.tensor(inputs.uniform_field(s.shape, w.lo, w.hi, w.seed), device="cuda")
     k, per = s.get_kernel()
-    kernel = f"{kernel_name(ace, w.d, k)} ({per} step(s) per launch)"
+    kernel = f"{kernel_name(ace, w.d, k, s.get_region2d())} ({per} step(s) per launch)"
     tgt = torch.tensor(inputs.uniform_field(s.shape, w.lo, w.hi, w.extra["target_seed"]),
                        device="cuda")
     s.forward_ckpt(phi0, w.steps, w.extra["ckpt_every"])  # warm-up, same sizes
@@ -194,8 +189,8 @@ def slab_share(ace, torch, w, full, interior=64, halo=3, iters=200):
 
 def batched_speedup(ace, torch):
     """The 4096-instance workload (half 1D, half 2D, mixed eps and BCs), 500
-    steps: one persistent launch (after the batch autotuner picks its LDS
-    limit) vs the same library's ace_step(500) called per instance in a loop
+    steps: one call (after the batch autotuner picks its region shape, depth
+    and LDS limit) vs the same library's ace_step(500) called per instance in a loop
     on one stream (step calls only in both timed regions)."""
     from paper_2312_07010_amd import inputs
     descs = inputs.batch_instances()
@@ -241,7 +236,7 @@ def batched_speedup(ace, torch):
 
 
 def batch_launch(ace, torch, steps=500, depth=4, resident_limit=8000, region=0):
-    """The batched workload's persistent launches alone, at a fixed choice
+    """The batched workload's launches alone, at a fixed choice
     (region depth, LDS limit, region height: 0 for LDS-plane regions, 32 or
     64 for register-resident ones in a kernel of their own), issued directly
     (no graph) so that counter tools see them: one untimed and one timed
@@ -385,13 +380,14 @@ def timed_pop(ace, torch, w, steps=40, warmup=3):
     wall = time.perf_counter() - t0
     gpu_s = e0.elapsed_time(e1) / 1e3
     q, n = g.q, float(g.total)
-    # the carried form (the default for d >= 2) reads phi and writes the q
-    # populations and phi: 8 q + 16 bytes per node update; reading and
-    # writing all q populations (the fused form) would be 16 q
-    per = 8.0 * q + 16.0
+    # the carried form (the default for d >= 2) reads and writes phi, 16 bytes
+    # per node update, and the call's last step also writes the q populations,
+    # 8 q more; reading and writing all q populations (the fused form) would
+    # be 16 q
+    per = 16.0 + 8.0 * q / steps
     out = {"value": n * steps / wall, "unit": "grid-pt updates/s", "steps": steps,
            "ms_per_step": wall * 1e3 / steps, "avg_launch_us": gpu_s / steps * 1e6,
-           "kernel": "k_pop_update, carried phi (1 step per launch)",
+           "kernel": "k_pop_update, carried phi (1 step per launch, populations at the last)",
            "populations": q, "bytes_per_update": per,
            "roofline_frac": per * n * steps / gpu_s / HBM_PEAK,
            "frac_at_16q_bytes": 16.0 * q * n * steps / gpu_s / HBM_PEAK,
@@ -436,7 +432,7 @@ def main():
     ap.add_argument("--only", choices=["adjoint", "batched", "batch-launch"], default=None,
                     help="run only the adjoint-ratio or the batched measurement (for profiling) "
                          "and print its result; batch-launch: only the batched workload's "
-                         "persistent launch, issued without graph replay (for counter collection)")
+                         "launches, issued without graph replay (for counter collection)")
     args = ap.parse_args()
     if args.gpus != 1:
         print(json.dumps({"error": "this build runs on one GPU; --gpus must be 1"}))
