@@ -167,7 +167,9 @@ int ace_set_kernel(ace_solver *s, int kernel, int depth);
  * nodes held in registers, rows_per_thread consecutive rows per thread
  * (rows / rows_per_thread wavefronts per workgroup), with a ring of depth
  * nodes recomputed: (2, 32, 4), (3, 48, 3), (3, 48, 4), (3, 32, 2),
- * (4, 32, 4), (4, 32, 2).  ace_autotune chooses among all of them.  Runs
+ * (4, 32, 4), (4, 32, 2).  ace_autotune chooses among all of them.  It and
+ * the default choice also take (4, 48, 3), which ace_get_region3d reports and
+ * the autotuner's file carries but which is not set by name.  Runs
  * shorter than the depth, and planes (M1 * M2) of 2^28 nodes or more, take
  * the two-step or one-step kernel.  Error:
  * ACE_E_ARG when d != 3 or the triple is not instantiated. */

@@ -1420,7 +1420,10 @@ int ace_run_monitored(ace_solver *s, int64_t nsteps, int64_t every, double *E, d
         // partials of an interval's launch; a persistent grid writes fewer.
         const int64_t np0 = partials_for(s, k, std::min<int64_t>(every, std::max<int64_t>(nsteps, 1)));
         const int64_t batch = std::max<int64_t>(1, std::min<int64_t>(nmon, ((int64_t)1 << 22) / (3 * np0)));
-        ACE_TRY(grow(&s->monparts, &s->monparts_cap, batch * 3 * np0));
+        // (without that memory each monitor is reduced by itself, as are those
+        // of which only one fits)
+        const bool many = batch > 1 && grow(&s->monparts, &s->monparts_cap, batch * 3 * np0) >= 0;
+        if (batch > 1 && !many) (void)hipGetLastError();
         int64_t j = 0, kept = 0, npk = 0;  // monitors done, of them not reduced yet, and their partials
         auto flush = [&]() -> int {
             if (kept > 0)
@@ -1435,16 +1438,17 @@ int ace_run_monitored(ace_solver *s, int64_t nsteps, int64_t every, double *E, d
             } else {
                 const int64_t seg = std::min<int64_t>(every, nsteps - st);
                 const int64_t want = partials_for(s, k, seg);
-                if (want != np0 || kept == batch) ACE_TRY(flush());
+                const bool keep = many && want == np0;
+                if (!keep || kept == batch) ACE_TRY(flush());
                 int64_t np = 0;
-                double *parts = want == np0 ? s->monparts + 3 * np0 * kept : s->partials;
-                if (want != np0 && 3 * want > s->partials_cap) return ACE_E_STATE;
+                double *parts = keep ? s->monparts + 3 * np0 * kept : s->partials;
+                if (!keep && 3 * want > s->partials_cap) return ACE_E_STATE;
                 int64_t done = launch_between(s, k, s->buf[s->cur], s->buf[s->cur ^ 1], seg, parts, &np);
                 if (done < 0) return (int)done;
                 s->cur ^= 1;
                 s->steps += done;
                 if (kept > 0 && np != npk) ACE_TRY(flush());  // (their slots are read before this one's is reused)
-                if (parts == s->monparts + 3 * np0 * kept) {
+                if (keep && parts == s->monparts + 3 * np0 * kept) {
                     ++kept;
                     npk = np;
                 } else {
