@@ -12,6 +12,13 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+
+
 def _args(M, bc, dt=1e-3):
     d = len(M)
     N = [m + (-2, 1, 0)[bc] for m in M]
