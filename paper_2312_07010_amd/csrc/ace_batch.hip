@@ -6,7 +6,9 @@
 //     alternating between the two arenas.  (One workgroup per whole instance
 //     left the largest one's time as the launch's: 66 ms for the 1024
 //     instances whose rounds take 22.)
-//   * 1D instances likewise, one wavefront per segment (ace_tb1.h).
+//   * 1D instances likewise, one wavefront per segment (ace_tb1.h); those whose
+//     indices a segment's 32 bits do not hold (tb1_supported, from about 2^30
+//     nodes) by the one-step kernel, a launch per step.
 //   * with LDS-plane regions chosen, 2D instances: one workgroup each for all
 //     steps, a small field in LDS, others over 32 x 64 LDS regions.
 // Every instance carries its own shape, boundary condition, kappa, h and root
@@ -33,6 +35,15 @@
 #include "ace_tile2d.h"
 
 namespace ace {
+
+// How a batch steps an instance of this shape at region rows `region`: all
+// its steps by one workgroup, in rounds over 2D regions or 1D segments, or a
+// launch per step.
+int batch_route(const Shape &s, int region)
+{
+    if (s.d == 1) return tb1_supported(s) ? BATCH_SEGMENTS : BATCH_STEPS;
+    return region != 0 && s.M1 * s.M2 <= INT32_MAX ? BATCH_REGIONS : BATCH_SINGLE;  // (regions index with 32 bits)
+}
 
 struct BatchInst {
     int d, bc;
@@ -403,10 +414,11 @@ struct ace_batch {
     // pieces of every launch kind, one device array: regions of the 2D
     // instances at the current depth and region, segments of the 1D ones,
     // chunks of all instances (for the copies and the monitor), and those of
-    // the instances in regions and in segments
+    // the instances in regions, in segments and of `by_step`
     Piece *pieces = nullptr;
     int64_t pieces_cap = 0;
-    int n_regions = 0, n_segments = 0, n_chunks = 0, n_chunks2 = 0, n_chunks1 = 0;
+    int n_regions = 0, n_segments = 0, n_chunks = 0, n_chunks2 = 0, n_chunks1 = 0, n_chunks0 = 0;
+    std::vector<int> by_step;  // 1D instances too large for segments
     int *chunk_first = nullptr;  // count + 1
     int n_single = 0;  // order[]: the 2D instances of k_batch
     double *arena_a = nullptr, *arena_b = nullptr;
@@ -442,17 +454,21 @@ int upload_tasks(ace_batch *b)
     // the tables below are read by any launch still running on the stream
     BT_HIP(hipStreamSynchronize(b->stream));
     drop_graphs(b);
-    std::vector<int> large2, large1, single;
+    std::vector<int> large2, large1, single, by_step;
     for (int i = 0; i < b->count; ++i) {
         BatchInst &I = b->host_inst[i];
         // (in LDS, a small instance takes longer than as its few regions or
         // segments: 200 of 16^2 to 60^2 and of 128 to 4096 nodes x 500 steps
         // 1.97 against 0.97 ms)
         I.resident = I.d == 2 && b->region == 0 && I.total <= b->resident_limit;
-        if (I.d == 1) large1.push_back(i);
-        else if (b->region != 0 && I.total <= INT32_MAX) large2.push_back(i);  // (regions index with 32 bits)
-        else single.push_back(i);
+        switch (batch_route(shape_of(b->prob[i]), b->region)) {
+        case BATCH_SEGMENTS: large1.push_back(i); break;
+        case BATCH_REGIONS: large2.push_back(i); break;
+        case BATCH_STEPS: by_step.push_back(i); break;
+        default: single.push_back(i);
+        }
     }
+    b->by_step = by_step;
     // workgroups that take a whole instance: the costly ones first
     std::stable_sort(single.begin(), single.end(),
                      [&](int x, int y) { return b->host_inst[x].total > b->host_inst[y].total; });
@@ -510,6 +526,7 @@ int upload_tasks(ace_batch *b)
     };
     b->n_chunks2 = chunks_of(large2);
     b->n_chunks1 = chunks_of(large1);
+    b->n_chunks0 = chunks_of(by_step);
     if (p.size() > (size_t)INT32_MAX) return ACE_E_NOMEM;
     if ((int64_t)p.size() > b->pieces_cap) {
         if (b->pieces) (void)hipFree(b->pieces);
@@ -575,6 +592,16 @@ hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
         });
         if (rounds & 1) copy_back(chunk_pieces(b) + b->n_chunks + b->n_chunks2, b->n_chunks1);
     }
+    for (int i : b->by_step) {
+        const BatchInst &I = b->host_inst[i];
+        double *in = b->arena_a + I.off, *out = b->arena_b + I.off;
+        for (int64_t k = 0; k < nsteps; ++k, std::swap(in, out)) {
+            const hipError_t e = launch_step_direct(shape_of(b->prob[i]), I.c, in, out, nullptr, nullptr, st);
+            if (e != hipSuccess) return e;
+        }
+    }
+    if (b->n_chunks0 > 0 && (nsteps & 1))
+        copy_back(chunk_pieces(b) + b->n_chunks + b->n_chunks2 + b->n_chunks1, b->n_chunks0);
     if (b->n_single > 0)
         hipLaunchKernelGGL(k_batch, dim3(b->n_single), dim3(kBT), 0, st, b->inst,
                            b->order_dev, b->arena_a, b->arena_b, nsteps, b->depth);

@@ -193,6 +193,9 @@ hipError_t launch_step_tb1(const Shape &s, const StepCoef &c, const double *in, 
 hipError_t launch_resident1(const Shape &s, const StepCoef &c, double *field, int64_t nsteps, int64_t every,
                             double *mon, int R, int K, hipStream_t st);
 
+enum { BATCH_SINGLE = 0, BATCH_REGIONS = 1, BATCH_SEGMENTS = 2, BATCH_STEPS = 3 };
+int batch_route(const Shape &s, int region);  // ace_batch.hip
+
 // One launch of the 2D reverse sweep (ace_adj2.hip): n_rev workgroups (0 or
 // adj2_tiles()) take Sr transposed steps from mu_in = mu^{m+Sr} (or
 // lambda^{m+Sr}, if phi_end = phi^{m+Sr} is given) to mu_out = mu^m (lambda^m if
