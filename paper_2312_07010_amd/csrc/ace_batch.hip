@@ -42,7 +42,7 @@ namespace ace {
 int batch_route(const Shape &s, int region)
 {
     if (s.d == 1) return tb1_supported(s) ? BATCH_SEGMENTS : BATCH_STEPS;
-    return region != 0 && s.M1 * s.M2 <= INT32_MAX ? BATCH_REGIONS : BATCH_SINGLE;  // (regions index with 32 bits)
+    return region != 0 && tb2_supported(s) ? BATCH_REGIONS : BATCH_SINGLE;
 }
 
 struct BatchInst {

@@ -178,7 +178,7 @@ hipError_t launch_step_tb2(int v, const Shape &s, const StepCoef &c, const doubl
 int64_t tb2_blocks(int v, const Shape &s, int K);
 inline int tb2_max_depth(int v) { return TB2_TABLE[v].rows / 2 - 4; }
 int tb2_find(int rows, int rpt);  // variant index, or -1
-bool tb2_supported(const Shape &s);  // d == 2 with fewer than 2^31 nodes
+bool tb2_supported(const Shape &s);  // d == 2 with fewer than 2^31 nodes, and 2^30 - 1 per axis
 
 // 1D: K steps per launch (1 <= K < 32 R) with one wavefront per 64 R - 2 K
 // output nodes, R nodes per lane (1, 2 or 4); same partials contract as the

@@ -20,7 +20,13 @@ int64_t tb2_blocks_v1(const Shape &, int);
 int64_t tb2_blocks_v2(const Shape &, int);
 int64_t tb2_blocks_v3(const Shape &, int);
 
-bool tb2_supported(const Shape &s) { return tblock2d_supported(s) && s.M1 * s.M2 < ((int64_t)1 << 31); }
+// (node numbers, and per axis the boundary images' period of at most 2 (n + 1),
+// are 32-bit)
+bool tb2_supported(const Shape &s)
+{
+    constexpr int64_t axis = ((int64_t)1 << 30) - 1;
+    return tblock2d_supported(s) && s.M1 < axis && s.M2 < axis && s.M1 * s.M2 < ((int64_t)1 << 31);
+}
 
 int tb2_find(int rows, int rpt)
 {

@@ -38,3 +38,18 @@ def test_batch_1d_route(lib, n, bc):
         assert route in (SEGMENTS, STEPS)
         assert route == STEPS or _image_is_32_bit([n])
         assert route == SEGMENTS or n >= 2 ** 30 - 1  # (what fits stays on the segments)
+
+
+@pytest.mark.parametrize("bc", [HN, HD, P])
+@pytest.mark.parametrize("M", [(1, 2 ** 30 - 2), (1, 2 ** 30 - 1), (2 ** 30 - 2, 1), (2 ** 30 - 1, 1), (2 ** 30, 1), (1, 2 ** 30 + 2),
+                               (2 ** 31 - 1, 1), (3, 2 ** 29), (46341, 46340), (46340, 46341), (46341, 46341), (5, 7)])
+def test_2d_regions(lib, M, bc):
+    s = _shape(M, bc)
+    regions = bool(lib._ZN3ace13tb2_supportedERKNS_5ShapeE(ctypes.byref(s)) & 0xff)
+    small = M[0] * M[1] < 2 ** 31
+    assert not regions or (small and _image_is_32_bit(M))
+    assert regions or not small or not _image_is_32_bit(M)  # (what fits stays on the regions)
+    route = lib._ZN3ace11batch_routeERKNS_5ShapeEi
+    for rows in (32, 64):
+        assert route(ctypes.byref(s), rows) == (REGIONS if regions else SINGLE)
+    assert route(ctypes.byref(s), 0) == SINGLE
