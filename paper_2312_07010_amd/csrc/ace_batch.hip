@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <map>
+#include <new>
 #include <numeric>
 #include <string>
 #include <vector>
@@ -398,7 +399,6 @@ struct ace_batch {
     int count = 0;
     std::vector<Problem> prob;
     std::vector<BatchInst> host_inst;
-    std::vector<int> order;
     std::vector<int64_t> packed;  // offsets of the fields back to back
     int64_t arena_total = 0, packed_total = 0;
     int64_t resident_limit = RESIDENT_MAX;  // tuned: largest field stepped in LDS
@@ -416,11 +416,10 @@ struct ace_batch {
     // chunks of all instances (for the copies and the monitor), and those of
     // the instances in regions, in segments and of `by_step`
     Piece *pieces = nullptr;
-    int64_t pieces_cap = 0;
     int n_regions = 0, n_segments = 0, n_chunks = 0, n_chunks2 = 0, n_chunks1 = 0, n_chunks0 = 0;
     std::vector<int> by_step;  // 1D instances too large for segments
     int *chunk_first = nullptr;  // count + 1
-    int n_single = 0;  // order[]: the 2D instances of k_batch
+    int n_single = 0;  // order_dev[]: the 2D instances of k_batch
     double *arena_a = nullptr, *arena_b = nullptr;
     double *trip = nullptr, *partials = nullptr;
     int use_graphs = 1;  // 0: the launches are issued directly on every step call
@@ -447,39 +446,45 @@ void drop_graphs(ace_batch *b)
     b->graph_defs.clear();
 }
 
-// Sorts the instances into their kinds of work and uploads the tables of the
-// launches (at the current limit, depth and region).
-int upload_tasks(ace_batch *b)
+// What a batch's launches are made from: the choices, the instances of each
+// kind of work and the tables on the device.
+struct Choice {
+    int64_t resident_limit;
+    int depth, depth_fixed, region;
+};
+
+Choice choice_of(const ace_batch *b) { return {b->resident_limit, b->depth, b->depth_fixed, b->region}; }
+
+// Sorts the instances into their kinds of work at choice c, uploads the tables
+// of the launches, and only then takes both over: on an error the batch keeps
+// the choice and the tables it had.
+int upload_tables(ace_batch *b, Choice c)
 {
     // the tables below are read by any launch still running on the stream
     BT_HIP(hipStreamSynchronize(b->stream));
-    drop_graphs(b);
+    std::vector<BatchInst> inst = b->host_inst;
     std::vector<int> large2, large1, single, by_step;
     for (int i = 0; i < b->count; ++i) {
-        BatchInst &I = b->host_inst[i];
+        BatchInst &I = inst[i];
         // (in LDS, a small instance takes longer than as its few regions or
         // segments: 200 of 16^2 to 60^2 and of 128 to 4096 nodes x 500 steps
         // 1.97 against 0.97 ms)
-        I.resident = I.d == 2 && b->region == 0 && I.total <= b->resident_limit;
-        switch (batch_route(shape_of(b->prob[i]), b->region)) {
+        I.resident = I.d == 2 && c.region == 0 && I.total <= c.resident_limit;
+        switch (batch_route(shape_of(b->prob[i]), c.region)) {
         case BATCH_SEGMENTS: large1.push_back(i); break;
         case BATCH_REGIONS: large2.push_back(i); break;
         case BATCH_STEPS: by_step.push_back(i); break;
         default: single.push_back(i);
         }
     }
-    b->by_step = by_step;
     // workgroups that take a whole instance: the costly ones first
-    std::stable_sort(single.begin(), single.end(),
-                     [&](int x, int y) { return b->host_inst[x].total > b->host_inst[y].total; });
-    b->order = single;
-    b->n_single = (int)single.size();
+    std::stable_sort(single.begin(), single.end(), [&](int x, int y) { return inst[x].total > inst[y].total; });
     // regions of one code path (boundary condition, root variant) next to each other
     std::stable_sort(large2.begin(), large2.end(), [&](int x, int y) {
-        const BatchInst &X = b->host_inst[x], &Y = b->host_inst[y];
+        const BatchInst &X = inst[x], &Y = inst[y];
         return X.bc != Y.bc ? X.bc < Y.bc : X.c.rv < Y.c.rv;
     });
-    if (!b->depth_fixed && b->region == 64) {
+    if (!c.depth_fixed && c.region == 64) {
         // the least modelled time per step: workgroups of the busiest of 256
         // CUs, two of which run together (0.62 us per level alone, 1.1 the
         // two), 3 levels to load and store, and 3.7 us per launch.  On 16
@@ -491,60 +496,84 @@ int upload_tasks(ace_batch *b)
         for (int K = 2; K <= kMaxDepth; ++K) {
             int64_t n = 0;
             for (int i : large2) {
-                const BatchInst &I = b->host_inst[i];
+                const BatchInst &I = inst[i];
                 n += ((I.M1 + 63 - 2 * K) / (64 - 2 * K)) * ((I.M2 + 63 - 2 * K) / (64 - 2 * K));
             }
             const int64_t busiest = (n + 255) / 256;
             const double us = (3.7 + (K + 3) * (1.1 * (double)(busiest / 2) + 0.62 * (double)(busiest % 2))) / K;
             if (us >= best) continue;
             best = us;
-            b->depth = K;
+            c.depth = K;
         }
     }
     std::vector<Piece> p;
-    const int oy = std::max(1, b->region - 2 * b->depth), ox = 64 - 2 * b->depth;
+    const int oy = std::max(1, c.region - 2 * c.depth), ox = 64 - 2 * c.depth;
     for (int i : large2) {
-        const BatchInst &I = b->host_inst[i];
+        const BatchInst &I = inst[i];
         for (int y = 0; y < (I.M1 + oy - 1) / oy; ++y)
             for (int x = 0; x < (I.M2 + ox - 1) / ox; ++x) p.push_back({i, y, x});
     }
-    b->n_regions = (int)p.size();
+    const size_t n_regions = p.size();
     for (int i : large1)
-        for (int64_t a = 0; a * kSegOut < b->host_inst[i].total; ++a) p.push_back({i, (int)a, 0});
-    b->n_segments = (int)p.size() - b->n_regions;
+        for (int64_t a = 0; a * kSegOut < inst[i].total; ++a) p.push_back({i, (int)a, 0});
+    const size_t n_segments = p.size() - n_regions;
+    auto chunks_of = [&](int i) {
+        for (int64_t a = 0; a * kChunk < inst[i].total; ++a) p.push_back({i, (int)a, 0});
+    };
     std::vector<int> first(b->count + 1, 0);
     for (int i = 0; i < b->count; ++i) {
-        for (int64_t a = 0; a * kChunk < b->host_inst[i].total; ++a) p.push_back({i, (int)a, 0});
-        first[i + 1] = (int)p.size() - b->n_regions - b->n_segments;
+        chunks_of(i);
+        first[i + 1] = (int)(p.size() - n_regions - n_segments);
     }
-    b->n_chunks = first[b->count];
-    auto chunks_of = [&](const std::vector<int> &v) {
-        const size_t before = p.size();
-        for (int i : v)
-            for (int64_t a = 0; a * kChunk < b->host_inst[i].total; ++a) p.push_back({i, (int)a, 0});
-        return (int)(p.size() - before);
-    };
-    b->n_chunks2 = chunks_of(large2);
-    b->n_chunks1 = chunks_of(large1);
-    b->n_chunks0 = chunks_of(by_step);
+    size_t n_of[3], before = p.size();
+    const std::vector<int> *kinds[3] = {&large2, &large1, &by_step};
+    for (int k = 0; k < 3; ++k) {
+        for (int i : *kinds[k]) chunks_of(i);
+        n_of[k] = p.size() - before;
+        before = p.size();
+    }
     if (p.size() > (size_t)INT32_MAX) return ACE_E_NOMEM;
-    if ((int64_t)p.size() > b->pieces_cap) {
-        if (b->pieces) (void)hipFree(b->pieces);
-        b->pieces = nullptr;
-        b->pieces_cap = 0;
-        BT_HIP(hipMalloc((void **)&b->pieces, sizeof(Piece) * p.size()));
-        b->pieces_cap = (int64_t)p.size();
-    }
-    if (!b->partials) {  // (the chunks do not depend on the choices)
-        BT_HIP(hipMalloc((void **)&b->partials, sizeof(double) * 3 * (size_t)b->n_chunks));
+    if (!b->partials) {  // (the chunks do not depend on the choice)
+        BT_HIP(hipMalloc((void **)&b->partials, sizeof(double) * 3 * (size_t)first[b->count]));
         BT_HIP(hipMalloc((void **)&b->chunk_first, sizeof(int) * first.size()));
         BT_HIP(hipMemcpy(b->chunk_first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice));
     }
-    BT_HIP(hipMemcpy(b->pieces, p.data(), sizeof(Piece) * p.size(), hipMemcpyHostToDevice));
-    BT_HIP(hipMemcpy(b->inst, b->host_inst.data(), sizeof(BatchInst) * b->count, hipMemcpyHostToDevice));
-    if (!b->order.empty())
-        BT_HIP(hipMemcpy(b->order_dev, b->order.data(), sizeof(int) * b->order.size(), hipMemcpyHostToDevice));
+    Piece *pieces = nullptr;
+    BT_HIP(hipMalloc((void **)&pieces, sizeof(Piece) * p.size()));
+    int rc = hip_status(hipMemcpy(pieces, p.data(), sizeof(Piece) * p.size(), hipMemcpyHostToDevice));
+    if (rc >= 0) rc = hip_status(hipMemcpy(b->inst, inst.data(), sizeof(BatchInst) * b->count, hipMemcpyHostToDevice));
+    if (rc >= 0 && !single.empty())
+        rc = hip_status(hipMemcpy(b->order_dev, single.data(), sizeof(int) * single.size(), hipMemcpyHostToDevice));
+    if (rc < 0) {
+        (void)hipFree(pieces);
+        return rc;
+    }
+    drop_graphs(b);
+    if (b->pieces) (void)hipFree(b->pieces);
+    b->pieces = pieces;
+    b->n_regions = (int)n_regions;
+    b->n_segments = (int)n_segments;
+    b->n_chunks = first[b->count];
+    b->n_chunks2 = (int)n_of[0];
+    b->n_chunks1 = (int)n_of[1];
+    b->n_chunks0 = (int)n_of[2];
+    b->n_single = (int)single.size();
+    b->by_step.swap(by_step);
+    b->host_inst.swap(inst);
+    b->resident_limit = c.resident_limit;
+    b->depth = c.depth;
+    b->depth_fixed = c.depth_fixed;
+    b->region = c.region;
     return ACE_OK;
+}
+
+int choose(ace_batch *b, const Choice &c)
+{
+    try {
+        return upload_tables(b, c);
+    } catch (const std::bad_alloc &) {
+        return ACE_E_NOMEM;
+    }
 }
 
 const Piece *chunk_pieces(const ace_batch *b) { return b->pieces + b->n_regions + b->n_segments; }
@@ -697,7 +726,7 @@ int ace_batch_create(int count, const ace_instance_desc *desc, ace_batch **out, 
         return fail(rc);
     if ((rc = hip_status(hipMalloc((void **)&b->trip, sizeof(double) * 3 * count))) < 0) return fail(rc);
     if ((rc = hip_status(hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking))) < 0) return fail(rc);
-    if ((rc = upload_tasks(b)) < 0) return fail(rc);
+    if ((rc = choose(b, choice_of(b))) < 0) return fail(rc);
     *out = b;
     return warn;
 }
@@ -798,11 +827,10 @@ int ace_batch_step(ace_batch *b, int64_t nsteps)
 int ace_batch_set_region(ace_batch *b, int rows)
 {
     if (!b || (rows != 0 && rows != 32 && rows != 64)) return ACE_E_ARG;
-    if (rows != b->region) {
-        b->region = rows;
-        return upload_tasks(b);
-    }
-    return ACE_OK;
+    if (rows == b->region) return ACE_OK;
+    Choice c = choice_of(b);
+    c.region = rows;
+    return choose(b, c);
 }
 
 int ace_batch_set_graphs(ace_batch *b, int enable)
@@ -863,18 +891,19 @@ int ace_batch_get_all(ace_batch *b, double *out, int where)
 int ace_batch_set_resident_limit(ace_batch *b, int64_t limit)
 {
     if (!b || limit < 0) return ACE_E_ARG;
-    b->resident_limit = std::min<int64_t>(limit, RESIDENT_MAX);
-    return upload_tasks(b);
+    Choice c = choice_of(b);
+    c.resident_limit = std::min<int64_t>(limit, RESIDENT_MAX);
+    return choose(b, c);
 }
 
 int ace_batch_set_depth(ace_batch *b, int depth)
 {
     if (!b || depth < 1 || depth > kMaxDepth) return ACE_E_ARG;
+    Choice c = choice_of(b);
+    c.depth = depth;
+    c.depth_fixed = 1;
+    if (depth != b->depth) return choose(b, c);
     b->depth_fixed = 1;
-    if (depth != b->depth) {
-        b->depth = depth;
-        return upload_tasks(b);
-    }
     return ACE_OK;
 }
 
@@ -890,6 +919,8 @@ int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap
     };
     int rc = hip_status(hipMemcpyAsync(save, b->arena_a, sizeof(double) * b->arena_total,
                                        hipMemcpyDeviceToDevice, b->stream));
+    const bool started = rc >= 0;  // the fields are saved
+    const Choice before = choice_of(b);
     // First the region shape and depth of the region rounds at the current
     // resident limit, then the resident limit at the chosen pair.
     const int depths[] = {2, 3, 4, 5, 6};
@@ -905,17 +936,10 @@ int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap
     if (rc >= 0) rc = hip_status(hipEventCreate(&e0));
     if (rc >= 0) rc = hip_status(hipEventCreate(&e1));
     bool first = true;
-    auto choose = [&](int64_t lim, int depth, int region) {
-        b->resident_limit = lim;
-        b->depth = depth;
-        b->depth_fixed = 1;
-        b->region = region;
-        return upload_tasks(b);
-    };
     // times one batch step of trial_steps for (lim, depth, region); returns ms or a negative error
     auto trial = [&](int64_t lim, int depth, int region, double *ms_out) -> int {
         int r;
-        if ((r = choose(lim, depth, region)) < 0) return r;
+        if ((r = choose(b, {lim, depth, 1, region})) < 0) return r;
         if ((r = restore()) < 0) return r;
         if ((r = ace_batch_step(b, trial_steps)) < 0) return r;  // builds the graph, warms up
         if ((r = restore()) < 0) return r;
@@ -959,8 +983,11 @@ int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    if (rc >= 0) rc = choose(best_lim, best_depth, best_region);
-    if (rc >= 0) rc = restore();
+    // (an error in a trial leaves the fields and the choice as they were)
+    if (rc >= 0) rc = choose(b, {best_lim, best_depth, 1, best_region});
+    else if (started) (void)choose(b, before);
+    const int rr = started ? restore() : ACE_OK;
+    if (rc >= 0) rc = rr;
     if (rc >= 0) rc = hip_status(hipStreamSynchronize(b->stream));
     (void)hipFree(save);
     if (rc < 0) return rc;

@@ -1,0 +1,37 @@
+"""What the library's host code asks of the HIP runtime, and what it leaves
+behind when the runtime refuses, on a stub runtime (no GPU, kernels do
+nothing)."""
+import hip_stub
+
+
+def test_batch_keeps_its_tables_when_new_ones_are_refused(tmp_path):
+    """A choice whose tables cannot be allocated leaves the batch with the
+    choice and the tables it had: the next step launches what it did before."""
+    hip_stub.run(tmp_path, """
+        b = batch([((300,), 2), ((200, 300), 0), ((90, 90), 1)])
+        b.set_depth(4)
+        b.set_graphs(False)
+        log()
+        b.step(8)
+        before = log()
+        assert sum("k_batch_regions" in x for x in before) == 2
+        stub.stub_refuse_from(ctypes.c_uint64(1))
+        for change in (lambda: b.set_depth(1), lambda: b.set_region(32), lambda: b.set_region(0),
+                       lambda: b.set_resident_limit(0), lambda: b.autotune(2)):
+            try:
+                change()
+                raise SystemExit("a refused allocation went unnoticed")
+            except ace.AceError as e:
+                assert e.code == ace.ACE_E_NOMEM, e.code
+            log()
+            b.step(8)
+            assert log() == before
+            b.monitor()
+            assert not any("(nil)" in x.split("args")[1] for x in log() if "args" in x)
+        stub.stub_refuse_from(ctypes.c_uint64(2 ** 64 - 1))
+        b.set_depth(1)
+        log()
+        b.step(8)
+        assert sum("k_batch_regions" in x for x in log()) == 8
+        b.close()
+    """)
