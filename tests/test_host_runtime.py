@@ -9,14 +9,14 @@ def test_batch_keeps_its_tables_when_new_ones_are_refused(tmp_path):
     choice and the tables it had: the next step launches what it did before."""
     hip_stub.run(tmp_path, """
         b = batch([((300,), 2), ((200, 300), 0), ((90, 90), 1)])
-        b.set_depth(4)
+        b.set_depth(1)
         b.set_graphs(False)
         log()
         b.step(8)
         before = log()
-        assert sum("k_batch_regions" in x for x in before) == 2
+        assert sum("k_batch_regions" in x for x in before) == 8
         stub.stub_refuse_from(ctypes.c_uint64(1))
-        for change in (lambda: b.set_depth(1), lambda: b.set_region(32), lambda: b.set_region(0),
+        for change in (lambda: b.set_depth(8), lambda: b.set_region(32), lambda: b.set_region(0),
                        lambda: b.set_resident_limit(0), lambda: b.autotune(2)):
             try:
                 change()
@@ -29,9 +29,9 @@ def test_batch_keeps_its_tables_when_new_ones_are_refused(tmp_path):
             b.monitor()
             assert not any("(nil)" in x.split("args")[1] for x in log() if "args" in x)
         stub.stub_refuse_from(ctypes.c_uint64(2 ** 64 - 1))
-        b.set_depth(1)
+        b.set_depth(4)
         log()
         b.step(8)
-        assert sum("k_batch_regions" in x for x in log()) == 8
+        assert sum("k_batch_regions" in x for x in log()) == 2
         b.close()
     """)
