@@ -8,7 +8,7 @@ def test_batch_keeps_its_tables_when_new_ones_are_refused(tmp_path):
     """A choice whose tables cannot be allocated leaves the batch with the
     choice and the tables it had: the next step launches what it did before."""
     hip_stub.run(tmp_path, """
-        b = batch([((300,), 2), ((200, 300), 0), ((90, 90), 1)])
+        b = batch([((300,), 2), ((2000, 300), 0), ((90, 90), 1)])
         b.set_depth(1)
         b.set_graphs(False)
         log()
@@ -16,7 +16,7 @@ def test_batch_keeps_its_tables_when_new_ones_are_refused(tmp_path):
         before = log()
         assert sum("k_batch_regions" in x for x in before) == 8
         stub.stub_refuse_from(ctypes.c_uint64(1))
-        for change in (lambda: b.set_depth(8), lambda: b.set_region(32), lambda: b.set_region(0),
+        for change in (lambda: b.set_region(32), lambda: b.set_depth(8), lambda: b.set_region(0),
                        lambda: b.set_resident_limit(0), lambda: b.autotune(2)):
             try:
                 change()
