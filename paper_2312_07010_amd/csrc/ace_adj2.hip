@@ -15,7 +15,11 @@
 // node.  mu passes between launches; the first takes lambda^T and phi^T, the
 // last writes lambda^0.  Boundary images as in the forward step: mu is even at
 // Neumann and odd at Dirichlet walls, phi enters squared.  dL/dkappa sums
-// phi^n Lambda mu (Lambda is symmetric), so phi's neighbours are not needed.
+// (phi^n - b) Lambda mu (Lambda is symmetric), so phi's neighbours are not
+// needed.  Without Dirichlet walls Lambda's columns sum to 0 and any b gives the
+// same sum: b is the state's first value if a node in the middle holds it too,
+// so that a uniform field's gradient is 0 as that of mu Lambda phi^n is and not
+// a residue of Lambda mu's roundings, and 0 otherwise.
 //
 // Bound: the states' bytes and the region levels' issue, about equally.  512^2
 // with 32-step segments: 15.5 us per launch of 8 transposed and 8 recomputed
@@ -43,6 +47,15 @@ __device__ __forceinline__ double dprime(double p2, const StepCoef &c)
     double r = __builtin_amdgcn_rcp(dp);
     r = fma(r, fma(-dp, r, 1.0), r);
     return fma(r, fma(-dp, r, 1.0), r);
+}
+
+// One lane's value, in scalar registers.
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u & 0xffffffffull), lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
 template <int BC, int RV, int TRW, int RYT>
@@ -83,20 +96,23 @@ __global__ __launch_bounds__(RX * TRW) void k_adj2(Shape s, StepCoef c0, Adj2Arg
     }
     // level t (1..S) uses phi^{m+S-t}, in slot t % 4, loaded three levels ahead
     // (a level takes under 1 us, a load from another XCD's cache over 1)
-    double v[RYT], ph[4][RYT];
-    auto fetch = [&](int t, double(&dst)[RYT]) {
+    double v[RYT], ph[4][RYT], base[4];
+    // (lane 0 holds a state's first value, the others the middle one)
+    const int probe = tx == 0 ? 0 : (g.M1 / 2) * g.M2 + g.M2 / 2;
+    auto fetch = [&](int t, double(&dst)[RYT], double &b) {
         const double *p = t >= S ? a.phi_first : a.phi_rest + (int64_t)(S - t - 1) * a.stride;
 #pragma unroll
         for (int r = 0; r < RYT; ++r) dst[r] = p[off[r]];
+        if (BC != BC_HD) b = p[probe];
     };
     g.load(s, a.mu_in, v);
     if (a.phi_end) {
 #pragma unroll
         for (int r = 0; r < RYT; ++r) ph[0][r] = a.phi_end[off[r]];
     }
-    fetch(1, ph[1]);
-    fetch(2, ph[2]);
-    fetch(3, ph[3]);
+    fetch(1, ph[1], base[1]);
+    fetch(2, ph[2], base[2]);
+    fetch(3, ph[3], base[3]);
     if (a.phi_end) {  // lambda^T: its mu from phi^T
 #pragma unroll
         for (int r = 0; r < RYT; ++r) v[r] *= dprime(ph[0][r] * ph[0][r], c);
@@ -107,8 +123,10 @@ __global__ __launch_bounds__(RX * TRW) void k_adj2(Shape s, StepCoef c0, Adj2Arg
     const int H = g.M1 - g.yr0 + S < RH ? g.M1 - g.yr0 + S : RH;
     double gs = 0.0;
     int t = 1;
-    auto level = [&](const double(&p_)[RYT], double(&next)[RYT]) __attribute__((always_inline)) -> bool {
-        if (t + 3 <= S) fetch(t + 3, next);
+    auto level = [&](const double(&p_)[RYT], double b, double(&next)[RYT], double &next_b)
+                     __attribute__((always_inline)) -> bool {
+        const double b0 = BC != BC_HD && lane_value(b, 0) == lane_value(b, 1) ? lane_value(b, 0) : 0.0;
+        if (t + 3 <= S) fetch(t + 3, next, next_b);
         const int rd = (t - 1) & 1;
         const double eT = eb(rd, 1, tr > 0 ? tr - 1 : 0)[tx];
         const double eB = eb(rd, 0, tr < TRW - 1 ? tr + 1 : TRW - 1)[tx];
@@ -132,7 +150,7 @@ __global__ __launch_bounds__(RX * TRW) void k_adj2(Shape s, StepCoef c0, Adj2Arg
                 const double jd = fma(-c.h3, p2, c.oph);
                 lam[r] = fma(c.kappa, lap, jd * mu);
                 rp[r] = dprime(p2, c);
-                gs = fma(oof[r] >= 0 ? p : 0.0, lap, gs);
+                gs = fma(oof[r] >= 0 ? p - b0 : 0.0, lap, gs);
             }
             const bool write_lambda = t == S && a.last;
 #pragma unroll
@@ -149,10 +167,10 @@ __global__ __launch_bounds__(RX * TRW) void k_adj2(Shape s, StepCoef c0, Adj2Arg
         return false;
     };
     for (;;) {
-        if (level(ph[1], ph[0])) break;
-        if (level(ph[2], ph[1])) break;
-        if (level(ph[3], ph[2])) break;
-        if (level(ph[0], ph[3])) break;
+        if (level(ph[1], base[1], ph[0], base[0])) break;
+        if (level(ph[2], base[2], ph[1], base[1])) break;
+        if (level(ph[3], base[3], ph[2], base[2])) break;
+        if (level(ph[0], base[0], ph[3], base[3])) break;
     }
 #pragma unroll
     for (int r = 0; r < RYT; ++r)

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint(Shape s, StepCoef c,
 // 3D: the transposed step on mu (ace_adj2.hip), a thread per column of Z planes
 // with all its values in flight at once: mu of the node and its neighbours,
 // phi of the node.  phi_end: mu_in is lambda, and its mu is taken at every
-// node read.  (k_adjoint reads three fields at seven nodes each and evaluates
+// node read.  dL/dkappa sums (phi - b) Lambda mu as in 2D.  (k_adjoint reads three fields at seven nodes each and evaluates
 // mu at all seven: 16.6 us per step of 96^3, this one 7.9.)
 template <int BC, int Z, bool FIRST>
 __global__ __launch_bounds__(col::CNT) void k_adjoint_col(int M0, int M1, int M2, int nb, StepCoef c,
@@ -141,6 +141,8 @@ __global__ __launch_bounds__(col::CNT) void k_adjoint_col(int M0, int M1, int M2
         p[i] = col::load(col::plane_at<BC>(phi, z, M0, PS), k.o);
     }
     q[Z + 1] = at(z0 + nz, k.o);
+    const double mid = phi[(int64_t)(M0 / 2) * PS + (M1 / 2) * M2 + M2 / 2];
+    const double b = BC != BC_HD && phi[0] == mid ? mid : 0.0;
     double g = 0.0;
 #pragma unroll
     for (int i = 0; i < Z; ++i) {
@@ -153,7 +155,7 @@ __global__ __launch_bounds__(col::CNT) void k_adjoint_col(int M0, int M1, int M2
         if (!last) v = mu_of(v, p[i], c);
         const __amdgpu_buffer_rsrc_t r = col::plane_rsrc(mu_out + (int64_t)(z0 + i) * PS, PS * 8);
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(col::BufB64, v), r, (int)k.o, 0, 0);
-        if (k.o != col::kNone) g = fma(p[i], lap, g);
+        if (k.o != col::kNone) g = fma(p[i] - b, lap, g);
     }
     g = wave_sum(g);
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = g;

@@ -9,6 +9,13 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+
 STEPS, W, KEEP = 5, 600, 300  # an odd count of one-step launches ends in the second arena
 
 
