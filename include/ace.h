@@ -117,7 +117,8 @@ int ace_params(const ace_solver *s, ace_params_t *p);
 /* Runs all later device work of the handle on this HIP stream (hipStream_t,
  * may be NULL for the default stream).  Switching to another stream first
  * waits for the old one and drops the graphs captured for it, so no replay
- * still in flight there loses its graph. */
+ * still in flight there loses its graph.  Where either stream is under capture
+ * it does not wait: there the caller has ordered them. */
 int ace_set_stream(ace_solver *s, void *hip_stream);
 
 /* Uses caller-owned device buffers a, b (each ace_shape total doubles) as

@@ -279,13 +279,17 @@ double energy_from(const Problem &p, const double *trip)
     return dxd * (trip[0] + cg * trip[1]);
 }
 
-void leave_stream(hipStream_t old, hipStream_t next)
+static bool capturing(hipStream_t stream)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(next, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return;
-    }
+    if (hipStreamIsCapturing(stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // (the default stream while another one captures)
+    return true;
+}
+
+void leave_stream(hipStream_t old, hipStream_t next)
+{
+    if (capturing(next) || capturing(old)) return;
     if (hipStreamSynchronize(old) != hipSuccess) (void)hipGetLastError();
 }
 

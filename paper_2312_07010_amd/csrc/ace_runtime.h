@@ -37,8 +37,9 @@ StepCoef coef_of(const Problem &p);
 // E = dxd (bulk + cg grad) with dxd = dx^d and cg = kappa / (2 dt).
 void energy_coefs(const Problem &p, double *dxd, double *cg);
 double energy_from(const Problem &p, const double *trip);
-// Waits for a handle's old stream before its work moves to `next` (a stream
-// under capture cannot wait for another: there the caller has ordered them).
+// Waits for a handle's old stream before its work moves to `next`.  Not where
+// either is under capture: a wait would break the old stream's, and a new
+// stream's cannot wait for another (the caller has ordered them).
 void leave_stream(hipStream_t old, hipStream_t next);
 // (Re)allocates *ptr to hold at least need doubles of device memory.
 int grow(double **ptr, int64_t *cap, int64_t need);

@@ -35,3 +35,30 @@ def test_batch_keeps_its_tables_when_new_ones_are_refused(tmp_path):
         assert sum("k_batch_regions" in x for x in log()) == 2
         b.close()
     """)
+
+
+def test_leaving_a_capturing_stream_does_not_wait_for_it(tmp_path):
+    """Switching a handle away from, or to, a stream under capture issues no
+    synchronisation (one on the old stream would break its capture); between
+    streams that do not capture it waits for the old one."""
+    hip_stub.run(tmp_path, """
+        A, B = 0x1000, 0x2000
+        s = solver(2, (300, 200), 0)
+        b = batch([((300,), 2), ((200, 300), 0)])
+        for h in (s, b):
+            h.set_stream(A)
+            log()
+            h.set_stream(B)
+            assert log() == ["sync 0x1000"]
+            stub.stub_set_capturing(ctypes.c_void_p(A), 1)
+            h.set_stream(A)
+            if h is s:
+                h.step(3)
+            h.set_stream(B)
+            assert not [x for x in log() if "sync" in x or "broken" in x]
+            stub.stub_set_capturing(ctypes.c_void_p(A), 0)
+        s.set_stream(None)
+        b.set_stream(None)
+        s.close()
+        b.close()
+    """)
