@@ -366,6 +366,8 @@ int ace_pop_destroy(ace_pop *p);
  * s, and the device bytes the handle holds (any output may be NULL). */
 int ace_pop_info(const ace_pop *p, int64_t M[3], int64_t *total, int *q, double *omega1,
                  double *s, int64_t *device_bytes);
+/* Stream of the handle's work; switching waits for the old stream first (as
+ * ace_set_stream). */
 int ace_pop_set_stream(ace_pop *p, void *hip_stream);
 /* Kernel of ace_pop_step (every choice computes the same result bit for
  * bit): ACE_POP_DIRECT one thread per node, phi of the node and its

@@ -671,6 +671,8 @@ int ace_pop_info(const ace_pop *P, int64_t M[3], int64_t *total, int *q, double 
 int ace_pop_set_stream(ace_pop *P, void *st)
 {
     if (!P) return ACE_E_ARG;
+    // (the populations, phi and the carried phi are written and read across calls)
+    if ((hipStream_t)st != P->stream) leave_stream(P->stream, (hipStream_t)st);
     P->stream = (hipStream_t)st;
     return ACE_OK;
 }

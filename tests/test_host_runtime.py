@@ -45,7 +45,8 @@ def test_leaving_a_capturing_stream_does_not_wait_for_it(tmp_path):
         A, B = 0x1000, 0x2000
         s = solver(2, (300, 200), 0)
         b = batch([((300,), 2), ((200, 300), 0)])
-        for h in (s, b):
+        p = ace.Pop(2, [64, 64], [0.0, 0.0], [64.0, 64.0], 7.0, 1e-3, 2)
+        for h in (s, b, p):
             h.set_stream(A)
             log()
             h.set_stream(B)
@@ -57,8 +58,6 @@ def test_leaving_a_capturing_stream_does_not_wait_for_it(tmp_path):
             h.set_stream(B)
             assert not [x for x in log() if "sync" in x or "broken" in x]
             stub.stub_set_capturing(ctypes.c_void_p(A), 0)
-        s.set_stream(None)
-        b.set_stream(None)
-        s.close()
-        b.close()
+            h.set_stream(None)
+            h.close()
     """)
