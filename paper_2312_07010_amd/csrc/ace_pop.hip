@@ -747,7 +747,13 @@ int ace_pop_step(ace_pop *P, int64_t nsteps)
         hipError_t e = launch_pop_step(P->shape, P->c, P->f[P->cur], P->f[P->cur ^ 1], mode,
                                        mode == 3 ? P->carry[P->ccur] : P->phi,
                                        mode == 3 ? P->carry[P->ccur ^ 1] : nullptr, pops, P->stream);
-        if (e != hipSuccess) return hip_status(e);
+        if (e != hipSuccess) {
+            if (mode == 3) {  // the populations are still those the call began with
+                P->steps -= t;
+                P->carry_ok = 0;
+            }
+            return hip_status(e);
+        }
         if (pops) P->cur ^= 1;
         if (mode == 3) P->ccur ^= 1;
         ++P->steps;

@@ -61,3 +61,29 @@ def test_leaving_a_capturing_stream_does_not_wait_for_it(tmp_path):
             h.set_stream(None)
             h.close()
     """)
+
+
+def test_population_step_that_fails_on_the_way(tmp_path):
+    """A launch refused in the middle of a call whose inner steps write phi alone
+    leaves the handle at the state the call began with: its step count, and phi
+    from its populations at the next step."""
+    hip_stub.run(tmp_path, """
+        import numpy as np
+        p = ace.Pop(2, [64, 64], [0.0, 0.0], [64.0, 64.0], 7.0, 1e-3, 2)
+        p.set_phi0(np.zeros((64, 64)))
+        p.step(2)
+        log()
+        stub.stub_fail_launch(ctypes.c_int64(3))
+        try:
+            p.step(6)
+            raise SystemExit("a refused launch went unnoticed")
+        except ace.AceError as e:
+            assert e.code == ace.ACE_E_HIP
+        stub.stub_fail_launch(ctypes.c_int64(-1))
+        assert L.ace_pop_step_count(p._h) == 2
+        log()
+        p.step(1)
+        assert ["k_pop_moment" in x for x in log()] == [True, False]
+        assert L.ace_pop_step_count(p._h) == 3
+        p.close()
+    """)
