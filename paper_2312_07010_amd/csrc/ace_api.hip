@@ -820,6 +820,23 @@ int graph_for(ace_solver *s, int kernel, hipGraphExec_t *out)
     return ACE_OK;
 }
 
+// Graph replays from buf[cur] for the first of nsteps steps, as long as two
+// more graphs' steps are left; the steps taken go to *done.
+int replay(ace_solver *s, int kernel, int64_t nsteps, int64_t *done)
+{
+    *done = 0;
+    if (s->graph_launches < 2) return ACE_OK;
+    const int64_t chunk = s->graph_launches * steps_per_launch_of(s, kernel);
+    while (nsteps - *done >= 2 * chunk) {
+        hipGraphExec_t e = nullptr;
+        ACE_TRY(graph_for(s, kernel, &e));
+        ACE_HIP(hipGraphLaunch(e, s->stream));
+        s->steps += chunk;  // even launch count: s->cur is unchanged
+        *done += chunk;
+    }
+    return ACE_OK;
+}
+
 int advance(ace_solver *s, int64_t nsteps)
 {
     if (nsteps <= 0) return ACE_OK;
@@ -829,18 +846,8 @@ int advance(ace_solver *s, int64_t nsteps)
         s->steps += nsteps;
         return ACE_OK;
     }
-    const int per = steps_per_launch_of(s, k);
     int64_t i = 0;
-    if (s->graph_launches >= 2) {
-        const int64_t chunk = s->graph_launches * per;
-        while (nsteps - i >= 2 * chunk) {
-            hipGraphExec_t e = nullptr;
-            ACE_TRY(graph_for(s, k, &e));
-            ACE_HIP(hipGraphLaunch(e, s->stream));
-            s->steps += chunk;  // even launch count: s->cur is unchanged
-            i += chunk;
-        }
-    }
+    ACE_TRY(replay(s, k, nsteps, &i));
     while (i < nsteps) {
         const int t = launch_steps(s, k, nsteps - i, false, nullptr);
         if (t < 0) return t;
@@ -1774,6 +1781,7 @@ int ace_forward_ckpt(ace_solver *s, const double *phi0, int where, int64_t nstep
     const size_t bytes = (size_t)total * sizeof(double);
     const int k = effective_kernel(s);
     const double *in = s->buf[s->cur];
+    int64_t in_ckpt = 0;  // steps the field at `in` is ahead of buf[cur], whose count is s->steps
     ACE_HIP(hipMemcpyAsync(s->ckpt, in, bytes, hipMemcpyDeviceToDevice, s->stream));
     for (int64_t j = 0; j < nck; ++j) {
         int64_t left = std::min<int64_t>(every, nsteps - j * every);
@@ -1785,17 +1793,26 @@ int ace_forward_ckpt(ace_solver *s, const double *phi0, int where, int64_t nstep
             continue;
         }
         // a segment's last launch writes the next checkpoint, which the next
-        // segment's first launch reads
+        // segment's first launch reads; graphs replay what lies between
         while (left > 0) {
+            if (in == s->buf[s->cur]) {
+                int64_t done = 0;
+                ACE_TRY(replay(s, k, left, &done));
+                left -= done;
+            }
             double *out = s->buf[s->cur ^ 1];
             const int64_t t = steps_of_launch(s, k, left);
             if (t == left && j + 1 < nck) out = s->ckpt + (j + 1) * total;
             const int taken = launch_between(s, k, in, out, left, nullptr, nullptr);
             if (taken < 0) return taken;
             if (taken != t) return ACE_E_STATE;
-            s->steps += taken;
             left -= taken;
-            if (out == s->buf[s->cur ^ 1]) s->cur ^= 1;
+            in_ckpt += taken;
+            if (out == s->buf[s->cur ^ 1]) {
+                s->cur ^= 1;
+                s->steps += in_ckpt;
+                in_ckpt = 0;
+            }
             in = out;
         }
     }

@@ -87,3 +87,37 @@ def test_population_step_that_fails_on_the_way(tmp_path):
         assert L.ace_pop_step_count(p._h) == 3
         p.close()
     """)
+
+
+def test_checkpointed_forward_replays_graphs(tmp_path):
+    """Segments of many launches are replayed between the launches that read and
+    write checkpoints; a launch refused on the way leaves the step count of the
+    field the handle holds."""
+    hip_stub.run(tmp_path, """
+        import numpy as np
+        s = solver(3, (24, 20, 28), 0)
+        s.set_kernel(ace.ACE_KERNEL_DIRECT)  # one step per launch
+        phi = np.zeros(s.shape)
+        s.set_graph_launches(32)
+        log()
+        s.forward_ckpt(phi, 450, 150)
+        lines = log()
+        steps = [x for x in lines if x.startswith("launch")]
+        assert sum(x == "instantiate" for x in lines) <= 2  # (one per buffer the segments begin in)
+        assert sum(x == "replay" for x in lines) == 9  # 3 of 32 steps a segment
+        captured = 32 * sum(x == "instantiate" for x in lines)
+        assert len(steps) - captured == 450 - 9 * 32
+        assert s.step_count == 450
+        s.set_graph_launches(0)
+        for after in (1, 3, 4, 5):
+            stub.stub_fail_launch(ctypes.c_int64(after))
+            try:
+                s.forward_ckpt(phi, 12, 4)
+                raise SystemExit("a refused launch went unnoticed")
+            except ace.AceError:
+                pass
+            # (launch 4 writes the second checkpoint, not the handle's field)
+            assert s.step_count == (3 if after == 4 else after)
+        stub.stub_fail_launch(ctypes.c_int64(-1))
+        s.close()
+    """)
