@@ -188,7 +188,7 @@ __global__ __launch_bounds__(RX * TRW) void k_adj2(Shape s, StepCoef c0, Adj2Arg
 template <int RYT>
 hipError_t launch(const Shape &s, const StepCoef &c, const Adj2Args &a, hipStream_t st)
 {
-    constexpr int TRW = 16;
+    constexpr int TRW = ADJ2_THREADS / 64;
     int tiles_x, n;
     tb2::tiles<TRW, RYT>(s, a.K, tiles_x, n);
     if (a.n_rev != 0 && a.n_rev != n) return hipErrorInvalidValue;

@@ -197,11 +197,16 @@ int64_t adjoint_col_blocks(const Shape &s)
     return ((s.M1 * s.M2 + col::CNT - 1) / col::CNT) * ((s.M0 + Z - 1) / Z);
 }
 
+bool adjoint_col_supported(const Shape &s)
+{
+    return col3d_supported(s) && adjoint_col_blocks(s) <= max_blocks(col::CNT);
+}
+
 hipError_t launch_adjoint_col(const Shape &s, const StepCoef &c, const double *mu_in, const double *phi,
                               const double *phi_end, double *mu_out, double *gpart, int last, int accumulate,
                               hipStream_t st)
 {
-    if (!col3d_supported(s)) return hipErrorInvalidValue;
+    if (!adjoint_col_supported(s)) return hipErrorInvalidValue;
     const int nb = (int)((s.M1 * s.M2 + col::CNT - 1) / col::CNT);
     const dim3 grid((unsigned)adjoint_col_blocks(s));
     auto go = [&](auto BCc, auto Zc) {

@@ -478,12 +478,15 @@ double tb3_us(int v, const Shape &s, int zc, bool fex)
     return (std::max(march, hbm) + 0.1 * march) / K;
 }
 
-// Plane chunks of variant v, the least modelled time first.
+// Plane chunks of variant v that one launch can hold, the least modelled time
+// first (none: a plane has too many tiles).
 std::vector<int> tb3_chunks(int v, const Shape &s, bool fex)
 {
+    const int64_t most = max_blocks(64 * TB3_TABLE[v].rows / TB3_TABLE[v].rpt);
     std::vector<std::pair<double, int>> t;
     for (int zc : TB3_CHUNKS)
-        if (zc <= std::max<int64_t>(s.M0, 8)) t.push_back({tb3_us(v, s, zc, fex), zc});
+        if (zc <= std::max<int64_t>(s.M0, 8) && tb3_partials_needed(v, s, zc) <= most)
+            t.push_back({tb3_us(v, s, zc, fex), zc});
     std::stable_sort(t.begin(), t.end(), [](const auto &a, const auto &b) { return a.first < b.first; });
     std::vector<int> out;
     for (const auto &x : t) out.push_back(x.second);
@@ -595,25 +598,30 @@ bool monitor_resident(const ace_solver *s, int64_t every)
     return 1.5 + steps * (0.18 + 2.35e-4 * n) < blocked;
 }
 
+bool on_tb2(const ace_solver *s, int K) { return use_tb2(s) && tb2_fits(s->tb2, s->shape, K); }
+
 // One launch of the handle's 2D blocked kernel (K steps; level_stride > 0:
-// every level written, as in launch_step_tblock2d).
+// every level written, as in launch_step_tblock2d): on its register regions,
+// or on the LDS ones (of half the threads) where those are too many.
 hipError_t launch_blocked2d(const ace_solver *s, const double *in, double *out, double *parts,
                             int64_t *nparts, int K, int64_t level_stride, hipStream_t st)
 {
-    if (use_tb2(s)) return launch_step_tb2(s->tb2, s->shape, s->coef, in, out, parts, nparts, K, level_stride, st);
+    if (on_tb2(s, K)) return launch_step_tb2(s->tb2, s->shape, s->coef, in, out, parts, nparts, K, level_stride, st);
     return launch_step_tblock2d(s->shape, s->coef, in, out, parts, nparts, K, level_stride, st);
 }
 
 int64_t blocked2d_blocks(const ace_solver *s, int K)
 {
-    return use_tb2(s) ? tb2_blocks(s->tb2, s->shape, K) : tblock2d_blocks(s->shape, K);
+    return on_tb2(s, K) ? tb2_blocks(s->tb2, s->shape, K) : tblock2d_blocks(s->shape, K);
 }
 
 // The plane chunk of the handle's variant, unless it was set or tuned.
 void follow_chunk(ace_solver *s)
 {
     if (s->p.d != 3 || s->zchunk_fixed) return;
-    s->zchunk = (s->tb3 >= 0 && tb3_supported(s->shape)) ? tb3_chunks(s->tb3, s->shape, s->coef.fex)[0] : 32;
+    std::vector<int> zcs;
+    if (s->tb3 >= 0 && tb3_supported(s->shape)) zcs = tb3_chunks(s->tb3, s->shape, s->coef.fex);
+    s->zchunk = zcs.empty() ? 32 : zcs[0];
 }
 
 // The rule's kernel and launch shape for a new handle.
@@ -629,6 +637,7 @@ void plan_launch(ace_solver *s)
             for (int K = 2; K <= std::min(tb2_max_depth(v), tblock2d_max_depth()); ++K) {
                 const double us = TB2_MODEL[v].us(tb2_blocks(v, f, K), K) / K;
                 if (tb2_max_depth(v) < tblock2d_max_depth() || us >= best) continue;  // (any depth stays settable)
+                if (!tb2_fits(v, f, K)) continue;
                 best = us;
                 s->tb2 = v;
                 s->depth2 = K;
@@ -642,11 +651,15 @@ void plan_launch(ace_solver *s)
     }
     // (2D: the LDS-resident kernel takes 0.52 us per step at 40 x 40 and 1.03
     // at 64 x 64, the blocked one 0.65 at both)
-    if (f.d == 2 && s->p.total > 2048 && tblock2d_supported(f)) s->rule_kernel = ACE_KERNEL_TBLOCK;
+    if (f.d == 2 && s->p.total > 2048 && !s->plan_fixed &&
+        (s->tb2 >= 0 || tblock2d_blocks(f, s->depth2) <= max_blocks(TBLOCK2D_THREADS)))
+        s->rule_kernel = ACE_KERNEL_TBLOCK;
     if (f.d == 3 && tb3_supported(f)) {
         double of_depth[5] = {1e300, 1e300, 1e300, 1e300, 1e300};
         for (int v = 0; v < TB3_VARIANTS; ++v) {
-            const int zc = tb3_chunks(v, f, s->coef.fex)[0], K = TB3_TABLE[v].depth;
+            const std::vector<int> zcs = tb3_chunks(v, f, s->coef.fex);
+            if (zcs.empty()) continue;
+            const int zc = zcs[0], K = TB3_TABLE[v].depth;
             const double us = tb3_us(v, f, zc, s->coef.fex);
             if (us < of_depth[K]) {
                 of_depth[K] = us;
@@ -661,8 +674,8 @@ void plan_launch(ace_solver *s)
     }
     if (s->plan_fixed) return;
     if (f.d == 3 && s->rule_kernel == ACE_KERNEL_DIRECT &&
-        kColumnUs + kColumnUsPerNode * (double)s->p.total > best)
-        s->rule_kernel = ACE_KERNEL_TBLOCK;
+        (s->tb3 < 0 || !col3d_supported(f) || kColumnUs + kColumnUsPerNode * (double)s->p.total > best))
+        s->rule_kernel = ACE_KERNEL_TBLOCK;  // (without a region of k_tb3 the two-step kernel)
 }
 
 // The k_tb3 variant for a launch of `kernel` with `remaining` steps to go (-1:
@@ -909,23 +922,30 @@ int read_monitor(ace_solver *s, double *host3)
     return ACE_OK;
 }
 
-// Reverse sweep with the recompute of each segment in the launches of the one
-// after it (ace_adj2.hip).  Leaves lambda^0 in lam[*lc], dL/dkappa in gsum.
-int backward_regions(ace_solver *s, double *const lam[2], int *lc)
+// Region rows and depth of the reverse sweep with the least modelled time for
+// a segment; false where no launch can hold the regions of both its kinds.
+bool adj2_shape(const ace_solver *s, int *rows, int *K)
 {
-    const int64_t total = s->p.total, every = s->ck_every, nsteps = s->ck_steps;
-    // regions and depth with the least modelled time for a segment
-    int rows = 32, K = 8;
+    const int64_t every = s->ck_every;
     double best = 1e300;
     for (int v = 0; v < 2; ++v)
         for (int d = 2; d <= std::min<int64_t>(12, std::max<int64_t>(every, 2)); ++d) {
-            const int64_t launches = (std::min(every, nsteps) + d - 1) / d;
-            const double us = (double)launches * TB2_MODEL[v ? 2 : 1].us(2 * adj2_tiles(s->shape, v ? 64 : 32, d), d);
-            if (us >= best) continue;
+            const int64_t launches = (std::min(every, s->ck_steps) + d - 1) / d;
+            const int64_t blocks = 2 * adj2_tiles(s->shape, v ? 64 : 32, d);
+            const double us = (double)launches * TB2_MODEL[v ? 2 : 1].us(blocks, d);
+            if (us >= best || blocks > max_blocks(ADJ2_THREADS)) continue;
             best = us;
-            rows = v ? 64 : 32;
-            K = d;
+            *rows = v ? 64 : 32;
+            *K = d;
         }
+    return best < 1e300;
+}
+
+// Reverse sweep with the recompute of each segment in the launches of the one
+// after it (ace_adj2.hip).  Leaves lambda^0 in lam[*lc], dL/dkappa in gsum.
+int backward_regions(ace_solver *s, int rows, int K, double *const lam[2], int *lc)
+{
+    const int64_t total = s->p.total, every = s->ck_every, nsteps = s->ck_steps;
     const int n_tiles = (int)adj2_tiles(s->shape, rows, K);
     auto seg = [&](int64_t j) { return s->seg + (j & 1) * (every + 1) * total; };  // phi^{j every + 1} ..
     bool first = true;
@@ -978,7 +998,7 @@ int backward_steps(ace_solver *s, int k, double *const lam[2], int *lc)
     const int64_t total = s->p.total, every = s->ck_every, nsteps = s->ck_steps;
     const size_t bytes = (size_t)total * sizeof(double);
     const int64_t npart = adjoint_partials_needed(s->shape);
-    const bool columns = col3d_supported(s->shape);  // mu form, one sum for the sweep
+    const bool columns = adjoint_col_supported(s->shape);  // mu form, one sum for the sweep
     const bool blocked2d = (k == ACE_KERNEL_TBLOCK && s->p.d == 2);
     if (k == ACE_KERNEL_TBLOCK && !blocked2d) k = one_step_kernel(s->shape);
     if (!s->aux) ACE_HIP(hipStreamCreateWithFlags(&s->aux, hipStreamNonBlocking));
@@ -1772,7 +1792,7 @@ int ace_forward_ckpt(ace_solver *s, const double *phi0, int where, int64_t nstep
     ACE_TRY(grow(&s->seg, &s->seg_cap, 2 * (every + 1) * total));
     ACE_TRY(grow(&s->lam, &s->lam_cap, 2 * total));
     int64_t parts = adjoint_partials_needed(s->shape) * every;
-    if (col3d_supported(s->shape)) parts = std::max(parts, adjoint_col_blocks(s->shape));
+    if (adjoint_col_supported(s->shape)) parts = std::max(parts, adjoint_col_blocks(s->shape));
     if (tblock2d_supported(s->shape)) {
         parts = std::max<int64_t>(parts, tblock2d_blocks(s->shape, tblock2d_max_depth()) * every);
         if (tb2_supported(s->shape)) parts = std::max(parts, adj2_tiles(s->shape, 32, 12));
@@ -1836,7 +1856,7 @@ int ace_backward(ace_solver *s, const double *lambdaT, double *dphi0, double *de
     const size_t bytes = (size_t)total * sizeof(double);
     if (s->seg_cap < 2 * (every + 1) * total || s->lam_cap < 2 * total) return ACE_E_STATE;
     double *lam[2] = {s->lam, s->lam + total};
-    int lc = 0;
+    int lc = 0, rows = 0, K = 0;
     int k = effective_kernel(s);
     if (k == ACE_KERNEL_RESIDENT) k = ACE_KERNEL_DIRECT;
     ACE_HIP(hipMemcpyAsync(lam[0], lambdaT, bytes,
@@ -1844,8 +1864,8 @@ int ace_backward(ace_solver *s, const double *lambdaT, double *dphi0, double *de
                            s->stream));
     if (nsteps == 0) {
         ACE_HIP(hipMemsetAsync(s->gsum, 0, sizeof(double), s->stream));
-    } else if (k == ACE_KERNEL_TBLOCK && use_tb2(s)) {
-        ACE_TRY(backward_regions(s, lam, &lc));
+    } else if (k == ACE_KERNEL_TBLOCK && use_tb2(s) && adj2_shape(s, &rows, &K)) {
+        ACE_TRY(backward_regions(s, rows, K, lam, &lc));
     } else {
         ACE_TRY(backward_steps(s, k, lam, &lc));
     }

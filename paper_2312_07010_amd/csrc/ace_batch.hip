@@ -578,6 +578,15 @@ int choose(ace_batch *b, const Choice &c)
 
 const Piece *chunk_pieces(const ace_batch *b) { return b->pieces + b->n_regions + b->n_segments; }
 
+// f(first, count) for the parts of n workgroups that a launch of `threads`
+// each can hold (one, up to billions of nodes).
+template <class F>
+void in_parts(int64_t n, int threads, F &&f)
+{
+    const int64_t most = max_blocks(threads);
+    for (int64_t i = 0; i < n; i += most) f(i, (unsigned)std::min(most, n - i));
+}
+
 // f(steps, from, to) for each of an even number of rounds of at most `most`
 // steps (so that the fields end in the arena they began in), of equal length
 // to one step; only an odd number of one-step rounds stays odd.  Returns the
@@ -596,19 +605,28 @@ int64_t in_rounds(const ace_batch *b, int64_t nsteps, int most, F &&f)
     return rounds;
 }
 
+// Copies the chunks of pieces[0..n): see k_batch_copy.
+void copy_chunks(const ace_batch *b, hipStream_t st, const Piece *pieces, int n, const int64_t *packed, int to_packed,
+                 const double *src, double *dst)
+{
+    in_parts(n, kChunkThreads, [&](int64_t first, unsigned m) {
+        hipLaunchKernelGGL(k_batch_copy, dim3(m), dim3(kChunkThreads), 0, st, b->inst, pieces + first, packed,
+                           to_packed, src, dst);
+    });
+}
+
 // Every launch of a step call on stream st.
 hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
 {
     // the result of an odd number of rounds back into the first arena
-    auto copy_back = [&](const Piece *pieces, int n) {
-        hipLaunchKernelGGL(k_batch_copy, dim3(n), dim3(kChunkThreads), 0, st, b->inst, pieces, nullptr, 0, b->arena_b,
-                           b->arena_a);
-    };
+    auto copy_back = [&](const Piece *pieces, int n) { copy_chunks(b, st, pieces, n, nullptr, 0, b->arena_b, b->arena_a); };
     if (b->n_regions > 0) {
         auto go = [&](auto kern) {
             return in_rounds(b, nsteps, b->depth, [&](int S, const double *src, double *dst) {
-                hipLaunchKernelGGL(kern, dim3(b->n_regions), dim3(kBT), 0, st, b->inst, b->pieces, src, dst, b->depth,
-                                   S);
+                in_parts(b->n_regions, kBT, [&](int64_t first, unsigned n) {
+                    hipLaunchKernelGGL(kern, dim3(n), dim3(kBT), 0, st, b->inst, b->pieces + first, src, dst, b->depth,
+                                       S);
+                });
             });
         };
         const int64_t rounds = b->region == 64 ? go(k_batch_regions<4>) : go(k_batch_regions<2>);
@@ -616,8 +634,10 @@ hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
     }
     if (b->n_segments > 0) {
         const int64_t rounds = in_rounds(b, nsteps, kSegK, [&](int S, const double *src, double *dst) {
-            hipLaunchKernelGGL(k_batch_segments, dim3(b->n_segments), dim3(64), 0, st, b->inst,
-                               b->pieces + b->n_regions, src, dst, S);
+            in_parts(b->n_segments, 64, [&](int64_t first, unsigned n) {
+                hipLaunchKernelGGL(k_batch_segments, dim3(n), dim3(64), 0, st, b->inst,
+                                   b->pieces + b->n_regions + first, src, dst, S);
+            });
         });
         if (rounds & 1) copy_back(chunk_pieces(b) + b->n_chunks + b->n_chunks2, b->n_chunks1);
     }
@@ -631,9 +651,10 @@ hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
     }
     if (b->n_chunks0 > 0 && (nsteps & 1))
         copy_back(chunk_pieces(b) + b->n_chunks + b->n_chunks2 + b->n_chunks1, b->n_chunks0);
-    if (b->n_single > 0)
-        hipLaunchKernelGGL(k_batch, dim3(b->n_single), dim3(kBT), 0, st, b->inst,
-                           b->order_dev, b->arena_a, b->arena_b, nsteps, b->depth);
+    in_parts(b->n_single, kBT, [&](int64_t first, unsigned n) {
+        hipLaunchKernelGGL(k_batch, dim3(n), dim3(kBT), 0, st, b->inst, b->order_dev + first, b->arena_a, b->arena_b,
+                           nsteps, b->depth);
+    });
     return hipGetLastError();
 }
 
@@ -799,8 +820,7 @@ int ace_batch_set_all(ace_batch *b, const double *all, int where)
         BT_HIP(hipMemcpyAsync(b->arena_b, all, sizeof(double) * b->packed_total, hipMemcpyHostToDevice, b->stream));
         src = b->arena_b;
     }
-    hipLaunchKernelGGL(k_batch_copy, dim3(b->n_chunks), dim3(kChunkThreads), 0, b->stream, b->inst, chunk_pieces(b),
-                       b->packed_dev, 0, src, b->arena_a);
+    copy_chunks(b, b->stream, chunk_pieces(b), b->n_chunks, b->packed_dev, 0, src, b->arena_a);
     BT_HIP(hipGetLastError());
     if (where == ACE_HOST) BT_HIP(hipStreamSynchronize(b->stream));
     return warn;
@@ -843,10 +863,14 @@ int ace_batch_set_graphs(ace_batch *b, int enable)
 int ace_batch_monitor(ace_batch *b, double *E, double *maxn)
 {
     if (!b || !E || !maxn) return ACE_E_ARG;
-    hipLaunchKernelGGL(k_batch_monitor, dim3(b->n_chunks), dim3(kChunkThreads), 0, b->stream, b->inst,
-                       chunk_pieces(b), b->arena_a, b->partials);
-    hipLaunchKernelGGL(k_batch_monitor_sum, dim3(b->count), dim3(64), 0, b->stream, b->chunk_first, b->partials,
-                       b->trip);
+    in_parts(b->n_chunks, kChunkThreads, [&](int64_t first, unsigned n) {
+        hipLaunchKernelGGL(k_batch_monitor, dim3(n), dim3(kChunkThreads), 0, b->stream, b->inst,
+                           chunk_pieces(b) + first, b->arena_a, b->partials + 3 * first);
+    });
+    in_parts(b->count, 64, [&](int64_t first, unsigned n) {
+        hipLaunchKernelGGL(k_batch_monitor_sum, dim3(n), dim3(64), 0, b->stream, b->chunk_first + first, b->partials,
+                           b->trip + 3 * first);
+    });
     BT_HIP(hipGetLastError());
     std::vector<double> t(3 * (size_t)b->count);
     BT_HIP(hipMemcpyAsync(t.data(), b->trip, sizeof(double) * t.size(), hipMemcpyDeviceToHost,
@@ -878,8 +902,7 @@ int ace_batch_get_all(ace_batch *b, double *out, int where)
     if (!b || !out || (where != ACE_HOST && where != ACE_DEVICE)) return ACE_E_ARG;
     // gathered back to back: in the caller's memory, or in the second arena for one copy to the host
     double *dst = where == ACE_DEVICE ? out : b->arena_b;
-    hipLaunchKernelGGL(k_batch_copy, dim3(b->n_chunks), dim3(kChunkThreads), 0, b->stream, b->inst, chunk_pieces(b),
-                       b->packed_dev, 1, b->arena_a, dst);
+    copy_chunks(b, b->stream, chunk_pieces(b), b->n_chunks, b->packed_dev, 1, b->arena_a, dst);
     BT_HIP(hipGetLastError());
     if (where == ACE_HOST) {
         BT_HIP(hipMemcpyAsync(out, dst, sizeof(double) * b->packed_total, hipMemcpyDeviceToHost, b->stream));

@@ -98,7 +98,8 @@ int64_t blocks(const Shape &s, int Z)
 // in the compiled variants too)
 bool col3d_supported(const Shape &s)
 {
-    return s.d == 3 && s.M1 * s.M2 < ((int64_t)1 << 28) && s.M0 < INT32_MAX && blocks(s, 2) < INT32_MAX;
+    return s.d == 3 && s.M1 * s.M2 < ((int64_t)1 << 28) && s.M0 < INT32_MAX &&
+           blocks(s, planes_per_thread(s)) <= max_blocks(CNT);
 }
 
 int64_t col3d_partials_needed(const Shape &s) { return blocks(s, planes_per_thread(s)); }

@@ -75,6 +75,11 @@ struct Shape {
     int64_t M0, M1, M2;
 };
 
+// Workgroups of `threads` threads that one launch can hold: below 2^32 work
+// items along x.  Fields with an axis of a few nodes reach it first, since a
+// region or a column's workgroup is mostly empty there.
+constexpr int64_t max_blocks(int threads) { return (((int64_t)1 << 32) - 1) / threads; }
+
 // ---- launchers (each defined next to its kernel) ---------------------------
 
 // One step with one thread per node (neighbours through the cache).  If
@@ -177,6 +182,7 @@ hipError_t launch_step_tb2(int v, const Shape &s, const StepCoef &c, const doubl
                            double *partials, int64_t *nparts, int K, int64_t level_stride, hipStream_t st);
 int64_t tb2_blocks(int v, const Shape &s, int K);
 inline int tb2_max_depth(int v) { return TB2_TABLE[v].rows / 2 - 4; }
+bool tb2_fits(int v, const Shape &s, int K);  // within max_blocks
 int tb2_find(int rows, int rpt);  // variant index, or -1
 bool tb2_supported(const Shape &s);  // d == 2 with fewer than 2^31 nodes, and 2^30 - 1 per axis
 
@@ -212,11 +218,13 @@ struct Adj2Args {
     int64_t stride;
     int K, Sr, Sf, n_rev, last, accumulate;
 };
+constexpr int ADJ2_THREADS = 1024;  // per workgroup
 int64_t adj2_tiles(const Shape &s, int rows, int K);
 hipError_t launch_adj2(int rows, const Shape &s, const StepCoef &c, const Adj2Args &a, hipStream_t st);
 
 // 3D: one transposed step in the same form (planes of fewer than 2^28 nodes);
 // gpart: adjoint_col_blocks() sums.
+bool adjoint_col_supported(const Shape &s);
 int64_t adjoint_col_blocks(const Shape &s);
 hipError_t launch_adjoint_col(const Shape &s, const StepCoef &c, const double *mu_in, const double *phi,
                               const double *phi_end, double *mu_out, double *gpart, int last, int accumulate,
@@ -230,6 +238,7 @@ hipError_t launch_adjoint_tblock2d(const Shape &s, const StepCoef &c, const doub
 bool tblock2d_supported(const Shape &s);
 int tblock2d_max_depth();
 int64_t tblock2d_blocks(const Shape &s, int K);
+constexpr int TBLOCK2D_THREADS = 512;  // per workgroup
 
 // Adjoint step (reverse sweep) for one step n: reads lam (lambda^{n+1}),
 // phin (phi^n), phin1 (phi^{n+1}); writes lam_out (lambda^n) and per-block

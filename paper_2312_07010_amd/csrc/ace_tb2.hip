@@ -28,6 +28,11 @@ bool tb2_supported(const Shape &s)
     return tblock2d_supported(s) && s.M1 < axis && s.M2 < axis && s.M1 * s.M2 < ((int64_t)1 << 31);
 }
 
+bool tb2_fits(int v, const Shape &s, int K)
+{
+    return tb2_blocks(v, s, K) <= max_blocks(64 * TB2_TABLE[v].rows / TB2_TABLE[v].rpt);
+}
+
 int tb2_find(int rows, int rpt)
 {
     for (int v = 0; v < TB2_VARIANTS; ++v)

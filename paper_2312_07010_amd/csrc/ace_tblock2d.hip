@@ -32,7 +32,8 @@ using namespace tile2d;
 
 constexpr int BTR = 8;           // thread rows
 constexpr int BRT = BH / BTR;    // rows per thread
-constexpr int BNT = BX * BTR;    // 512 threads
+constexpr int BNT = BX * BTR;
+static_assert(BNT == TBLOCK2D_THREADS, "");
 
 // RV: the root variant (ROOT_*).
 template <int BC, bool MON, bool LEVELS, int RV>

@@ -12,6 +12,7 @@ ROOT = os.path.dirname(HERE)
 
 PRELUDE = """
 import ctypes, os, sys
+import numpy as np
 sys.path.insert(0, {root!r})
 stub = ctypes.CDLL({lib!r}, mode=ctypes.RTLD_GLOBAL)
 stub.stub_log.restype = ctypes.c_char_p

@@ -1,6 +1,8 @@
 """What the library's host code asks of the HIP runtime, and what it leaves
 behind when the runtime refuses, on a stub runtime (no GPU, kernels do
 nothing)."""
+import pytest
+
 import hip_stub
 
 
@@ -120,4 +122,58 @@ def test_checkpointed_forward_replays_graphs(tmp_path):
             assert s.step_count == (3 if after == 4 else after)
         stub.stub_fail_launch(ctypes.c_int64(-1))
         s.close()
+    """)
+
+
+@pytest.mark.parametrize("M,kernel", [((60_000_000, 1), "k_tb"), ((1, 300_000_000), "k_tb"), ((500_000_000, 1), "k_step_direct"),
+                                      ((2 ** 30, 1), "k_step_direct"), ((200_000_000, 1, 1), "k_t"), ((1, 1, 2 ** 28 - 1), "k_col3d"),
+                                      ((8, 20000, 20000), "k_tblock3d"), ((1000, 1000), "k_tb2"), ((200, 200, 200), "k_tb3")])
+def test_default_launches_hold_thin_fields(tmp_path, M, kernel):
+    """Fields with an axis of a few nodes, whose regions would be more workgroups of
+    1024 threads than one launch holds (2^32 work items): the default run, its
+    monitors and a reverse sweep launch nothing that is refused."""
+    hip_stub.run(tmp_path, f"""
+        M = {M!r}
+        s = solver(len(M), M, 1)
+        for n in (23, 3, 2, 1):
+            log()
+            s.step(n)
+            lines = log()
+            assert lines and all(x.startswith("launch") for x in lines), lines
+            if n == 23:
+                assert all({kernel!r} in x for x in lines[:1]), lines
+        E = np.zeros(16)
+        e, m = E.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), E.ctypes.data_as(ctypes.POINTER(ctypes.c_double))
+        assert L.ace_run_monitored(s._h, 23, 10, e, m) in (0, 3, 4)
+        assert not [x for x in log() if x.startswith("refused")]
+        phi = ctypes.c_void_p(L.ace_field_ptr(s._h))
+        if s.total < 2 ** 30:
+            assert L.ace_forward_ckpt(s._h, phi, ace.ACE_DEVICE, 7, 4) == 0
+            g = ctypes.c_double()
+            assert L.ace_backward(s._h, phi, phi, ctypes.byref(g), ace.ACE_DEVICE) == 0
+        assert not [x for x in log() if x.startswith("refused")]
+        s.close()
+    """)
+
+
+def test_batch_splits_launches_of_many_pieces(tmp_path):
+    """A launch of a batch with more pieces than one launch holds is split."""
+    hip_stub.run(tmp_path, """
+        b = batch([((500_000_000, 1), 1), ((300,), 2)])
+        b.set_region(64)
+        for call in (lambda: b.step(8), b.monitor, lambda: L.ace_batch_get_all(b._h, ctypes.c_void_p(4096), ace.ACE_DEVICE)):
+            log()
+            call()
+            lines = [x for x in log() if "launch" in x or "refused" in x]
+            assert lines and all(x.startswith("launch") for x in lines), lines
+        b.set_graphs(False)
+        b.step(8)
+        regions = [x for x in log() if "k_batch_regions" in x]
+        grids = [int(x.split("grid ")[1].split()[0]) for x in regions]
+        tables = [int(x.split()[-1], 16) for x in regions]
+        assert len(grids) > 2 and max(grids) * 1024 < 2 ** 32
+        per = len(grids) // 2  # (two rounds)
+        assert sum(grids[:per]) >= 500_000_000 // 62
+        assert all(t1 - t0 == 12 * g for t0, t1, g in zip(tables[:per], tables[1:per], grids))
+        b.close()
     """)
