@@ -14,15 +14,14 @@
 // Every instance carries its own shape, boundary condition, kappa, h and root
 // variant, and every update uses the same arithmetic as the single-instance
 // kernels, so each instance's result equals ace_step on that instance bit for
-// bit.  The launches of a step call are captured once per step count into a
-// HIP graph and replayed.
+// bit.  The launches of 64 rounds are captured once into a HIP graph, which the
+// step calls replay; the rest of a call is launched directly.
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
-#include <map>
 #include <new>
 #include <numeric>
 #include <string>
@@ -423,8 +422,8 @@ struct ace_batch {
     double *arena_a = nullptr, *arena_b = nullptr;
     double *trip = nullptr, *partials = nullptr;
     int use_graphs = 1;  // 0: the launches are issued directly on every step call
-    std::map<int64_t, hipGraphExec_t> graphs;
-    std::map<int64_t, hipGraph_t> graph_defs;
+    hipGraph_t graph = nullptr;  // graph_steps() steps at the current choice
+    hipGraphExec_t graph_exec = nullptr;
 };
 
 namespace {
@@ -439,11 +438,12 @@ namespace {
 void drop_graphs(ace_batch *b)
 {
     // a replay may still run on the handle's stream
-    if (!b->graphs.empty()) (void)hipStreamSynchronize(b->stream);
-    for (auto &kv : b->graphs) (void)hipGraphExecDestroy(kv.second);
-    for (auto &kv : b->graph_defs) (void)hipGraphDestroy(kv.second);
-    b->graphs.clear();
-    b->graph_defs.clear();
+    if (!b->graph_exec) return;
+    (void)hipStreamSynchronize(b->stream);
+    (void)hipGraphExecDestroy(b->graph_exec);
+    (void)hipGraphDestroy(b->graph);
+    b->graph_exec = nullptr;
+    b->graph = nullptr;
 }
 
 // What a batch's launches are made from: the choices, the instances of each
@@ -615,8 +615,8 @@ void copy_chunks(const ace_batch *b, hipStream_t st, const Piece *pieces, int n,
     });
 }
 
-// Every launch of a step call on stream st.
-hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
+// The rounds of nsteps steps of the instances in regions and in segments.
+hipError_t launch_rounds(const ace_batch *b, hipStream_t st, int64_t nsteps)
 {
     // the result of an odd number of rounds back into the first arena
     auto copy_back = [&](const Piece *pieces, int n) { copy_chunks(b, st, pieces, n, nullptr, 0, b->arena_b, b->arena_a); };
@@ -641,6 +641,13 @@ hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
         });
         if (rounds & 1) copy_back(chunk_pieces(b) + b->n_chunks + b->n_chunks2, b->n_chunks1);
     }
+    return hipGetLastError();
+}
+
+// All nsteps steps of the other instances: a launch per step, or all of them
+// in one workgroup's launch.
+hipError_t launch_others(const ace_batch *b, hipStream_t st, int64_t nsteps)
+{
     for (int i : b->by_step) {
         const BatchInst &I = b->host_inst[i];
         double *in = b->arena_a + I.off, *out = b->arena_b + I.off;
@@ -650,7 +657,8 @@ hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
         }
     }
     if (b->n_chunks0 > 0 && (nsteps & 1))
-        copy_back(chunk_pieces(b) + b->n_chunks + b->n_chunks2 + b->n_chunks1, b->n_chunks0);
+        copy_chunks(b, st, chunk_pieces(b) + b->n_chunks + b->n_chunks2 + b->n_chunks1, b->n_chunks0, nullptr, 0,
+                    b->arena_b, b->arena_a);
     in_parts(b->n_single, kBT, [&](int64_t first, unsigned n) {
         hipLaunchKernelGGL(k_batch, dim3(n), dim3(kBT), 0, st, b->inst, b->order_dev + first, b->arena_a, b->arena_b,
                            nsteps, b->depth);
@@ -658,34 +666,26 @@ hipError_t launch_batch(const ace_batch *b, hipStream_t st, int64_t nsteps)
     return hipGetLastError();
 }
 
-int get_graph(ace_batch *b, int64_t nsteps, hipGraphExec_t *out)
-{
-    auto it = b->graphs.find(nsteps);
-    if (it != b->graphs.end()) {
-        *out = it->second;
-        return ACE_OK;
-    }
-    hipGraph_t g = nullptr;
-    hipGraphExec_t e = nullptr;
-    BT_HIP(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
-    hipError_t le = launch_batch(b, b->capture, nsteps);
-    hipError_t ce = hipStreamEndCapture(b->capture, &g);
-    BT_HIP(le);
-    BT_HIP(ce);
-    hipError_t ie = hipGraphInstantiate(&e, g, nullptr, nullptr, 0);
-    if (ie != hipSuccess) {
-        (void)hipGraphDestroy(g);
-        return hip_status(ie);
-    }
-    b->graphs[nsteps] = e;
-    b->graph_defs[nsteps] = g;
-    *out = e;
-    return ACE_OK;
-}
+// Steps of the batch's one graph: 64 rounds of the regions (or of the segments
+// where there are no regions), so that its capture costs the same for any
+// number of steps a program asks for.
+int64_t graph_steps(const ace_batch *b) { return 64 * (int64_t)(b->n_regions > 0 ? b->depth : kSegK); }
 
-// Longer step calls replay a graph of this many steps (a graph holds a node
-// per round).
-constexpr int64_t kGraphSteps = 1024;
+int get_graph(ace_batch *b)
+{
+    if (b->graph_exec) return ACE_OK;
+    BT_HIP(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal));
+    hipError_t le = launch_rounds(b, b->capture, graph_steps(b));
+    hipError_t ce = hipStreamEndCapture(b->capture, &b->graph);
+    if (le == hipSuccess) le = ce;
+    if (le == hipSuccess) le = hipGraphInstantiate(&b->graph_exec, b->graph, nullptr, nullptr, 0);
+    if (le != hipSuccess) {
+        if (b->graph) (void)hipGraphDestroy(b->graph);
+        b->graph = nullptr;
+        b->graph_exec = nullptr;
+    }
+    return hip_status(le);
+}
 
 }  // namespace
 
@@ -830,17 +830,17 @@ int ace_batch_step(ace_batch *b, int64_t nsteps)
 {
     if (!b || nsteps < 0) return ACE_E_ARG;
     if (nsteps == 0) return ACE_OK;
-    while (nsteps > 0) {
-        const int64_t n = nsteps > 2 * kGraphSteps ? kGraphSteps : nsteps;
-        if (b->use_graphs) {
-            hipGraphExec_t e = nullptr;
-            BT_TRY(get_graph(b, n, &e));
-            BT_HIP(hipGraphLaunch(e, b->stream));
-        } else {
-            BT_HIP(launch_batch(b, b->stream, n));
+    if (b->n_regions + b->n_segments > 0) {
+        // (a rest of one step would be an odd round and need a copy back)
+        const int64_t P = graph_steps(b);
+        int64_t left = nsteps;
+        for (; b->use_graphs && left >= P && left != P + 1; left -= P) {
+            BT_TRY(get_graph(b));
+            BT_HIP(hipGraphLaunch(b->graph_exec, b->stream));
         }
-        nsteps -= n;
+        if (left > 0) BT_HIP(launch_rounds(b, b->stream, left));
     }
+    BT_HIP(launch_others(b, b->stream, nsteps));
     return ACE_OK;
 }
 

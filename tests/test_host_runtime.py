@@ -177,3 +177,30 @@ def test_batch_splits_launches_of_many_pieces(tmp_path):
         assert all(t1 - t0 == 12 * g for t0, t1, g in zip(tables[:per], tables[1:per], grids))
         b.close()
     """)
+
+
+def test_batch_captures_one_graph(tmp_path):
+    """Calls of many different step counts share one graph of 64 rounds, captured
+    by the first call it fits into; no call leaves an odd round to copy back."""
+    hip_stub.run(tmp_path, """
+        b = batch([((300,), 2), ((200, 300), 0), ((90, 90), 1)])
+        b.set_depth(5)
+        log()
+        b.step(319)
+        assert not [x for x in log() if x in ("instantiate", "replay")]
+        seen = []
+        for n in list(range(320, 360)) + [641, 1000, 2100, 5000]:
+            b.step(n)
+            lines = log()
+            seen += lines
+            replays = sum(x == "replay" for x in lines)
+            assert replays == n // 320 - (n % 320 == 1)
+            assert not [x for x in lines if "k_batch_copy" in x]
+            direct = sum("k_batch_regions" in x for x in lines) - 64 * ("instantiate" in lines)
+            assert direct <= 66
+        assert sum(x == "instantiate" for x in seen) == 1
+        b.set_depth(4)
+        b.step(256)
+        assert sum(x == "instantiate" for x in log()) == 1
+        b.close()
+    """)
