@@ -467,10 +467,10 @@ int ace_batch_set_depth(ace_batch *b, int depth);
  * Error: ACE_E_ARG for other values. */
 int ace_batch_set_region(ace_batch *b, int rows);
 /* Times one batch step of trial_steps steps on the current fields (which are
- * restored): first for the register regions (32, 64) at depths 2..6 and the
- * LDS-plane ones at depth 4 at the current resident limit, then for several
- * resident limits at the fastest pair.  Keeps the fastest and writes a JSON record of the timings into json
- * (capacity cap, may be NULL). */
+ * restored): for the register regions (32, 64) at depths 2..6 (and the depth
+ * the batch chose by itself, if deeper) and the LDS-plane ones at depth 4, and
+ * if these are the fastest for several resident limits.  Keeps the fastest and
+ * writes a JSON record of the timings into json (capacity cap, may be NULL). */
 int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap);
 
 /* ---- autotuner ------------------------------------------------------------ */

@@ -945,9 +945,13 @@ int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap
     const bool started = rc >= 0;  // the fields are saved
     const Choice before = choice_of(b);
     // First the region shape and depth of the region rounds at the current
-    // resident limit, then the resident limit at the chosen pair.
-    const int depths[] = {2, 3, 4, 5, 6};
-    const int regions[] = {0, 32, 64};
+    // resident limit, then, if whole instances per workgroup won (nothing else
+    // reads it), the resident limit.  The rule's own depth is among the trials
+    // also where it is beyond the others.
+    std::vector<std::pair<int, int>> shapes = {{0, 4}};  // (a whole instance per workgroup: only where all are small)
+    for (int region : {32, 64})
+        for (int depth = 2; depth <= 6; ++depth) shapes.push_back({region, depth});
+    if (!before.depth_fixed && before.region == 64 && before.depth > 6) shapes.push_back({64, before.depth});
     const int64_t limits[] = {0, 1024, 2048, 4096, RESIDENT_MAX};
     double best_ms = 1e300;
     int64_t best_lim = b->resident_limit;
@@ -981,22 +985,19 @@ int ace_batch_autotune(ace_batch *b, int64_t trial_steps, char *json, size_t cap
         return ACE_OK;
     };
     const int64_t lim0 = b->resident_limit;
-    for (int region : regions)
-        for (int depth : depths) {
-            if (rc < 0) break;
-            if (region == 0 && depth != 4) continue;  // (a whole instance per workgroup: only where all are small)
-            double ms = 0.0;
-            if ((rc = trial(lim0, depth, region, &ms)) < 0) break;
-            if (ms < best_ms) {
-                best_ms = ms;
-                best_depth = depth;
-                best_region = region;
-                best_lim = lim0;
-            }
-        }
-    for (int64_t lim : limits) {
+    for (const auto &[region, depth] : shapes) {
         if (rc < 0) break;
-        if (lim == lim0) continue;  // timed above at the chosen depth
+        double ms = 0.0;
+        if ((rc = trial(lim0, depth, region, &ms)) < 0) break;
+        if (ms < best_ms) {
+            best_ms = ms;
+            best_depth = depth;
+            best_region = region;
+        }
+    }
+    for (int64_t lim : limits) {
+        if (rc < 0 || best_region != 0) break;
+        if (lim == lim0) continue;  // timed above
         double ms = 0.0;
         if ((rc = trial(lim, best_depth, best_region, &ms)) < 0) break;
         if (ms < best_ms) {

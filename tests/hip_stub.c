@@ -120,7 +120,18 @@ int hipEventCreateWithFlags(void **e, unsigned f) { return hipEventCreate(e); }
 int hipEventDestroy(void *e) { free(e); return OK; }
 int hipEventRecord(void *e, void *s) { return OK; }
 int hipEventSynchronize(void *e) { return OK; }
-int hipEventElapsedTime(float *t, void *a, void *b) { *t = 1.0f; return OK; }
+static float g_ms = 1.0f, g_ms_step;
+void stub_elapsed(float first, float step) /* each time asked for: first, first + step, ... */
+{
+    g_ms = first;
+    g_ms_step = step;
+}
+int hipEventElapsedTime(float *t, void *a, void *b)
+{
+    *t = g_ms;
+    g_ms += g_ms_step;
+    return OK;
+}
 int hipGetDevice(int *d) { *d = 0; return OK; }
 int hipDeviceGetAttribute(int *v, int a, int d) { *v = 256; return OK; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *v, const void *f, int b, size_t m) { *v = 1; return OK; }

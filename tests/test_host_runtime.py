@@ -204,3 +204,26 @@ def test_batch_captures_one_graph(tmp_path):
         assert sum(x == "instantiate" for x in log()) == 1
         b.close()
     """)
+
+
+def test_batch_autotuner_trials(tmp_path):
+    """The batch autotuner times the depth the batch chose by itself, and resident
+    limits only where whole instances per workgroup are the fastest."""
+    hip_stub.run(tmp_path, """
+        import json
+        def tune(first, step, fixed=0):
+            b = batch([((200, 300), 0), ((90, 90), 1)])  # few regions: the rule takes depth 8
+            if fixed:
+                b.set_depth(fixed)
+            stub.stub_elapsed(ctypes.c_float(first), ctypes.c_float(step))
+            rec = json.loads(b.autotune(2))
+            b.close()
+            return [(c["region"], c["depth"]) for c in rec["candidates"]], rec["choice"]
+        trials, choice = tune(100.0, -1.0)  # the last shape is the fastest
+        assert trials[-1] == (64, 8) and len(trials) == 12
+        assert (choice["region"], choice["depth"], choice["resident_limit"]) == (64, 8, 8000)
+        trials, choice = tune(100.0, -1.0, fixed=8)
+        assert trials[-1] == (64, 6) and len(trials) == 11 and choice["depth"] == 6
+        trials, choice = tune(1.0, 1.0)  # the first one is
+        assert trials[12:] == [(0, 4)] * 4 and choice["region"] == 0
+    """)
