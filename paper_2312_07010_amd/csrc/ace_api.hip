@@ -541,13 +541,13 @@ Shape1 tb1_shape(const Shape &s)
     });
 }
 
-// All in one workgroup of up to 16 wavefronts on four SIMDs, an exchange
+// All in one workgroup of up to R1_WAVES wavefronts on four SIMDs, an exchange
 // 320 ns (256 nodes: 101 ns per step at 1 node and 16 steps; 1500: 250).
 Shape1 resident1_shape(const Shape &s)
 {
     return best_shape1([&](int i, int R, int K) {
         const int64_t waves = tb1_blocks(s, R, K);
-        if (waves > 16) return 1e300;
+        if (waves > R1_WAVES) return 1e300;
         return 320.0 / K + std::max(TB1_CHAIN[i] + 10.0, (double)((waves + 3) / 4) * TB1_ISSUE[i]);
     });
 }
@@ -645,7 +645,7 @@ void plan_launch(ace_solver *s)
     }
     if (f.d == 1 && tb1_supported(f)) {
         s->tb1 = tb1_shape(f);
-        if (f.M2 <= RESIDENT_MAX) s->res1 = resident1_shape(f);
+        if (f.M2 <= R1_MAX) s->res1 = resident1_shape(f);
         if (!s->plan_fixed)
             s->rule_kernel = s->res1.ns <= s->tb1.ns ? ACE_KERNEL_RESIDENT : ACE_KERNEL_TBLOCK;
     }

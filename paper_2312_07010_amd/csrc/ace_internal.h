@@ -193,9 +193,12 @@ bool tb1_supported(const Shape &s);  // d == 1 with fewer than 2^30 nodes
 int64_t tb1_blocks(const Shape &s, int R, int K);
 hipError_t launch_step_tb1(const Shape &s, const StepCoef &c, const double *in, double *out, double *partials,
                            int64_t *nparts, int R, int K, hipStream_t st);
-// 1D: all steps of up to RESIDENT_MAX nodes in one workgroup of tb1_blocks()
-// wavefronts (at most 16), which exchange every K steps; same contract as
-// launch_resident.
+// 1D: all steps of up to R1_MAX nodes in one workgroup of tb1_blocks()
+// wavefronts (at most R1_WAVES), which exchange every K steps; same contract as
+// launch_resident.  R1_MAX: the wavefronts' output nodes at the most nodes per
+// lane (4) and the least steps between exchanges that pay (8).
+constexpr int R1_WAVES = 16;
+constexpr int R1_MAX = R1_WAVES * (64 * 4 - 2 * 8);
 hipError_t launch_resident1(const Shape &s, const StepCoef &c, double *field, int64_t nsteps, int64_t every,
                             double *mon, int R, int K, hipStream_t st);
 

@@ -44,24 +44,22 @@ __global__ __launch_bounds__(64) void k_tb1(int n, StepCoef c0, const double *__
         if (own(first + r)) out[first + r] = v[r];
 }
 
-// All steps of a field of up to RESIDENT_MAX nodes in one workgroup: each
+// All steps of a field of up to R1_MAX nodes in one workgroup: each
 // wavefront advances its segment `K` steps in registers, then the wavefronts
 // exchange their output nodes through LDS (two buffers, one barrier).  A
 // step of the one-node-per-thread kernel (k_resident) waits for the barrier,
 // LDS and the dependent chain of a node each time, 0.35 us at 256 nodes; here
 // the chain is left.
-constexpr int R1_WAVES = 16;
-
 template <int BC, int RV, int R>
 __global__ __launch_bounds__(64 * R1_WAVES) void k_resident1(int n, StepCoef c0, double *__restrict__ field,
                                                             int64_t nsteps, int64_t every, double *__restrict__ mon,
                                                             int K)
 {
-    __shared__ double fb[2 * (RESIDENT_MAX + 1)];
+    __shared__ double fb[2 * (R1_MAX + 1)];
     __shared__ double red[3 * R1_WAVES];
     const StepCoef c = coef_vgpr<RV>(c0);
-    if (every > 0) tb1::resident<BC, RV, R, true>(n, c, field, nsteps, every, mon, K, fb, RESIDENT_MAX + 1, red);
-    else tb1::resident<BC, RV, R, false>(n, c, field, nsteps, 0, nullptr, K, fb, RESIDENT_MAX + 1, red);
+    if (every > 0) tb1::resident<BC, RV, R, true>(n, c, field, nsteps, every, mon, K, fb, R1_MAX + 1, red);
+    else tb1::resident<BC, RV, R, false>(n, c, field, nsteps, 0, nullptr, K, fb, R1_MAX + 1, red);
 }
 
 template <class F>
@@ -110,7 +108,7 @@ hipError_t launch_step_tb1(const Shape &s, const StepCoef &c, const double *in, 
 hipError_t launch_resident1(const Shape &s, const StepCoef &c, double *field, int64_t nsteps, int64_t every,
                             double *mon, int R, int K, hipStream_t st)
 {
-    if (!tb1_supported(s) || s.M2 > RESIDENT_MAX || (R != 1 && R != 2 && R != 4) || K < 1 || K >= 32 * R)
+    if (!tb1_supported(s) || s.M2 > R1_MAX || (R != 1 && R != 2 && R != 4) || K < 1 || K >= 32 * R)
         return hipErrorInvalidValue;
     const int64_t waves = tb1_blocks(s, R, K);
     if (waves > R1_WAVES) return hipErrorInvalidValue;
