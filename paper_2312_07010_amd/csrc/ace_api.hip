@@ -457,8 +457,12 @@ struct BlockModel {
     }
 };
 
-// k_tb3: fitted to launches of 64^3 to 512^3 fields at 16 plane chunks
-// (deviation 4 to 7%, 10% for the first variant).
+// k_tb3: fitted to launches of 64^3 to 512^3 fields at 16 plane chunks.  On 13
+// fields at dt <= 0.02 the five best chunks of each variant took 3 to 11% off
+// the model on the mean, and the rule's choice at most 11% more than the
+// fastest.  The root is not in the model: at dt = 0.1 and 0.2 (a Newton step)
+// launches take 40 to 50% more than it says, all variants alike, so the choice
+// stays within 3%.  (profiles/launch_models.txt)
 constexpr BlockModel TB3_MODEL[TB3_VARIANTS] = {{2, 0.93, 1.68, 1.7, 3.6}, {1, 1.78, 0, 2.7, 0.2}, {1, 1.84, 0, 2.1, 0.2},
                                                 {1, 1.33, 0, 2.6, 2.0},    {2, 1.61, 3.23, 0.1, 1.7}, {1, 1.63, 0, 1.0, 2.3},
                                                 {1, 2.19, 0, 1.5, 2.3}};
@@ -506,9 +510,13 @@ int one_step_kernel(const Shape &s)
     return ACE_KERNEL_DIRECT;
 }
 
-// k_tb2: fitted to 19 fields from 30 x 30 to 3000 x 3000 at depths 2 to 12
-// (deviation 4 to 7%); a level of the 32-row regions is bound by the rows of
-// one CU (0.28 us), so small fields take the deepest launch.
+// k_tb2: fitted to 19 fields from 30 x 30 to 3000 x 3000 at depths 2 to 12; a
+// level of the 32-row regions is bound by the rows of one CU (0.28 us), so
+// small fields take the deepest launch.  All shapes and depths deviate 3 to 10%
+// on the mean at dt <= 0.02.  The root is not in the model: at dt = 0.2 (a
+// Newton step) 401 x 283 takes 0.94 us per step for 0.69 modelled, 512^2 1.45
+// for 0.97, 1024^2 2.81 for 1.90.  The choice was the fastest shape on 14 of the
+// 19 and within 7% of it on the others.  (profiles/launch_models.txt)
 constexpr BlockModel TB2_MODEL[TB2_VARIANTS] = {{2, 0.295, 0.452, 2.7, 3.45}, {1, 0.281, 0, 2.9, 3.28},
                                                 {1, 0.622, 0, 1.2, 3.73}, {2, 0.133, 0.225, 3.8, 3.02}};
 
