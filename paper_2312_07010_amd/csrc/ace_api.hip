@@ -457,7 +457,7 @@ struct BlockModel {
     }
 };
 
-// k_tb3: fitted to launches of 64^3 to 512^3 fields at 16 plane chunks.  On 13
+// k_tb3: fitted to launches of 64^3 to 512^3 fields at 16 plane chunks.  On 14
 // fields at dt <= 0.02 the five best chunks of each variant took 3 to 11% off
 // the model on the mean, and the rule's choice at most 11% more than the
 // fastest.  The root is not in the model: at dt = 0.1 and 0.2 (a Newton step)
